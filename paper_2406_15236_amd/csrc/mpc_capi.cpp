@@ -31,17 +31,31 @@ struct BoxPlan {
   int nlz;
 };
 
+// Cells per tile: the mean particle count of a tile is at most 84 % of the
+// capacity of one collide pass, so that about one tile in 400 at 10 particles
+// per cell needs a second pass; the tiles of a row are of about equal length.
+int auto_tile_cells(double density, int l0) {
+  const double target = 0.84 * kTileCap / density;
+  const int most = (int)std::max(1.0, std::min<double>(kTileMaxCells, floor(target)));
+  const int per_row = (l0 + most - 1) / most;
+  return (l0 + per_row - 1) / per_row;
+}
+
 struct Plan {
   std::vector<BoxPlan> box;
   uint64_t ntot = 0, ctot = 0, cpad = 0;
   uint32_t nscan = 0;
   uint64_t max_tiles = 0, npblocks = 0;
+  uint64_t run_pool = 0;  // runs of all tiles' tables per state buffer
+  size_t charge = 0;      // bytes the static scratch is checked against
   size_t rec = 0;  // bytes per particle record
   bool split = false;
   // byte offsets in the workspace: records of the two state buffers and, for
   // FP64 and FP32, their logical-index arrays (the split record holds its id)
   size_t off_rec[2] = {}, off_id[2] = {};
-  size_t off_rank = 0, off_phs = 0;
+  size_t off_rank = 0, off_phs = 0, off_least = 0, off_later = 0, off_bstep = 0;
+  size_t off_tcnt[2] = {}, off_runs[2] = {}, off_rhead[2] = {}, off_rnext[2] = {}, off_toff = 0,
+         off_tblk = 0;
   size_t off_key = 0, off_perm = 0, off_hist = 0, off_offset = 0, off_scan = 0, off_ctrl = 0,
          off_boxes = 0, off_tiles = 0, off_pblocks = 0, off_partials = 0, off_vmean = 0,
          off_draws = 0;
@@ -98,6 +112,38 @@ int validate(const mpc_params* p, int32_t nbox, std::string* why) {
   return MPC_OK;
 }
 
+// What a call of the allocation-free entry point is charged against the limit
+// of its scratch: state and ids 56 B per particle and buffer, 10 B per
+// particle and 8 B per cell for binning, 32 B of draws per cell, tables.  The
+// limit is part of the interface, so it does not follow the workspace layout.
+size_t scratch_charge(const mpc_params* p, const Plan& P) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) { off = align256(off + bytes); };
+  const size_t nbox = P.box.size();
+  uint64_t tiles = 0;
+  for (size_t b = 0; b < nbox; ++b)
+    tiles += (uint64_t)p[b].L[1] * P.box[b].nlz * ((p[b].L[0] + kMinTileCells - 1) / kMinTileCells);
+  for (int k = 0; k < 2; ++k) {
+    take(P.rec * P.ntot);
+    if (!P.split) take(4 * P.ntot);
+  }
+  take(4 * P.ntot);
+  take(4 * P.ntot);
+  take(2 * P.ntot);
+  take(4 * P.cpad);
+  take(4 * (P.cpad + 1));
+  take(4 * (size_t)P.nscan);
+  take(32);
+  take(280 * nbox);
+  take(20 * tiles);
+  take(8 * P.npblocks);
+  take(32 * P.npblocks);
+  take(24 * nbox);
+  take(32 * P.cpad);
+  if (p[0].flags & MPC_WALLS_Z) take(48 * P.cpad);
+  return off;
+}
+
 int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   int rc = validate(p, nbox, why);
   if (rc) return rc;
@@ -122,7 +168,11 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
     P.box[b].nlz = nlz;
     P.ntot += P.box[b].n;
     P.ctot += P.box[b].ncell;
-    P.max_tiles += (uint64_t)q.L[1] * nlz * ((q.L[0] + kMinTileCells - 1) / kMinTileCells);
+    const uint64_t rows = (uint64_t)q.L[1] * nlz;
+    const int ta = auto_tile_cells(q.density, q.L[0]);
+    const uint64_t auto_tiles = rows * ((q.L[0] + ta - 1) / ta);
+    P.max_tiles += std::max(auto_tiles, rows * ((q.L[0] + kMinTileCells - 1) / kMinTileCells));
+    P.run_pool += auto_tiles * kMaxRuns;
     P.npblocks += (P.box[b].n + kPartBlock - 1) / kPartBlock;
   }
   P.nscan = (uint32_t)((P.ctot + kScanBlock - 1) / kScanBlock);
@@ -144,20 +194,44 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
     P.off_rec[s] = take(P.rec * P.ntot);
     P.off_id[s] = P.split ? 0 : take(4 * P.ntot);
   }
+  // the binning export and the run lists of the tiles share their memory:
+  // the export is formed from the last step's input when it is asked for, and
+  // the next step then sorts the state by tile again
+  const size_t shared0 = off;
   P.off_key = take(4 * P.ntot);
   P.off_perm = take(4 * P.ntot);
   P.off_rank = take(2 * P.ntot);
   P.off_hist = take(4 * P.cpad);
   P.off_offset = take(4 * (P.cpad + 1));
   P.off_scan = take(4 * (size_t)P.nscan);
+  const size_t shared1 = off;
+  off = shared0;
+  // a tiling with more tiles than the automatic one has shorter run tables,
+  // of at least one run a tile
+  P.run_pool = std::max<uint64_t>(P.run_pool, P.max_tiles);
+  for (int k = 0; k < 2; ++k) {
+    P.off_tcnt[k] = take(8 * P.max_tiles);
+    P.off_runs[k] = take(sizeof(Run) * P.run_pool);
+    P.off_rhead[k] = take(4 * P.run_pool);
+    P.off_rnext[k] = take(4 * P.ntot);
+  }
+  P.off_tblk = take(4 * (P.max_tiles / kTileBlock + 1));
+  off = std::max(off, shared1);
+  P.off_toff = take(4 * P.max_tiles);
   P.off_ctrl = take(sizeof(Ctrl));
   P.off_boxes = take(sizeof(BoxDev) * nbox);
+  P.off_bstep = take(sizeof(BoxStep) * nbox);
   P.off_tiles = take(sizeof(Tile) * P.max_tiles);
   P.off_pblocks = take(sizeof(PBlock) * P.npblocks);
   P.off_partials = take(sizeof(double) * 4 * P.npblocks);
   P.off_vmean = take(sizeof(double) * 3 * nbox);
-  P.off_draws = take(sizeof(CellDraw) * P.cpad);
+  P.off_draws = take(sizeof(double4) * P.cpad);
+  if (p[0].flags & MPC_MBS) {
+    P.off_least = take(4 * P.cpad);
+    P.off_later = take(sizeof(Attempt) * (P.cpad / 4));
+  }
   P.off_phs = (p[0].flags & MPC_WALLS_Z) ? take(sizeof(PhantomSums) * P.cpad) : 0;
+  P.charge = scratch_charge(p, P);
   P.total = off;
   return MPC_OK;
 }
@@ -166,7 +240,10 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
 // one call lives here.  Each device holds its own copy from module load to
 // process end; host code reaches it only through the address that
 // hipGetSymbolAddress returns for the current device.
-constexpr size_t kScratchBytes = (size_t)256 << 20;
+constexpr size_t kScratchLimit = (size_t)256 << 20;  // see scratch_charge
+// the workspace of a call within the limit: at most 5/3 of its charge (sparse
+// boxes, where the cells' draws and the tiles' tables dominate)
+constexpr size_t kScratchBytes = (size_t)432 << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex scratch_mu;
@@ -217,6 +294,8 @@ struct mpc_sim {
   uint32_t cur = 0;
   bool keys_valid = false;
   bool have_binning = false;
+  bool binning_ready = false;  // the binning export holds the last step's binning
+  std::vector<char> stepped;   // per box: its slots are the output of a step of this tiling
   bool use_graph = true;
   int32_t graph_steps = 1;         // steps per replay of the chunk graph
   bool graph_ready = false;
@@ -245,17 +324,10 @@ int hip_fail(mpc_sim* s, hipError_t e, const char* where) {
     if (_e != hipSuccess) return hip_fail((s), _e, #expr); \
   } while (0)
 
-// Cells per tile so that a tile's mean particle count is ~95 % of the LDS
-// capacity of one pass (larger tiles amortise the per-tile work; the Poisson
-// excess of a full tile goes to a second pass).
-int auto_tile_cells(double density) {
-  const double target = 0.95 * kTileCap / density;
-  return (int)std::max<double>(kMinTileCells, std::min<double>(kTileMaxCells, floor(target)));
-}
-
 // Tiles are runs of at most T consecutive cells inside one row (fixed y and z),
-// so a tile's particles land in the rows y +- 1, z +- 1 of the next step and
-// its next-step histogram fits a small on-chip window.  Tiles are listed so
+// so a tile's particles land in three tiles of nine rows of the next step
+// (others are handled one by one).  Tiles are numbered in key order, which is
+// the order of their particles in memory, and listed (processed) so
 // that the persistent grid, which hands each XCD a contiguous part of the list,
 // keeps cells that exchange particles on one XCD at the same time: each XCD
 // gets a slab of z planes, walked in blocks of `yblock` rows with z inside a
@@ -271,15 +343,18 @@ void build_tiles(mpc_sim* s) {
   std::vector<Keyed> keyed;
   const int yb = std::max(1, s->yblock);
   for (size_t b = 0; b < s->boxes.size(); ++b) {
-    const BoxDev& B = s->boxes[b];
-    int T = s->tile_override ? s->tile_override : auto_tile_cells(B.density);
-    T = std::max(kMinTileCells, std::min(kTileMaxCells, T));
+    BoxDev& B = s->boxes[b];
+    const int T = s->tile_override ? s->tile_override : auto_tile_cells(B.density, B.L[0]);
+    B.T = (uint32_t)T;
+    B.ntx = (uint32_t)((B.L[0] + T - 1) / T);
+    B.tbase = (uint32_t)keyed.size();
     const uint64_t L0 = (uint64_t)B.L[0], L1 = (uint64_t)B.L[1];
     for (uint64_t cz = 0; cz < (uint64_t)B.nlz; ++cz) {
       for (uint64_t cy = 0; cy < L1; ++cy) {
         for (uint64_t cx = 0; cx < L0; cx += T) {
           Tile t;
           t.c0 = B.cbase + (uint32_t)((cz * L1 + cy) * L0 + cx);
+          t.tid = (uint32_t)keyed.size();
           t.nc = (uint16_t)std::min<uint64_t>(T, L0 - cx);
           t.box = (uint16_t)b;
           t.x0 = (uint32_t)cx;
@@ -302,17 +377,23 @@ void build_tiles(mpc_sim* s) {
                    [](const Keyed& a, const Keyed& b) { return a.k < b.k; });
   for (const Keyed& kt : keyed) s->tiles.push_back(kt.t);
   s->L.ntiles = (uint32_t)s->tiles.size();
+  s->dev.ntile = s->L.ntiles;
+  s->dev.maxr = (uint32_t)std::min<uint64_t>(kMaxRuns, s->plan.run_pool / s->tiles.size());
+  s->keys_valid = false;  // the run lists belong to a tiling
+  s->stepped.assign(s->boxes.size(), 0);
   // default persistent grid: at most 8 one-wave workgroups per CU in flight
   // (more waves per XCD evict the gathered rows from L2), oversubscribed 2x
   // so that freed slots take the remaining workgroups (tail balance)
   uint32_t g = s->grid_override ? (uint32_t)s->grid_override
-                                : (uint32_t)(2 * s->num_cu * std::min(8, std::max(1, s->occupancy)));
+                                : (uint32_t)(4 * s->num_cu * std::max(1, s->occupancy));
   g = std::max<uint32_t>(1, std::min<uint32_t>(g, s->L.ntiles));
   s->L.collide_grid = g;
 }
 
 int upload_tables(mpc_sim* s) {
   HIPCHK(s, hipMemcpyAsync(s->dev.tiles, s->tiles.data(), sizeof(Tile) * s->tiles.size(),
+                           hipMemcpyHostToDevice, s->L.stream));
+  HIPCHK(s, hipMemcpyAsync(s->dev.boxes, s->boxes.data(), sizeof(BoxDev) * s->boxes.size(),
                            hipMemcpyHostToDevice, s->L.stream));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
   return MPC_OK;
@@ -337,6 +418,10 @@ int check_sticky(mpc_sim* s) {
              "it was streamed but not collided";
     return MPC_ERANGE;
   }
+  if (c.err & kErrDraws) {
+    s->err = "the list of repeated thermostat draws of a block of cells is full";
+    return MPC_ERANGE;
+  }
   if (c.err & kErrFixRange) {
     s->err = "a fixed-point summand was outside |x| < 2^37 (cell units)";
     return MPC_ERANGE;
@@ -344,23 +429,23 @@ int check_sticky(mpc_sim* s) {
   return MPC_OK;
 }
 
-// One step's launches (scan, scatter, collide, advance) on `st`.
+// One step's launches on `st`.
 hipError_t enqueue_step(mpc_sim* s, hipStream_t st) {
   Launch l = s->L;
   l.stream = st;
-  hipError_t e;
-  if ((e = launch_scan(s->dev, l)) != hipSuccess) return e;
-  if ((e = launch_phantoms(s->dev, l)) != hipSuccess) return e;
-  if ((e = launch_scatter(s->dev, l)) != hipSuccess) return e;
-  if ((e = launch_collide(s->dev, l)) != hipSuccess) return e;
-  return launch_advance(s->dev, l);
+  const hipError_t e = launch_prepare(s->dev, l);
+  return e != hipSuccess ? e : launch_collide(s->dev, l);
 }
 
+// A state set from outside (or a binning export, which takes the memory of
+// the run lists): sort by tile of the next step into the other buffer.
 int ensure_keys(mpc_sim* s) {
   if (s->keys_valid) return MPC_OK;
-  HIPCHK(s, launch_zero_u32(s->dev.hist, s->plan.cpad, s->L.stream));
-  HIPCHK(s, launch_key_hist(s->dev, s->L));
+  HIPCHK(s, launch_sort(s->dev, s->L, s->cur, s->cur ^ 1u));
+  s->cur ^= 1u;
+  HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   s->keys_valid = true;
+  s->binning_ready = false;
   return MPC_OK;
 }
 
@@ -450,39 +535,49 @@ int read_ids(mpc_sim* s, const StatePtrs& S, uint64_t p0, std::vector<uint32_t>&
   return MPC_OK;
 }
 
-int obs_all(mpc_sim* s, std::vector<double>& P, std::vector<double>& E,
-            std::vector<double>& K) {
-  const size_t nbox = s->boxes.size();
-  const size_t npb = s->pblocks.size();
-  std::vector<double> part(4 * npb);
-  HIPCHK(s, launch_obs_pass1(s->dev, s->L));
-  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials, sizeof(double) * 4 * npb,
-                           hipMemcpyDeviceToHost, s->L.stream));
-  HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  P.assign(3 * nbox, 0.0);
-  E.assign(nbox, 0.0);
-  K.assign(nbox, 0.0);
-  std::vector<double> vm(3 * nbox);
-  for (size_t b = 0; b < nbox; ++b) {
-    Neumaier a[4];
-    for (uint32_t q = s->box_pb0[b]; q < s->box_pb0[b + 1]; ++q)
-      for (int k = 0; k < 4; ++k) a[k].add(part[4 * q + k]);
-    for (int k = 0; k < 3; ++k) P[3 * b + k] = a[k].val();
-    E[b] = a[3].val();
-    const double M = (double)s->boxes[b].np * s->boxes[b].mass;
-    for (int k = 0; k < 3; ++k) vm[3 * b + k] = P[3 * b + k] / M;
+// Cells per tile of the order of the observables' sums: a mean of 95 % of its
+// passes' capacity.
+uint32_t obs_tile_cells(double density) {
+  const double target = 0.95 * kObsPass / density;
+  return (uint32_t)std::max<double>(kMinTileCells, std::min<double>(kTileMaxCells, floor(target)));
+}
+
+// Momentum P[3], kinetic energy E and relative kinetic energy K of one box.
+int obs_box(mpc_sim* s, int32_t box, double* P, double* E, double* K) {
+  const BoxDev& B = s->boxes[box];
+  const uint32_t pb0 = s->box_pb0[box], npb = s->box_pb0[box + 1] - pb0;
+  std::vector<double> part(4 * (size_t)npb);
+  uint32_t* order = nullptr;
+  if (s->form == MPC_FP64 && s->stepped[box]) {
+    // the chains of the buffer that the next step writes are free until then
+    order = s->dev.rnext[s->cur ^ 1u];
+    s->binning_ready = false;
+    HIPCHK(s, launch_obs_order(s->dev, s->L, (uint32_t)box, (uint32_t)B.L[1] * (uint32_t)B.nlz,
+                               (uint32_t)B.L[0], s->cur, obs_tile_cells(B.density), order));
   }
-  HIPCHK(s, hipMemcpyAsync(s->vmean, vm.data(), sizeof(double) * 3 * nbox, hipMemcpyHostToDevice,
+  HIPCHK(s, launch_obs_pass1(s->dev, s->L, pb0, npb, s->cur, order));
+  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials + 4 * (size_t)pb0,
+                           sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
+  HIPCHK(s, hipStreamSynchronize(s->L.stream));
+  Neumaier a[4];
+  for (uint32_t q = 0; q < npb; ++q)
+    for (int k = 0; k < 4; ++k) a[k].add(part[4 * (size_t)q + k]);
+  const double M = (double)B.np * B.mass;
+  double vm[3];
+  for (int k = 0; k < 3; ++k) {
+    P[k] = a[k].val();
+    vm[k] = P[k] / M;
+  }
+  *E = a[3].val();
+  HIPCHK(s, hipMemcpyAsync(s->vmean + 3 * (size_t)box, vm, sizeof vm, hipMemcpyHostToDevice,
                            s->L.stream));
-  HIPCHK(s, launch_obs_pass2(s->dev, s->L, s->vmean));
-  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials, sizeof(double) * 4 * npb,
-                           hipMemcpyDeviceToHost, s->L.stream));
+  HIPCHK(s, launch_obs_pass2(s->dev, s->L, pb0, npb, s->cur, s->vmean));
+  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials + 4 * (size_t)pb0,
+                           sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  for (size_t b = 0; b < nbox; ++b) {
-    Neumaier a;
-    for (uint32_t q = s->box_pb0[b]; q < s->box_pb0[b + 1]; ++q) a.add(part[4 * q]);
-    K[b] = a.val();
-  }
+  Neumaier k2;
+  for (uint32_t q = 0; q < npb; ++q) k2.add(part[4 * (size_t)q]);
+  *K = k2.val();
   return MPC_OK;
 }
 
@@ -545,6 +640,15 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->dev.hist = (uint32_t*)(ws + P.off_hist);
   s->dev.offset = (uint32_t*)(ws + P.off_offset);
   s->dev.scan_blk = (uint32_t*)(ws + P.off_scan);
+  for (int k = 0; k < 2; ++k) {
+    s->dev.tcnt[k] = (unsigned long long*)(ws + P.off_tcnt[k]);
+    s->dev.runs[k] = (Run*)(ws + P.off_runs[k]);
+    s->dev.rhead[k] = (uint32_t*)(ws + P.off_rhead[k]);
+    s->dev.rnext[k] = (uint32_t*)(ws + P.off_rnext[k]);
+  }
+  s->dev.toff = (uint32_t*)(ws + P.off_toff);
+  s->dev.tblk = (uint32_t*)(ws + P.off_tblk);
+  s->dev.bstep = (BoxStep*)(ws + P.off_bstep);
   s->dev.ctrl = (Ctrl*)(ws + P.off_ctrl);
   s->dev.boxes = (BoxDev*)(ws + P.off_boxes);
   s->dev.tiles = (Tile*)(ws + P.off_tiles);
@@ -552,7 +656,15 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->dev.partials = (double*)(ws + P.off_partials);
   s->dev.ntot = (uint32_t)P.ntot;
   s->vmean = (double*)(ws + P.off_vmean);
-  s->dev.draws = (CellDraw*)(ws + P.off_draws);
+  s->dev.draws = (double4*)(ws + P.off_draws);
+  if (p[0].flags & MPC_MBS) {
+    s->dev.least = (uint32_t*)(ws + P.off_least);
+    s->dev.later = (Attempt*)(ws + P.off_later);
+  }
+  // blocks of the draws: large ones let one wavefront make the chains of many
+  // cells, small ones keep a small box on many compute units
+  s->dev.drawb = kMinDrawBlock;
+  while (s->dev.drawb < kMaxDrawBlock && P.ctot / (2 * s->dev.drawb) >= 1024) s->dev.drawb *= 2;
   s->dev.phs = (p[0].flags & MPC_WALLS_Z) ? (PhantomSums*)(ws + P.off_phs) : nullptr;
 
   // boxes
@@ -634,15 +746,8 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
     return code;
   };
   if ((rc = upload_tables(s))) return fail(rc);
-  if (hipMemcpyAsync(s->dev.boxes, s->boxes.data(), sizeof(BoxDev) * s->boxes.size(),
+  if (hipMemcpyAsync(s->dev.pblocks, s->pblocks.data(), sizeof(PBlock) * s->pblocks.size(),
                      hipMemcpyHostToDevice, s->L.stream) != hipSuccess ||
-      hipMemcpyAsync(s->dev.pblocks, s->pblocks.data(), sizeof(PBlock) * s->pblocks.size(),
-                     hipMemcpyHostToDevice, s->L.stream) != hipSuccess ||
-      launch_zero_u32(s->dev.hist, P.cpad, s->L.stream) != hipSuccess ||
-      launch_zero_u32(s->dev.perm, P.ntot, s->L.stream) != hipSuccess ||
-      launch_zero_u32(s->dev.key, P.ntot, s->L.stream) != hipSuccess ||
-      launch_zero_u32((uint32_t*)s->dev.rank, (P.ntot + 1) / 2, s->L.stream) != hipSuccess ||
-      launch_zero_u32(s->dev.offset, P.cpad + 1, s->L.stream) != hipSuccess ||
       launch_set_ctrl(s->dev, s->L, 0, 0, s->R, 1) != hipSuccess ||
       hipStreamSynchronize(s->L.stream) != hipSuccess)
     return fail(MPC_EHIP);
@@ -716,6 +821,8 @@ int mpc_step(mpc_sim* s, int64_t nsteps) {
   }
   advance_mirror(s, nsteps);
   s->have_binning = true;
+  s->binning_ready = false;
+  s->stepped.assign(s->boxes.size(), 1);
   return MPC_OK;
 }
 
@@ -734,21 +841,15 @@ int mpc_step_profiled(mpc_sim* s, int64_t nsteps, mpc_kernel_times* acc) {
   int kinds_prologue = 0;
   HIPCHK(s, mark());
   if (!s->keys_valid) {
-    HIPCHK(s, launch_zero_u32(s->dev.hist, s->plan.cpad, st));
-    HIPCHK(s, launch_key_hist(s->dev, s->L));
-    s->keys_valid = true;
+    int rc = ensure_keys(s);
+    if (rc) return rc;
     HIPCHK(s, mark());
     kinds_prologue = 1;
   }
   for (int64_t k = 0; k < nsteps; ++k) {
-    HIPCHK(s, launch_scan(s->dev, s->L));
-    HIPCHK(s, launch_phantoms(s->dev, s->L));
-    HIPCHK(s, mark());
-    HIPCHK(s, launch_scatter(s->dev, s->L));
+    HIPCHK(s, launch_prepare(s->dev, s->L));
     HIPCHK(s, mark());
     HIPCHK(s, launch_collide(s->dev, s->L));
-    HIPCHK(s, mark());
-    HIPCHK(s, launch_advance(s->dev, s->L));
     HIPCHK(s, mark());
   }
   HIPCHK(s, hipStreamSynchronize(st));
@@ -765,16 +866,15 @@ int mpc_step_profiled(mpc_sim* s, int64_t nsteps, mpc_kernel_times* acc) {
   }
   for (int64_t k = 0; k < nsteps; ++k) {
     acc->scan_ms += span();
-    acc->scatter_ms += span();
     acc->collide_ms += span();
-    acc->other_ms += span();
     acc->scan_launches += 1;
-    acc->scatter_launches += 1;
     acc->collide_launches += 1;
   }
   for (hipEvent_t x : ev) (void)hipEventDestroy(x);
   advance_mirror(s, nsteps);
   s->have_binning = true;
+  s->binning_ready = false;
+  s->stepped.assign(s->boxes.size(), 1);
   return MPC_OK;
 }
 
@@ -802,6 +902,7 @@ int mpc_set_step(mpc_sim* s, uint64_t step) {
   s->step = step;
   s->keys_valid = false;
   s->have_binning = false;
+  s->binning_ready = false;
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
   return MPC_OK;
@@ -811,12 +912,11 @@ int mpc_init_state(mpc_sim* s, uint64_t init_seed) {
   if (!s) return MPC_EINVAL;
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 1));
   HIPCHK(s, launch_init_state(s->dev, s->L, init_seed));
-  std::vector<double> P, E, K;
   // mean of each box
   const size_t nbox = s->boxes.size();
   const size_t npb = s->pblocks.size();
   std::vector<double> part(4 * npb);
-  HIPCHK(s, launch_obs_pass1(s->dev, s->L));
+  HIPCHK(s, launch_obs_pass1(s->dev, s->L, 0, (uint32_t)npb, s->cur, nullptr));
   HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials, sizeof(double) * 4 * npb,
                            hipMemcpyDeviceToHost, s->L.stream));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
@@ -834,6 +934,8 @@ int mpc_init_state(mpc_sim* s, uint64_t init_seed) {
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
   s->keys_valid = false;
   s->have_binning = false;
+  s->binning_ready = false;
+  s->stepped.assign(s->boxes.size(), 0);
   return MPC_OK;
 }
 
@@ -918,6 +1020,8 @@ int mpc_set_state(mpc_sim* s, int32_t box, const double* x, const double* v, int
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
   s->keys_valid = false;
   s->have_binning = false;
+  s->binning_ready = false;
+  s->stepped[box] = 0;
   return MPC_OK;
 }
 
@@ -1053,15 +1157,15 @@ int mpc_observables(mpc_sim* s, int32_t box, mpc_obs* out) {
   if (!s || !out || box < 0 || box >= (int32_t)s->boxes.size()) return MPC_EINVAL;
   int rc = mpc_sync(s);
   if (rc) return rc;
-  std::vector<double> P, E, K;
-  if ((rc = obs_all(s, P, E, K))) return rc;
+  double P[3], E, K;
+  if ((rc = obs_box(s, box, P, &E, &K))) return rc;
   const BoxDev& B = s->boxes[box];
   const double a = s->params[box].a;
   out->step = s->step;
   out->n = B.np;
-  for (int k = 0; k < 3; ++k) out->P[k] = P[3 * box + k] * a;
-  out->E = E[box] * a * a;
-  out->T = B.np > 1 ? K[box] / (3.0 * (double)(B.np - 1)) * a * a : 0.0;
+  for (int k = 0; k < 3; ++k) out->P[k] = P[k] * a;
+  out->E = E * a * a;
+  out->T = B.np > 1 ? K / (3.0 * (double)(B.np - 1)) * a * a : 0.0;
   out->mass_total = (double)B.np * B.mass;
   if (!isfinite(out->E) || !isfinite(out->P[0]) || !isfinite(out->P[1]) || !isfinite(out->P[2])) {
     s->err = "non-finite observables";
@@ -1081,7 +1185,12 @@ int mpc_get_binning(mpc_sim* s, int32_t box, uint32_t* key, uint32_t* perm, uint
   // the last step read the buffer that is not current; its ids give the
   // logical order before that step
   const StatePtrs& Sin = s->dev.S[s->cur ^ 1u];
-  HIPCHK(s, launch_canon_perm(s->dev, s->L, Sin));
+  if (!s->binning_ready) {
+    s->keys_valid = false;  // the export takes the memory of the run lists
+    HIPCHK(s, launch_binning(s->dev, s->L, Sin, s->step - 1));
+    HIPCHK(s, launch_canon_perm(s->dev, s->L, Sin));
+    s->binning_ready = true;
+  }
   const BoxDev& B = s->boxes[box];
   std::vector<uint32_t> off(B.nc + 1), pm(B.np), lid(B.np);
   if ((rc = copy_d2h(s, s->dev.offset, B.cbase, off))) return rc;
@@ -1163,6 +1272,8 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
     s->step = step0;
     s->keys_valid = false;
     s->have_binning = false;
+    s->binning_ready = false;
+    s->stepped.assign(s->boxes.size(), 0);
     HIPCHK(s, launch_set_ctrl(s->dev, s->L, step0, cur0, s->R, 1));
     return MPC_OK;
   };
@@ -1261,7 +1372,7 @@ int mpc_run_noalloc(const mpc_params* p, double* x, double* v, int64_t n, uint64
   int rc = make_plan(p, 1, P, &why);
   if (rc) return rc;
   if ((uint64_t)n != P.box[0].n) return MPC_EINVAL;
-  if (P.total > kScratchBytes) return MPC_ERANGE;
+  if (P.charge > kScratchLimit || P.total > kScratchBytes) return MPC_ERANGE;
   void* ws = nullptr;
   if ((rc = scratch_of_current_device(&ws))) return rc;
   mpc_sim* s = nullptr;

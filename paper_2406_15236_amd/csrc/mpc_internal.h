@@ -10,16 +10,25 @@ constexpr int kThreads = 256;               // threads per workgroup (4 wave64)
 constexpr int kCollideThreads = 64;         // collide workgroup: one wave64
 constexpr int kTileCap = 256;               // particles held in LDS per tile pass
 constexpr int kTileMaxCells = 32;           // cells per collide tile (< kCollideThreads)
+constexpr int kObsPass = 256;               // particles per pass of the observables' order
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
 constexpr int kPartBlock = kThreads * 4;    // particles per block of per-particle kernels
+constexpr int kMaxRuns = 32;                // runs in a tile's table (more go to chains)
+constexpr int kGroups = 27;                 // next-step tiles of a pass: 3 per row, 9 rows
+constexpr int kTileBlock = kThreads * 4;    // tiles per block of the tile prefix
+constexpr uint32_t kTileDirect = 16384;     // most tiles with a prefix in one launch
+constexpr uint32_t kMinDrawBlock = 256, kMaxDrawBlock = 2048;  // cells per block of the draws
+constexpr uint32_t kNeverAccepted = 1024;   // more particles than a cell can hold
+constexpr uint32_t kNoSlot = 0xffffffffu;
 
 // Random-stream tags (counter word 3); counter = {draw, id, step, tag}.
 enum : uint32_t { kTagShift = 1, kTagAxis = 2, kTagThermo = 3, kTagPhantom = 4,
                   kTagInitPos = 5, kTagInitVel = 6 };
 
 // Sticky error bits in Ctrl::err.
-enum : uint32_t { kErrKey = 1u, kErrCellOverflow = 2u, kErrFixRange = 4u };
+enum : uint32_t { kErrKey = 1u, kErrCellOverflow = 2u, kErrFixRange = 4u,
+                 kErrDraws = 8u };
 
 enum : int { kFormF64 = 0, kFormF32 = 1, kFormSplit = 2 };
 
@@ -51,10 +60,20 @@ struct BoxDev {
   uint32_t le;         // periodic z with Lees-Edwards shear
   float leuf;          // leu as float
   double leu;          // Lees-Edwards: x velocity of the image above the box
+  uint32_t tbase;      // first tile (key order)
+  uint32_t T, ntx;     // cells per tile, tiles per row
+  uint32_t pad1;
+};
+
+struct BoxStep {       // per box and step, written by the prepare kernel
+  double s[3], sn[3];  // lattice shifts of t and t + 1
+  double d1, d2;       // Lees-Edwards offsets at the end of step t and t + 1
+  int32_t w[2];        // first row (y, z) of the window of next-step rows
 };
 
 struct Tile {          // one collide work item: cells [c0, c0 + nc) of box `box`
   uint32_t c0;         // first global cell key
+  uint32_t tid;        // index in key order (run lists, counters, output positions)
   uint16_t nc;
   uint16_t box;
   uint32_t x0, y0, z0; // coordinates of the first cell in its box (z0: key layer)
@@ -70,12 +89,19 @@ struct Ctrl {          // device-resident step state, read by every kernel
   uint32_t cur;        // which state buffer holds the current state (flips every step)
   uint32_t err;        // sticky error bits
   int32_t reorder;     // R
-  uint32_t pad[3];
+  uint32_t done;       // workgroups of the running collide that have finished
+  uint32_t pad[2];
 };
 
-struct CellDraw {       // random draws of one cell for the current step
-  double n[3];         // rotation axis
-  double Ek;           // thermostat target energy, 0 = no scaling
+struct Run {           // consecutive slots of the state that belong to one tile
+  uint32_t start, count;
+};
+
+struct Attempt {        // of a cell's gamma draw
+  double z;
+  uint16_t least;      // smallest particle count that accepts it
+  uint16_t next;       // the cell's next attempt in the segment; 0: none
+  uint32_t pad;
 };
 
 struct PhantomSums {   // phantom particles of an occupied wall-cut cell
@@ -109,11 +135,11 @@ constexpr size_t rec_bytes(int form) {
   return form == kFormF64 ? sizeof(RecF64) : (form == kFormF32 ? sizeof(RecF32) : sizeof(RecSplit));
 }
 
-// One state buffer.  Every step writes the state into the other buffer, cell
-// by cell of the current step, and inside the particles of one tile pass
-// grouped by their cell of the next step (so that the next step gathers
-// contiguous runs).  The logical index of slot i (its index in the caller's
-// order, renumbered to the (cell, index) order on reorder steps) is
+// One state buffer.  Every step writes the state into the other buffer, tile
+// by tile of the current step in key order, and inside the particles of one
+// tile pass grouped by their tile of the next step (so that the next step
+// gathers contiguous runs).  The logical index of slot i (its index in the
+// caller's order, renumbered to the (cell, index) order on reorder steps) is
 // id[i * id_stride]: an array of its own for FP64 and FP32 (stride 1), the id
 // word of the record for the split form (stride 8).
 struct StatePtrs {
@@ -124,19 +150,34 @@ struct StatePtrs {
 
 struct Dev {           // device pointers carved from the workspace
   StatePtrs S[2];
+  // binning export (shares its memory with the run lists below)
   uint32_t* key;       // cell key per particle (storage order)
   uint16_t* rank;      // rank of the particle among those counted for its key
   uint32_t* perm;      // position in (cell, any order) -> stored slot
-  uint32_t* hist;      // particles per cell of the next step; zeroed by the scan
+  uint32_t* hist;      // particles per cell
   uint32_t* offset;    // exclusive prefix, ncell + 1
   uint32_t* scan_blk;  // per scan-block totals
+  // run lists of the tiles, one set per state buffer
+  unsigned long long* tcnt[2];  // particles << 32 | runs
+  Run* runs[2];        // maxr per tile
+  uint32_t* rhead[2];  // maxr chain heads per tile (tiles with more runs)
+  uint32_t* rnext[2];  // next slot of a chain, per slot
+  uint32_t* toff;      // first output slot of each tile
+  uint32_t* tblk;      // particles per block of tiles
+  uint32_t maxr, ntile;
+  BoxStep* bstep;
   Ctrl* ctrl;
   BoxDev* boxes;
   Tile* tiles;
   PBlock* pblocks;
   double* partials;    // per-block observable partial sums
-  CellDraw* draws;     // per-cell draws of the current step (written by the scan)
-  PhantomSums* phs;    // walls only: phantom sums of wall-cut cells (written by the scan)
+  double4* draws;      // per cell: rotation axis, z of attempt 0 of the gamma draw
+  // thermostat: per cell, the least count that accepts attempt 0 and the first
+  // of its later attempts << 16 in the block's segment of drawb / 4 attempts
+  uint32_t* least;
+  Attempt* later;
+  uint32_t drawb;      // cells per block of the draws
+  PhantomSums* phs;    // walls only: phantom sums of wall-cut cells
   uint32_t ntot;       // particles over all boxes (bound of every particle index)
 };
 
@@ -157,17 +198,22 @@ struct Launch {
 
 // Launchers (mpc_kernels.hip).
 hipError_t launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s);
-hipError_t launch_key_hist(const Dev& d, const Launch& l);
-hipError_t launch_scan(const Dev& d, const Launch& l);
-hipError_t launch_scatter(const Dev& d, const Launch& l);
-hipError_t launch_phantoms(const Dev& d, const Launch& l);
+hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s);
+hipError_t launch_binning(const Dev& d, const Launch& l, const StatePtrs& S, uint64_t t);
+hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to);
+hipError_t launch_prepare(const Dev& d, const Launch& l);
 hipError_t launch_collide(const Dev& d, const Launch& l);
-hipError_t launch_advance(const Dev& d, const Launch& l);
 hipError_t launch_set_ctrl(const Dev& d, const Launch& l, uint64_t step, uint32_t cur,
                            int32_t reorder, int clear_err);
 hipError_t launch_init_state(const Dev& d, const Launch& l, uint64_t seed);
-hipError_t launch_obs_pass1(const Dev& d, const Launch& l);
-hipError_t launch_obs_pass2(const Dev& d, const Launch& l, const double* vmean_dev);
+// observables of particle blocks [pb0, pb0 + npb) of state buffer cur; order:
+// slots in the order of the sums (null: slot order)
+hipError_t launch_obs_order(const Dev& d, const Launch& l, uint32_t box, uint32_t nrows,
+                            uint32_t l0, uint32_t cur, uint32_t To, uint32_t* order);
+hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
+                            const uint32_t* order);
+hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
+                            const double* vmean_dev);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
 // inv: np entries filled with 0xffffffff by the caller (null: slots are the
 // logical order); lidx: box-local logical indices; out: [6][m] FP64

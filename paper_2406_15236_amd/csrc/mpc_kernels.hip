@@ -1,19 +1,22 @@
 // mpc_kernels.hip -- gfx950 kernels of the MPC-SRD step (arXiv:2406.15236, Sec. II).
 //
+// Cells are grouped into tiles (runs of at most 32 cells of one row).  A state
+// buffer holds the particles of a tile's collision of the previous step next
+// to each other, grouped by the tile that they reach in the next step, and
+// every tile has a list of those runs (first slot, count).
+//
 // One step t on the device (steady state):
-//   scan    : offset = exclusive prefix of hist (particles per cell of step t),
-//             per-cell random draws; hist is zeroed for the next count
-//   scatter : perm[offset[key] + rank] = i (each particle already holds its
-//             rank inside its cell)
-//   collide : per tile of cells: gather the cell segments through perm, order
-//             each segment by logical index in LDS, stream (Eq. 1), sum the
-//             cells one thread per cell, rotate (Eq. 2) + scale with the draws,
-//             stream + bin for step t+1, and write the state into the other
-//             buffer, each tile pass grouped by next-step cell; the next
-//             step's counts and ranks come from one atomic per (pass, cell).
-//   advance : t += 1, flip the buffers.
-// The prologue kernel computes key/hist/rank of step t when the state was set
-// from outside.  Every kernel reads the step index and buffer from Ctrl, so a
+//   prepare : position of every tile's output (prefix of the particles per
+//             tile), random draws of every cell, phantom particles (walls),
+//             lattice shifts of t and t + 1
+//   collide : per tile: gather its runs, stream (Eq. 1), order by cell and
+//             logical index in LDS, sum the cells, rotate (Eq. 2) + scale with
+//             the draws, stream + bin for step t+1, write the state into the
+//             other buffer grouped by next-step tile and append one run per
+//             such tile to its list.  The last workgroup advances t and flips
+//             the buffers.
+// When the state was set from outside, a counting sort by tile puts it in this
+// order first.  Every kernel reads the step index and buffer from Ctrl, so a
 // captured graph of one step can be replayed.
 #include <math.h>
 
@@ -38,6 +41,7 @@ __device__ __forceinline__ Tile load_tile(const Tile* p, uint32_t i) {
   t.c0 = r.c0;
   t.nc = r.nc;
   t.box = r.box;
+  t.tid = r.tid;
   t.x0 = r.x0;
   t.y0 = r.y0;
   t.z0 = r.z0;
@@ -54,6 +58,12 @@ __device__ __forceinline__ PBlock load_pblock(const PBlock* p, uint32_t i) {
 // ---------------------------------------------------------------------------
 // Random draws of the method
 // ---------------------------------------------------------------------------
+// Angles here are at most 2 pi.  Told so, the compiler drops the reduction of
+// huge arguments from sin and cos (the limit is that of their short branch),
+// which would set the register count of the prepare kernel (109 instead of 81
+// VGPRs) and of the collide with the thermostat.
+constexpr double kSmallAngle = 0x1p30;
+
 __device__ __forceinline__ Words4 draw(BoxRef B, uint32_t j, uint32_t id, uint64_t t,
                                        uint32_t tag) {
   return philox10(j, id, (uint32_t)t, tag, B.key_lo, B.key_hi);
@@ -76,37 +86,62 @@ __device__ __forceinline__ void axis_of(BoxRef B, uint64_t t, uint32_t key, doub
   const double r = sqrt(1.0 - z * z);
   const double phi = kTwoPi * u2;
   double sp, cp;
+  __builtin_assume(__builtin_fabs(phi) < kSmallAngle);
   sincos(phi, &sp, &cp);
   n[0] = r * cp;
   n[1] = r * sp;
   n[2] = z;
 }
 
-// Gamma(shape, 1) by Marsaglia-Tsang; attempt j uses THERMO draw j
-// (Box-Muller cosine branch from words 0,1; acceptance uniform from 2,3).
-// Returns false if 64 attempts were rejected.
-__device__ __forceinline__ bool gamma_of(BoxRef B, uint64_t t, uint32_t key, double shape,
-                                      double* out) {
-  const double d = shape - 1.0 / 3.0;
-  const double c = 1.0 / sqrt(9.0 * d);
+// Attempt j of the gamma draw: the normal z (Box-Muller cosine branch of
+// THERMO draw j, words 0 and 1) and log of the acceptance uniform (words 2
+// and 3).  Neither depends on the shape.
+__device__ __forceinline__ void gamma_attempt(uint32_t key_lo, uint32_t key_hi, uint64_t t,
+                                              uint32_t key, uint32_t j, double& z, double& lu) {
+  const Words4 w = philox10(j, key, (uint32_t)t, kTagThermo, key_lo, key_hi);
+  const double u1 = u32_open_of(w.w[0]);
+  const double u2 = (double)w.w[1] * 0x1p-32;
+  const double ph = kTwoPi * u2;
+  __builtin_assume(__builtin_fabs(ph) < kSmallAngle);
+  z = sqrt(-2.0 * log(u1)) * cos(ph);
+  lu = log(u53_open_of(w.w[2], w.w[3]));
+}
+
+// Gamma(shape, 1) by Marsaglia-Tsang with shape 3 (n - 1) / 2 for the n
+// particles of a cell: d v for an accepted attempt, else -1.
+struct GammaDC {
+  double d, c;
+};
+__device__ __forceinline__ GammaDC gamma_dc(uint32_t n) {
+  const double d = 1.5 * (double)(n - 1) - 1.0 / 3.0;
+  return {d, 1.0 / sqrt(9.0 * d)};
+}
+__device__ __forceinline__ bool gamma_accepts(uint32_t n, double z, double lu) {
+  const GammaDC g = gamma_dc(n);
+  double vv = 1.0 + g.c * z;
+  if (vv <= 0.0) return false;
+  vv = vv * vv * vv;
+  const double rhs = 0.5 * z * z + g.d - g.d * vv + g.d * log(vv);
+  return lu < rhs;
+}
+// Smallest n that accepts attempt (z, lu), kNeverAccepted if that is more than
+// a cell can hold.  The acceptance bound rises with n: with y = c z it is
+// (z^2 / 9) N(y) / y^2, N(y) = 3 (log(1 + y) - y + y^2 / 2 - y^3 / 3) =
+// -3 int_0^y s^3 / (1 + s) ds, and N(y) / y^2 rises to 0 as |y| falls.  So an
+// attempt accepted for n is accepted for every larger n.  The search starts
+// where the leading term of the bound, -z^4 / (108 d), crosses lu.
+__device__ __forceinline__ uint32_t gamma_least(double z, double lu) {
+  const double ds = z * z * z * z / (-108.0 * lu);
+  uint32_t n = (uint32_t)fmin(2.0 + ds * (2.0 / 3.0), (double)kNeverAccepted);
+  if (n < kNeverAccepted && gamma_accepts(n, z, lu)) {
 #pragma unroll 1
-  for (uint32_t j = 0; j < 64; ++j) {
-    const Words4 w = draw(B, j, key, t, kTagThermo);
-    const double u1 = u32_open_of(w.w[0]);
-    const double u2 = (double)w.w[1] * 0x1p-32;
-    const double z = sqrt(-2.0 * log(u1)) * cos(kTwoPi * u2);
-    double vv = 1.0 + c * z;
-    if (vv <= 0.0) continue;
-    vv = vv * vv * vv;
-    const double u = u53_open_of(w.w[2], w.w[3]);
-    const double lhs = log(u);
-    const double rhs = 0.5 * z * z + d - d * vv + d * log(vv);
-    if (lhs < rhs) {
-      *out = d * vv;
-      return true;
-    }
+    while (n > 2u && gamma_accepts(n - 1u, z, lu)) --n;
+  } else {
+#pragma unroll 1
+    while (n < kNeverAccepted && !gamma_accepts(n + 1u, z, lu)) ++n;
+    n = min(n + 1u, kNeverAccepted);
   }
-  return false;
+  return n;
 }
 
 // Phantom particles of a wall-cut cell: Poisson(<N_c> f_w) count by inversion
@@ -143,6 +178,7 @@ __device__ __forceinline__ double phantom_normal(BoxRef B, uint64_t t, uint32_t 
   const uint32_t pr = (m % 4) / 2;
   const double r = sqrt(-2.0 * log(u32_open_of(pc.w.w[2 * pr])));
   const double th = kTwoPi * ((double)pc.w.w[2 * pr + 1] * 0x1p-32);
+  __builtin_assume(__builtin_fabs(th) < kSmallAngle);
   return (m % 2 == 0) ? r * cos(th) : r * sin(th);
 }
 
@@ -163,7 +199,7 @@ __device__ __forceinline__ double wall_fraction(double sz, int cz, int H) {
 // ---------------------------------------------------------------------------
 // Periodic wrap into [0, L): one image shift (selects), then the rare cases
 // (rounding onto L, far outside, non-finite) on a cold path.
-__device__ __noinline__ double wrap64_rare(double x, double L) {
+__device__ __forceinline__ double wrap64_rare(double x, double L) {
   if (x == L) return 0.0;
   if (isfinite(x)) {
     x = x - L * floor(x / L);
@@ -178,7 +214,7 @@ __device__ __forceinline__ double wrap64(double x, double L) {
   return x;
 }
 
-__device__ __noinline__ float wrap32_rare(float x, float L) {
+__device__ __forceinline__ float wrap32_rare(float x, float L) {
   if (x == L) return 0.0f;
   if (isfinite(x)) {
     x = x - L * floorf(x / L);
@@ -301,7 +337,7 @@ __device__ __forceinline__ uint32_t split_encode(const int (&c)[3]) {
   return (uint32_t)c[0] | ((uint32_t)c[1] << kSplitXBits) |
          ((uint32_t)c[2] << (kSplitXBits + kSplitYBits));
 }
-__device__ __noinline__ int wrap_cell_rare(int c, int L) { return ((c % L) + L) % L; }
+__device__ __forceinline__ int wrap_cell_rare(int c, int L) { return ((c % L) + L) % L; }
 __device__ __forceinline__ int wrap_cell(int c, int L) {
   c = c < 0 ? c + L : (c >= L ? c - L : c);
   if (__builtin_expect(c < 0 || c >= L, 0)) c = wrap_cell_rare(c, L);
@@ -499,18 +535,7 @@ struct Form<kFormF64> {
   };
   using Vs = double;
   using Xs = double;
-  static constexpr bool kHasCell = false;
-  __device__ static void to_lds(const P& p, Xs* x0, Xs* x1, Xs* x2, uint32_t*, uint32_t q) {
-    x0[q] = p.x[0];
-    x1[q] = p.x[1];
-    x2[q] = p.x[2];
-  }
-  __device__ static void from_lds(P& p, const Xs* x0, const Xs* x1, const Xs* x2,
-                                  const uint32_t*, uint32_t q) {
-    p.x[0] = x0[q];
-    p.x[1] = x1[q];
-    p.x[2] = x2[q];
-  }
+  __device__ static Xs pos(const P& p, int k) { return p.x[k]; }
   // record: three 16-byte words (x0 x1 | x2 v0 | v1 v2)
   __device__ static void load(const StatePtrs& S, uint32_t i, P& p, Vv& v) {
     const double2* r = (const double2*)S.rec + 3 * (size_t)i;
@@ -554,6 +579,18 @@ struct Form<kFormF64> {
   }
   // Lees-Edwards side of the collision cell: +1 below the lower z face,
   // -1 above the upper one, else 0
+  // x coordinate of the collision cell (as coords)
+  __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
+    const double y = (double)p.x[0] + s[0];
+    int c = (int)floor(y >= -2.0 && y < B.Ld[0] + 2.0 ? y : 0.0);
+    if (le) {
+      const double cz = floor((double)p.x[2] + s[2]);
+      if (cz < 0.0 || cz >= B.Ld[2])
+        c = wrap1((int)floor((cz < 0.0 ? (double)p.x[0] + dle : (double)p.x[0] - dle) + s[0]),
+                  B.L[0]);
+    }
+    return wrap1(c, B.L[0]);
+  }
   __device__ static int le_side(const P& p, double sz, BoxRef B) {
     const double cz = floor(p.x[2] + sz);
     return cz < 0.0 ? 1 : (cz >= B.Ld[2] ? -1 : 0);
@@ -570,18 +607,7 @@ struct Form<kFormF32> {
   };
   using Vs = float;
   using Xs = float;
-  static constexpr bool kHasCell = false;
-  __device__ static void to_lds(const P& p, Xs* x0, Xs* x1, Xs* x2, uint32_t*, uint32_t q) {
-    x0[q] = p.x[0];
-    x1[q] = p.x[1];
-    x2[q] = p.x[2];
-  }
-  __device__ static void from_lds(P& p, const Xs* x0, const Xs* x1, const Xs* x2,
-                                  const uint32_t*, uint32_t q) {
-    p.x[0] = x0[q];
-    p.x[1] = x1[q];
-    p.x[2] = x2[q];
-  }
+  __device__ static Xs pos(const P& p, int k) { return p.x[k]; }
   // record: three 8-byte words (x0 x1 | x2 v0 | v1 v2)
   __device__ static void load(const StatePtrs& S, uint32_t i, P& p, Vv& v) {
     const float2* r = (const float2*)S.rec + 3 * (size_t)i;
@@ -623,6 +649,18 @@ struct Form<kFormF32> {
     const double xf[3] = {(double)p.x[0], (double)p.x[1], (double)p.x[2]};
     coords_of<W>(ci, xf, s, B, c, err, dle, le);
   }
+  // x coordinate of the collision cell (as coords)
+  __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
+    const double y = (double)p.x[0] + s[0];
+    int c = (int)floor(y >= -2.0 && y < B.Ld[0] + 2.0 ? y : 0.0);
+    if (le) {
+      const double cz = floor((double)p.x[2] + s[2]);
+      if (cz < 0.0 || cz >= B.Ld[2])
+        c = wrap1((int)floor((cz < 0.0 ? (double)p.x[0] + dle : (double)p.x[0] - dle) + s[0]),
+                  B.L[0]);
+    }
+    return wrap1(c, B.L[0]);
+  }
   __device__ static int le_side(const P& p, double sz, BoxRef B) {
     const double cz = floor((double)p.x[2] + sz);
     return cz < 0.0 ? 1 : (cz >= B.Ld[2] ? -1 : 0);
@@ -640,20 +678,7 @@ struct Form<kFormSplit> {
   };
   using Vs = float;
   using Xs = float;
-  static constexpr bool kHasCell = true;
-  __device__ static void to_lds(const P& p, Xs* x0, Xs* x1, Xs* x2, uint32_t* c, uint32_t q) {
-    x0[q] = p.o[0];
-    x1[q] = p.o[1];
-    x2[q] = p.o[2];
-    c[q] = p.cell;
-  }
-  __device__ static void from_lds(P& p, const Xs* x0, const Xs* x1, const Xs* x2,
-                                  const uint32_t* c, uint32_t q) {
-    p.o[0] = x0[q];
-    p.o[1] = x1[q];
-    p.o[2] = x2[q];
-    p.cell = c[q];
-  }
+  __device__ static Xs pos(const P& p, int k) { return p.o[k]; }
   // record: two 16-byte words (cell o0 o1 o2 | v0 v1 v2 id).  The gather
   // reads the id word with a load of its own after the 28 bytes of state
   // (measured 8 % faster for the collide than one 16-byte load of v and id).
@@ -705,6 +730,20 @@ struct Form<kFormSplit> {
     coords<W>(p, s, B, c, err, dle, le);
     return linear_key(c, B);
   }
+  // x coordinate of the collision cell (as coords)
+  __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
+    const int cx = (int)(p.cell & ((1u << kSplitXBits) - 1));
+    if (le) {
+      int ci[3];
+      split_decode(p.cell, ci);
+      const int cz = ci[2] + (int)floor((double)p.o[2] + s[2]);
+      const double xo = (double)p.o[0];
+      if (cz < 0 || cz >= B.L[2])
+        return wrap1(wrap1(cx + (int)floor((cz < 0 ? xo + dle : xo - dle) + s[0]), B.L[0]), B.L[0]);
+      return wrap1(cx + (int)floor(xo + s[0]), B.L[0]);
+    }
+    return wrap1(cx + (int)floorf(p.o[0] + (float)s[0]), B.L[0]);
+  }
   __device__ static int le_side(const P& p, double sz, BoxRef B) {
     int ci[3];
     split_decode(p.cell, ci);
@@ -716,21 +755,18 @@ struct Form<kFormSplit> {
 // ---------------------------------------------------------------------------
 // Small kernels
 // ---------------------------------------------------------------------------
-__global__ void k_zero_u32(uint32_t* p, uint64_t n) {
+__global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t value) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
+  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+    p[i] = value;
 }
 
 __global__ void k_set_ctrl(Ctrl* c, uint64_t step, uint32_t cur, int32_t reorder, int clear_err) {
   c->step = step;
   c->cur = cur;
   c->reorder = reorder;
+  c->done = 0u;
   if (clear_err) c->err = 0u;
-}
-
-__global__ void k_advance(Ctrl* c) {
-  c->cur ^= 1u;
-  c->step = c->step + 1;
 }
 
 // hist[c] += 1 for every active lane, one atomic per distinct key in the
@@ -756,15 +792,14 @@ __device__ __forceinline__ uint32_t wave_hist_rank(uint32_t* hist, uint32_t c, b
   return old + before;
 }
 
-// Prologue: key and histogram of step t from the current state.
+// Binning export: cell key, histogram and in-cell rank of step t for the
+// particles of state buffer S (the input of that step).
 template <int F, bool W>
-__global__ __launch_bounds__(kThreads) void k_key_hist(Dev d) {
+__global__ __launch_bounds__(kThreads) void k_key_hist(Dev d, StatePtrs S, uint64_t t) {
   using Fm = Form<F>;
   __shared__ double s_sh[3];
   const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
   BoxRef B = as_const(d.boxes)[pb.box];
-  const uint64_t t = d.ctrl->step;
-  const StatePtrs S = d.S[d.ctrl->cur];
   if (threadIdx.x == 0) {
     double s[3];
     shift_of(B, t, s);
@@ -861,48 +896,11 @@ __global__ __launch_bounds__(1024) void k_scan_top(uint32_t* __restrict__ blk, u
   }
 }
 
-// Box that owns global cell c (boxes are stored in ascending cbase).
-__device__ __forceinline__ uint32_t box_of_cell(const BoxDev* boxes, uint32_t nbox, uint32_t c) {
-  uint32_t lo = 0, hi = nbox;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (as_const(boxes)[mid].cbase <= c) {
-      lo = mid;
-    } else {
-      hi = mid;
-    }
-  }
-  return lo;
-}
-
-// Random draws of one occupied cell for step t: the rotation axis and, with
-// the thermostat, the target energy E_k = kT * Gamma(3 (n - 1) / 2), where n
-// counts phantoms too (walls).  Ek = 0 means "no scaling".
-template <bool W, bool M>
-__device__ __forceinline__ void cell_draws(BoxRef B, uint64_t t, uint32_t lkey, uint32_t nf,
-                                           double sz, CellDraw& out) {
-  uint32_t ntot = nf;
-  if (W && !B.slip) {
-    const int cz = (int)(lkey / (uint32_t)(B.L[0] * B.L[1])) - 1;
-    const double fw = wall_fraction(sz, cz, B.L[2]);
-    if (fw > 0.0) ntot += (uint32_t)phantom_count(B, t, lkey, fw);
-  }
-  axis_of(B, t, lkey, out.n);
-  out.Ek = 0.0;
-  if (M && ntot >= 2) {
-    double gv;
-    if (gamma_of(B, t, lkey, 1.5 * (double)(ntot - 1), &gv)) out.Ek = B.kT * gv;
-  }
-}
-
-// Each thread owns kScanItems consecutive cells: offsets, then the cell draws
-// of its occupied cells (all lanes busy: one thread per 16 cells).
-template <bool W, bool M>
-__global__ __launch_bounds__(kThreads) void k_scan_down(Dev d, uint32_t nblk, uint32_t nbox,
-                                                        uint32_t ctot) {
+// Each thread owns kScanItems consecutive cells.
+__global__ __launch_bounds__(kThreads) void k_scan_down(Dev d, uint32_t nblk) {
   __shared__ uint32_t s_w[kThreads / 64];
   const uint64_t base = (uint64_t)blockIdx.x * kScanBlock + (uint64_t)threadIdx.x * kScanItems;
-  uint4* h4 = (uint4*)(d.hist + base);
+  const uint4* h4 = (const uint4*)(d.hist + base);
   uint32_t v[kScanItems];
 #pragma unroll
   for (int k = 0; k < kScanItems / 4; ++k) {
@@ -911,7 +909,6 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(Dev d, uint32_t nblk, ui
     v[4 * k + 1] = q.y;
     v[4 * k + 2] = q.z;
     v[4 * k + 3] = q.w;
-    h4[k] = make_uint4(0u, 0u, 0u, 0u);  // the next collide counts from zero
   }
   uint32_t sum = 0;
 #pragma unroll
@@ -934,108 +931,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(Dev d, uint32_t nblk, ui
   }
   if (blockIdx.x == nblk - 1 && threadIdx.x == kThreads - 1)
     d.offset[(uint64_t)nblk * kScanBlock] = run;
-
-  // per-cell draws for step t; the counts go through LDS so that consecutive
-  // lanes draw (and store the 32-byte records of) consecutive cells
-  __shared__ uint4 s_cnt[kScanBlock / 4];
-#pragma unroll
-  for (int k = 0; k < kScanItems / 4; ++k)
-    s_cnt[threadIdx.x * (kScanItems / 4) + k] =
-        make_uint4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
-  __syncthreads();
-  const uint64_t blk0 = (uint64_t)blockIdx.x * kScanBlock;
-  if (blk0 + threadIdx.x >= ctot) return;
-  const uint32_t* cnt = (const uint32_t*)s_cnt;
-  const uint64_t t = as_const(d.ctrl)->step;
-  uint32_t b = box_of_cell(d.boxes, nbox, (uint32_t)(blk0 + threadIdx.x));
-  double sz = 0.0;
-  if (W) {
-    double sh[3];
-    shift_of(as_const(d.boxes)[b], t, sh);
-    sz = sh[2];
-  }
-#pragma unroll 1
-  for (int k = 0; k < kScanItems; ++k) {
-    const uint32_t c = (uint32_t)(blk0 + (uint64_t)k * kThreads + threadIdx.x);
-    if (c >= ctot) break;
-    while (c >= as_const(d.boxes)[b].cbase + as_const(d.boxes)[b].nc) {
-      ++b;
-      if (W) {
-        double sh[3];
-        shift_of(as_const(d.boxes)[b], t, sh);
-        sz = sh[2];
-      }
-    }
-    const uint32_t nf = cnt[k * kThreads + threadIdx.x];
-    if (nf == 0u) continue;
-    BoxRef B = as_const(d.boxes)[b];
-    CellDraw cd;
-    cell_draws<W, M>(B, t, c - B.cbase, nf, sz, cd);
-    d.draws[c] = cd;
-  }
 }
 
-// ---------------------------------------------------------------------------
-// Scatter: slot of each particle inside its cell segment (order inside a
-// segment is arbitrary here and made canonical in collide).
-// ---------------------------------------------------------------------------
-// Phantom particles of the occupied cells of the two wall-cut layers of every
-// box (one thread per cell of those layers): count, velocity sum and squared-
-// speed sum (velocities N(0, kT/m) per component; rounded to FP32 for the
-// split form), read by the collide's cell sums.
-__global__ __launch_bounds__(kThreads) void k_phantom_sums(Dev d, uint32_t nbox, uint32_t wcells,
-                                                           int round32) {
-  const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
-  if (i >= wcells) return;
-  uint32_t lo = 0, hi = nbox;
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (d.boxes[mid].wcbase <= i) {
-      lo = mid;
-    } else {
-      hi = mid;
-    }
-  }
-  BoxRef B = as_const(d.boxes)[lo];
-  if (B.slip) return;  // slip walls carry no phantoms
-  const uint64_t t = as_const(d.ctrl)->step;
-  double sh[3];
-  shift_of(B, t, sh);
-  const uint32_t plane = (uint32_t)B.L[0] * (uint32_t)B.L[1];
-  const uint32_t li = i - B.wcbase;
-  const uint32_t top = li / plane;
-  const int H = B.L[2];
-  // key layer (c_z + 1) of the cut cells: c_z in {0, H} for s_z >= 0, {-1, H-1} else
-  const int czk = sh[2] >= 0.0 ? (top ? H + 1 : 1) : (top ? H : 0);
-  const uint32_t lkey = (uint32_t)czk * plane + (li - top * plane);
-  const uint32_t c = B.cbase + lkey;
-  if (d.offset[c + 1] == d.offset[c]) return;  // not occupied: no collision
-  const double fw = wall_fraction(sh[2], czk - 1, H);
-  if (!(fw > 0.0)) return;
-  const int nph = phantom_count(B, t, lkey, fw);
-  PhantomSums ps;
-  ps.v[0] = ps.v[1] = ps.v[2] = 0.0;
-  ps.v2 = 0.0;
-  PhantomCache pc;
-  pc.j = 0xffffffffu;
-  // phantoms move with the wall that fills their part of the cell
-  const double uw = top ? B.uw : -B.uw;
-#pragma unroll 1
-  for (int q = 0; q < nph; ++q) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      double vp = B.sd * phantom_normal(B, t, lkey, 3 * q + k, pc);
-      if (k == 0) vp = vp + uw;
-      if (round32) vp = (double)(float)vp;
-      ps.v[k] = ps.v[k] + vp;
-      ps.v2 = ps.v2 + vp * vp;
-    }
-  }
-  ps.n = (double)nph;
-  ps.pad = 0.0;
-  d.phs[c] = ps;
-}
-
+// Binning export: slot of each particle inside its cell segment (the order
+// inside a segment is made canonical afterwards).
 __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict__ key,
                                                       const uint16_t* __restrict__ rank,
                                                       const uint32_t* __restrict__ offset,
@@ -1064,40 +963,379 @@ __global__ __launch_bounds__(kThreads) void k_scatter(const uint32_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Collide (+ stream/bin of the next step)
+// Tiles
 // ---------------------------------------------------------------------------
-// Entry of next-step cell c in the window of the tile whose first cell is
-// (x0, y0, z0): row r = (dz + 1) * 3 + (dy + 1) for the rows y0 + dy, z0 + dz
-// (dy, dz in {-1, 0, 1}; periodic axes taken modulo L), column
-// dx = (c_x - x0 + 1) mod L0 < WX = cells of the tile + 2.  False when the
-// cell lies outside the window (the particle moved more than one cell).
-template <bool W>
-__device__ __forceinline__ bool win_entry(const int (&c)[3], int x0, int y0, int z0, int WX,
-                                          int L0, int L1, int L2, int& r, int& dx) {
-  dx = wrap1(c[0] - x0 + 1, L0);
-  int dy = c[1] - y0;
-  dy += L1 & -(int)(dy < -1);
-  dy -= L1 & -(int)(dy > 1);
-  int dz = c[2] - z0;
-  if (!W) {
-    dz += L2 & -(int)(dz < -1);
-    dz -= L2 & -(int)(dz > 1);
-  }
-  r = (dz + 1) * 3 + (dy + 1);
-  return (unsigned)dx < (unsigned)WX && (unsigned)(dy + 1) < 3u && (unsigned)(dz + 1) < 3u;
+// Tile (key order) of the cell with coordinates c.
+__device__ __forceinline__ uint32_t tile_of(BoxRef B, const int (&c)[3]) {
+  return B.tbase + ((uint32_t)c[2] * (uint32_t)B.L[1] + (uint32_t)c[1]) * B.ntx +
+         (uint32_t)c[0] / B.T;
 }
 
-// Number of entries of seg[b..e) smaller than i (four independent LDS reads
-// per trip so that they overlap).
-__device__ __forceinline__ uint32_t rank_in_segment(const uint32_t* seg, uint32_t b, uint32_t e,
-                                                    uint32_t i) {
-  uint32_t r = 0, q = b;
-  for (; q + 4 <= e; q += 4) {
-    const uint32_t a0 = seg[q], a1 = seg[q + 1], a2 = seg[q + 2], a3 = seg[q + 3];
-    r += (a0 < i ? 1u : 0u) + (a1 < i ? 1u : 0u) + (a2 < i ? 1u : 0u) + (a3 < i ? 1u : 0u);
+// Sort by tile of a state set from outside (order arbitrary): particles per
+// tile of step t (high word of the tile's counter) ...
+template <int F, bool W>
+__global__ __launch_bounds__(kThreads) void k_tile_count(Dev d, uint32_t from, uint32_t to) {
+  using Fm = Form<F>;
+  __shared__ double s_sh[3];
+  const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
+  BoxRef B = as_const(d.boxes)[pb.box];
+  const uint64_t t = d.ctrl->step;
+  const StatePtrs S = d.S[from];
+  if (threadIdx.x == 0) {
+    double s[3];
+    shift_of(B, t, s);
+    s_sh[0] = s[0];
+    s_sh[1] = s[1];
+    s_sh[2] = s[2];
   }
-  for (; q < e; ++q) r += seg[q] < i ? 1u : 0u;
-  return r;
+  __syncthreads();
+  const double s[3] = {s_sh[0], s_sh[1], s_sh[2]};
+  const double dle = W ? 0.0 : le_offset(B, t + 1);
+  const uint32_t pend = B.pbase + B.np;
+  uint32_t err = 0;
+#pragma unroll
+  for (int k = 0; k < kPartBlock / kThreads; ++k) {
+    const uint32_t i = pb.p0 + k * kThreads + threadIdx.x;
+    if (i >= pend) continue;
+    typename Fm::P p;
+    typename Fm::Vv v;
+    Fm::load(S, i, p, v);
+    Fm::template stream<W>(p, v, B, dle, !W && B.le);
+    int c[3];
+    Fm::template coords<W>(p, s, B, c, err, dle, !W && B.le);
+    atomicAdd(&d.tcnt[to][tile_of(B, c)], 1ull << 32);
+  }
+  if (err) atomicOr(&d.ctrl->err, err);
+}
+
+// ... and, once the prefix of those counts is known, the records into the
+// other buffer, tile by tile (the low word counts the particles placed).
+template <int F, bool W>
+__global__ __launch_bounds__(kThreads) void k_tile_scatter(Dev d, uint32_t from, uint32_t to) {
+  using Fm = Form<F>;
+  __shared__ double s_sh[3];
+  const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
+  BoxRef B = as_const(d.boxes)[pb.box];
+  const uint64_t t = d.ctrl->step;
+  const StatePtrs in = d.S[from], out = d.S[to];
+  if (threadIdx.x == 0) {
+    double s[3];
+    shift_of(B, t, s);
+    s_sh[0] = s[0];
+    s_sh[1] = s[1];
+    s_sh[2] = s[2];
+  }
+  __syncthreads();
+  const double s[3] = {s_sh[0], s_sh[1], s_sh[2]};
+  const double dle = W ? 0.0 : le_offset(B, t + 1);
+  const uint32_t pend = B.pbase + B.np;
+  uint32_t err = 0;
+#pragma unroll
+  for (int k = 0; k < kPartBlock / kThreads; ++k) {
+    const uint32_t i = pb.p0 + k * kThreads + threadIdx.x;
+    if (i >= pend) continue;
+    typename Fm::P p, p2;
+    typename Fm::Vv v, v2;
+    uint32_t id;
+    Fm::load_all(in, i, p, v, id);
+    p2 = p;
+    v2 = v;
+    Fm::template stream<W>(p2, v2, B, dle, !W && B.le);
+    int c[3];
+    Fm::template coords<W>(p2, s, B, c, err, dle, !W && B.le);
+    const uint32_t tl = tile_of(B, c);
+    const uint32_t j = d.toff[tl] + (uint32_t)atomicAdd(&d.tcnt[to][tl], 1ull);
+    if (j < d.ntot) Fm::store_all(out, j, p, v, id);
+  }
+  if (err) atomicOr(&d.ctrl->err, err);
+}
+
+// ... and one run per occupied tile.
+__global__ __launch_bounds__(kThreads) void k_tile_runs(Dev d, uint32_t to) {
+  const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
+  if (i >= d.ntile) return;
+  const uint32_t n = (uint32_t)(d.tcnt[to][i] >> 32);
+  d.tcnt[to][i] = (unsigned long long)n << 32 | (n ? 1u : 0u);
+  d.runs[to][(size_t)i * d.maxr] = Run{d.toff[i], n};
+}
+
+// ---------------------------------------------------------------------------
+// Prepare: everything a step's collide reads besides the particles
+// ---------------------------------------------------------------------------
+// Particles per block of kTileBlock tiles (only for more than kTileDirect
+// tiles; below that every block of the prefix sums the counts before it).
+__global__ __launch_bounds__(kThreads) void k_tile_reduce(Dev d, int fixed_buf) {
+  __shared__ uint32_t s_w[kThreads / 64];
+  const uint32_t buf = fixed_buf >= 0 ? (uint32_t)fixed_buf : as_const(d.ctrl)->cur;
+  const unsigned long long* cnt = d.tcnt[buf];
+  uint32_t sum = 0;
+#pragma unroll
+  for (int k = 0; k < kTileBlock / kThreads; ++k) {
+    const uint32_t i = blockIdx.x * kTileBlock + k * kThreads + threadIdx.x;
+    if (i < d.ntile) sum += (uint32_t)(cnt[i] >> 32);
+  }
+  uint32_t total;
+  block_exclusive_scan(sum, s_w, total);
+  if (threadIdx.x == 0) d.tblk[blockIdx.x] = total;
+}
+
+// toff of the tiles of one block: exclusive prefix of the particles per tile.
+__device__ __forceinline__ void tile_prefix(const Dev& d, uint32_t blk, uint32_t buf) {
+  __shared__ uint32_t s_w[kThreads / 64];
+  const unsigned long long* cnt = d.tcnt[buf];
+  const uint32_t b0 = blk * kTileBlock;
+  // particles of all tiles before this block
+  uint32_t before = 0;
+  if (d.ntile > kTileDirect) {
+    for (uint32_t i = threadIdx.x; i < blk; i += kThreads) before += d.tblk[i];
+  } else {
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < b0; i += kThreads) before += (uint32_t)(cnt[i] >> 32);
+  }
+  uint32_t run;
+  block_exclusive_scan(before, s_w, run);
+  constexpr int K = kTileBlock / kThreads;
+  const uint32_t i0 = b0 + threadIdx.x * K;
+  uint32_t c[K], sum = 0;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    c[k] = i0 + k < d.ntile ? (uint32_t)(cnt[i0 + k] >> 32) : 0u;
+    sum += c[k];
+  }
+  uint32_t total;
+  run += block_exclusive_scan(sum, s_w, total);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (i0 + k < d.ntile) d.toff[i0 + k] = run;
+    run += c[k];
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void k_tile_scan(Dev d, uint32_t buf) {
+  tile_prefix(d, blockIdx.x, buf);
+}
+
+// Box that owns global cell c (boxes are stored in ascending cbase).
+__device__ __forceinline__ uint32_t box_of_cell(const BoxDev* boxes, uint32_t nbox, uint32_t c) {
+  uint32_t lo = 0, hi = nbox;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (as_const(boxes)[mid].cbase <= c) {
+      lo = mid;
+    } else {
+      hi = mid;
+    }
+  }
+  return lo;
+}
+
+// Random draws of one block of cells for step t: the rotation axis and, with
+// the thermostat, the gamma draw.  The number of particles n of a cell, which
+// sets the shape, is known to the collide only; so an attempt is kept with the
+// smallest n that accepts it.  Attempt 0 stands in the cell's record.  A cell
+// whose attempt 0 is not accepted for every n (one in 37) gets a chain of
+// later attempts up to one that is, in the block's segment of `later` (entry 0
+// unused).  One wavefront of the block works the chains out: made by every
+// wavefront for its own cells they took the prepare kernel from 0.3 to 1.1 ms
+// at 256^3.  The collide then needs neither logarithm nor cosine, which had
+// cost it a quarter of its wavefronts in registers.
+template <bool M>
+__device__ __forceinline__ void cell_draws(const Dev& d, uint32_t nbox, uint32_t blk,
+                                           uint32_t ctot) {
+  __shared__ uint32_t s_n, s_m;
+  __shared__ uint16_t s_cell[kMaxDrawBlock];
+  if (M) {
+    if (threadIdx.x == 0) s_n = s_m = 0u;
+    __syncthreads();
+  }
+  const uint64_t t = as_const(d.ctrl)->step;
+  const uint32_t c0 = blk * d.drawb;
+#pragma unroll 1
+  for (uint32_t k = threadIdx.x; k < d.drawb; k += kThreads) {
+    const uint32_t c = c0 + k;
+    if (c >= ctot) break;
+    BoxRef B = as_const(d.boxes)[box_of_cell(d.boxes, nbox, c)];
+    double n[3], z = 0.0;
+    axis_of(B, t, c - B.cbase, n);
+    if (M) {
+      double lu;
+      gamma_attempt(B.key_lo, B.key_hi, t, c - B.cbase, 0, z, lu);
+      if (gamma_accepts(2u, z, lu)) {
+        d.least[c] = 2u;
+      } else {
+        s_cell[atomicAdd(&s_n, 1u)] = (uint16_t)k;
+      }
+    }
+    double2* o = (double2*)d.draws + 2 * (size_t)c;
+    o[0] = make_double2(n[0], n[1]);
+    o[1] = make_double2(n[2], z);
+  }
+  if (!M) return;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  Attempt* seg = d.later + (size_t)blk * (d.drawb / 4);
+  for (uint32_t q = threadIdx.x; q < s_n; q += 64) {
+    const uint32_t c = c0 + s_cell[q];
+    BoxRef B = as_const(d.boxes)[box_of_cell(d.boxes, nbox, c)];
+    uint32_t word = 0, prev = 0;
+#pragma unroll 1
+    for (uint32_t j = 0; j < 64; ++j) {
+      double z, lu;
+      gamma_attempt(B.key_lo, B.key_hi, t, c - B.cbase, j, z, lu);
+      const uint32_t l = gamma_least(z, lu);
+      if (j == 0) {
+        word = l;
+        continue;
+      }
+      const uint32_t m = 1u + atomicAdd(&s_m, 1u);
+      if (m >= d.drawb / 4) {
+        atomicOr(&d.ctrl->err, kErrDraws);
+        break;
+      }
+      seg[m] = Attempt{z, (uint16_t)l, 0, 0};
+      if (prev) {
+        seg[prev].next = (uint16_t)m;
+      } else {
+        word |= m << 16;
+      }
+      prev = m;
+      if (l == 2u) break;
+    }
+    d.least[c] = word;
+  }
+}
+
+// Phantom particles of the cells of the two wall-cut layers of every box:
+// count, velocity sum and squared-speed sum (velocities N(0, kT/m) per
+// component; rounded to FP32 for the split form), read by the cell sums.
+__device__ __forceinline__ void phantom_sums(const Dev& d, uint32_t nbox, uint32_t i,
+                                             int round32) {
+  uint32_t lo = 0, hi = nbox;
+  while (hi - lo > 1) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (d.boxes[mid].wcbase <= i) {
+      lo = mid;
+    } else {
+      hi = mid;
+    }
+  }
+  BoxRef B = as_const(d.boxes)[lo];
+  if (B.slip) return;  // slip walls carry no phantoms
+  const uint64_t t = as_const(d.ctrl)->step;
+  double sh[3];
+  shift_of(B, t, sh);
+  const uint32_t plane = (uint32_t)B.L[0] * (uint32_t)B.L[1];
+  const uint32_t li = i - B.wcbase;
+  const uint32_t top = li / plane;
+  const int H = B.L[2];
+  // key layer (c_z + 1) of the cut cells: c_z in {0, H} for s_z >= 0, {-1, H-1} else
+  const int czk = sh[2] >= 0.0 ? (top ? H + 1 : 1) : (top ? H : 0);
+  const uint32_t lkey = (uint32_t)czk * plane + (li - top * plane);
+  const double fw = wall_fraction(sh[2], czk - 1, H);
+  if (!(fw > 0.0)) return;
+  const int nph = phantom_count(B, t, lkey, fw);
+  PhantomSums ps;
+  ps.v[0] = ps.v[1] = ps.v[2] = 0.0;
+  ps.v2 = 0.0;
+  PhantomCache pc;
+  pc.j = 0xffffffffu;
+  // phantoms move with the wall that fills their part of the cell
+  const double uw = top ? B.uw : -B.uw;
+#pragma unroll 1
+  for (int q = 0; q < nph; ++q) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      double vp = B.sd * phantom_normal(B, t, lkey, 3 * q + k, pc);
+      if (k == 0) vp = vp + uw;
+      if (round32) vp = (double)(float)vp;
+      ps.v[k] = ps.v[k] + vp;
+      ps.v2 = ps.v2 + vp * vp;
+    }
+  }
+  ps.n = (double)nph;
+  ps.pad = 0.0;
+  d.phs[B.cbase + lkey] = ps;
+}
+
+// One launch; the role of a block follows from its index: phantoms first (the
+// longest threads), then the tile prefix, the per-box step data, the draws.
+template <bool M>
+__global__ __launch_bounds__(kThreads) void k_prepare(Dev d, uint32_t nbox, uint32_t ctot,
+                                                      uint32_t wcells, int round32) {
+  uint32_t b = blockIdx.x;
+  const uint32_t nph = (wcells + kThreads - 1) / kThreads;
+  if (b < nph) {
+    const uint32_t i = b * kThreads + threadIdx.x;
+    if (i < wcells) phantom_sums(d, nbox, i, round32);
+    return;
+  }
+  b -= nph;
+  const uint32_t nts = (d.ntile + kTileBlock - 1) / kTileBlock;
+  if (b < nts) {
+    tile_prefix(d, b, as_const(d.ctrl)->cur);
+    return;
+  }
+  b -= nts;
+  const uint32_t nbs = (nbox + kThreads - 1) / kThreads;
+  if (b < nbs) {
+    const uint32_t i = b * kThreads + threadIdx.x;
+    if (i >= nbox) return;
+    const BoxDev& Bg = d.boxes[i];
+    BoxRef B = *as_const(&Bg);
+    const uint64_t t = as_const(d.ctrl)->step;
+    BoxStep st;
+    shift_of(B, t, st.s);
+    shift_of(B, t + 1, st.sn);
+    st.d1 = B.le ? le_offset(B, t + 1) : 0.0;
+    st.d2 = B.le ? le_offset(B, t + 2) : 0.0;
+    // first row of the window of next-step rows around a row: the lattice
+    // moves by sn - s, so particles move to rows between -1 and 1, or for
+    // shifts beyond half a cell between 0 and 2 or -2 and 0
+    for (int k = 1; k < 3; ++k) {
+      const double ds = st.sn[k] - st.s[k];
+      const int lk = k == 1 ? B.L[1] : B.nlz;
+      st.w[k - 1] = lk < 4 ? -1 : (ds > 0.5 ? 0 : (ds < -0.5 ? -2 : -1));
+    }
+    d.bstep[i] = st;
+    return;
+  }
+  b -= nbs;
+  cell_draws<M>(d, nbox, b, ctot);
+}
+
+// ---------------------------------------------------------------------------
+// Collide (+ stream/bin of the next step)
+// ---------------------------------------------------------------------------
+// Inclusive sum over the 64 lanes (DPP row shifts and broadcasts, no LDS).
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+  return (uint32_t)x;
+}
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Appends the run [start, start + n) of the output buffer to the list of tile
+// `dest`: a slot of its table, or (table full) a chain of single particles
+// from one of maxr heads.
+__device__ __forceinline__ void push_run(const Dev& d, uint32_t out, uint32_t dest, uint32_t start,
+                                         uint32_t n) {
+  if (dest >= d.ntile) return;
+  const uint32_t slot =
+      (uint32_t)atomicAdd(&d.tcnt[out][dest], (unsigned long long)n << 32 | 1ull);
+  if (slot < d.maxr) {
+    d.runs[out][(size_t)dest * d.maxr + slot] = Run{start, n};
+  } else {
+    uint32_t* next = d.rnext[out];
+    for (uint32_t q = 0; q + 1 < n; ++q) next[start + q] = start + q + 1;
+    next[start + n - 1] = atomicExch(&d.rhead[out][(size_t)dest * d.maxr + slot % d.maxr], start);
+  }
 }
 
 // Per-cell record of the collision, FP64 forms: the update rotates with the
@@ -1246,7 +1484,8 @@ __device__ __forceinline__ double fix_value(Fix a) {
 }
 
 template <int F, bool W, bool M, bool A, bool X>
-__device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd,
+__device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, const double (&axis)[3],
+                          double Ek,
                           const PhantomSums* __restrict__ ph,
                           const typename Form<F>::Vs* __restrict__ sv0,
                           const typename Form<F>::Vs* __restrict__ sv1,
@@ -1383,7 +1622,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
       const double VV = V[0] * V[0] + V[1] * V[1] + V[2] * V[2];
       K = K + m * (pv2 - 2.0 * vV + (double)nph * VV);
     }
-    if (cd.Ek > 0.0 && K > 0.0) kappa = sqrt((2.0 * cd.Ek) / K);
+    if (Ek > 0.0 && K > 0.0) kappa = sqrt((2.0 * Ek) / K);
   }
   // SRD+a (Eqs. 3-4, periodic boxes): omega = I^-1 dL with
   // dL = sum r_ic x (u_i - D u_i) and I the inertia tensor, both about the
@@ -1504,7 +1743,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
     const double xx = ss[1] + ss[2], yy = ss[0] + ss[2], zz = ss[0] + ss[1];
     const double xy = -ss[3], xz = -ss[4], yz = -ss[5];
     // rotation matrix D(alpha, n), row major
-    const double n[3] = {cd.n[0], cd.n[1], cd.n[2]};
+    const double n[3] = {axis[0], axis[1], axis[2]};
     const double ca = B.ca, sa = B.sa, omc = B.omc;
     const double D[9] = {ca + omc * n[0] * n[0],        omc * n[0] * n[1] - sa * n[2],
                          omc * n[0] * n[2] + sa * n[1], omc * n[1] * n[0] + sa * n[2],
@@ -1541,7 +1780,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
       // omega x r_ic to the drawn energy; their kinetic energy is
       // K + m (2 omega . L_D + omega . I omega), K that of the u_i
       kappa = 1.0;
-      if (cd.Ek > 0.0) {
+      if (Ek > 0.0) {
         const double Io[3] = {xx * om[0] + xy * om[1] + xz * om[2],
                               xy * om[0] + yy * om[1] + yz * om[2],
                               xz * om[0] + yz * om[1] + zz * om[2]};
@@ -1552,7 +1791,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
           q = q + om[k] * Io[k];
         }
         const double K2 = K + m * (2.0 * cr + q);
-        if (K2 > 0.0) kappa = sqrt((2.0 * cd.Ek) / K2);
+        if (K2 > 0.0) kappa = sqrt((2.0 * Ek) / K2);
       }
 #pragma unroll
       for (int k = 0; k < 3; ++k) om[k] = kappa * om[k];
@@ -1569,7 +1808,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
     }
   }
   if constexpr (F == kFormSplit) {
-    const double n[3] = {cd.n[0], cd.n[1], cd.n[2]};
+    const double n[3] = {axis[0], axis[1], axis[2]};
     const double ca = B.ca, sa = B.sa, omc = B.omc;
     const double R[9] = {ca + omc * n[0] * n[0],        omc * n[0] * n[1] - sa * n[2],
                          omc * n[0] * n[2] + sa * n[1], omc * n[1] * n[0] + sa * n[2],
@@ -1585,7 +1824,7 @@ __device__ void cell_work(BoxRef B, uint32_t lkey, double sz, const CellDraw& cd
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       out->V[k] = coll ? V[k] : 0.0;
-      out->n[k] = coll ? cd.n[k] : 0.0;
+      out->n[k] = coll ? axis[k] : 0.0;
     }
     out->kappa = coll ? kappa : 0.0;
   }
@@ -1613,8 +1852,38 @@ struct TileWalk {
   }
 };
 
+// Sources of a tile: its runs, then (more than maxr runs) its chains, one per
+// lane.  f(i, active) is called by the whole wavefront for up to 64 slots at
+// a time.
+template <class Fn>
+__device__ __forceinline__ void for_each_source(const Dev& d, uint32_t in, uint32_t tid,
+                                                uint32_t nrun, uint32_t lane, Fn f) {
+  const uint32_t nt = min(nrun, d.maxr);
+  for (uint32_t r = 0; r < nt; ++r) {
+    const Run run = d.runs[in][(size_t)tid * d.maxr + r];
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)run.count);
+    for (uint32_t q0 = 0; q0 < n; q0 += 64) {
+      const uint32_t i = run.start + q0 + lane;
+      f(i, q0 + lane < n && i < d.ntot);
+    }
+  }
+  if (nrun <= d.maxr) return;
+  uint32_t i = lane < d.maxr ? d.rhead[in][(size_t)tid * d.maxr + lane] : kNoSlot;
+  while (__ballot(i < d.ntot)) {
+    const bool on = i < d.ntot;
+    f(i, on);
+    i = on ? d.rnext[in][i] : kNoSlot;
+  }
+}
+
+// One wavefront per tile (persistent grid).  The particles stay in registers,
+// four per lane, from the gather to the store; LDS holds what lanes exchange:
+// the ids of each cell for the canonical order, the velocities in that order
+// for the cell sums, the cells' records.  That is 10 KB in FP64 (it was
+// 18.8 KB with the positions and the binning of single cells in LDS), so
+// registers decide the waves per SIMD.
 template <int F, bool W, bool M, bool A, bool X, bool E>
-__global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu((W || A || X) ? 2 : 3)))
+__global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu(A ? 2 : (F == kFormF64 ? 3 : 4))))
 void k_collide(Dev d, uint32_t ntiles, int xcd_remap) {
   using Fm = Form<F>;
   using Vs = typename Fm::Vs;
@@ -1623,35 +1892,34 @@ void k_collide(Dev d, uint32_t ntiles, int xcd_remap) {
   constexpr int NS = kTileCap / kCollideThreads;
   static_assert(kTileMaxCells < NT, "one lane per cell offset (nc + 1) of a tile");
   static_assert(2 * kTileMaxCells <= NT, "two lanes per cell in the cell sums");
+  static_assert(kMaxRuns <= NT, "one lane per run of a tile");
   static_assert(NT == 64, "the workgroup is one wavefront (see wave_sync)");
-  __shared__ uint32_t s_off[kTileMaxCells + 1];
-  __shared__ uint32_t s_idx[kTileCap];   // perm entries, segment order as scattered
-  __shared__ uint32_t s_rk[kTileCap];    // logical index of each entry (ids tracked)
-  __shared__ uint32_t s_idc[kTileCap];   // logical index at the canonical position
-  __shared__ uint8_t s_lc[kTileCap];     // local cell of each slot
-  __shared__ Vs s_v[3][kTileCap];        // streamed velocities, canonical order
-  __shared__ Xs s_x[3][kTileCap];        // streamed positions (offsets), canonical order
-  __shared__ uint32_t s_c[Fm::kHasCell ? kTileCap : 1];
+  // id segments, each padded to a multiple of four (read four at a time);
+  // before the ids: run marks and source slots; after them: far tiles
+  constexpr int kIds = kTileCap + 4 * kTileMaxCells;
+  __shared__ __align__(16) uint32_t s_id[kIds];
+  __shared__ uint32_t s_cnt[kTileMaxCells];
+  __shared__ uint32_t s_off[kTileMaxCells + 1];  // offsets: plain | padded << 16
+  __shared__ uint32_t s_delta[kMaxRuns];
+  __shared__ uint32_t s_grp[kGroups + 1];
+  __shared__ uint32_t s_tot[kTileMaxCells + 1];  // offsets of the whole tile (several passes)
+  __shared__ Vs s_v[3][kTileCap];                // streamed velocities, canonical order
+  __shared__ Xs s_x[A ? 3 : 1][A ? kTileCap : 1];
   __shared__ typename CellRec<F, A>::T s_cell[kTileMaxCells];
-  __shared__ int8_t s_side[E ? kTileCap : 1];  // Lees-Edwards side of each slot
-  __shared__ double s_sh[8];  // shifts of t and t + 1; Lees-Edwards offsets of t + 1, t + 2
-  // next-step window of the tile: cells x0-1 .. x0+nc of the rows (y0 +- 1,
-  // z0 +- 1), plus one entry for particles that leave it; per pass: counts,
-  // then their exclusive prefix (the output order of the pass)
-  constexpr int kWin = 9 * (kTileMaxCells + 2) + 1;
-  __shared__ uint32_t s_pc[kWin];
+  __shared__ int8_t s_side[(E && A) ? kTileCap : 1];  // Lees-Edwards side of each slot
 
   const uint64_t t = as_const(d.ctrl)->step;
   const uint32_t cur = as_const(d.ctrl)->cur;
   const int32_t R = as_const(d.ctrl)->reorder;
-  // the state is always written into the other buffer (cell by cell, each
-  // tile pass grouped by next-step cell); logical indices are renumbered to
-  // the canonical (cell, index) order on reorder steps
+  // the state is always written into the other buffer; logical indices are
+  // renumbered to the canonical (cell, index) order on reorder steps
   const bool renumber = R > 0 && (t + 1) % (uint64_t)R == 0;
+  const uint32_t nxt = cur ^ 1u;
   const StatePtrs in = d.S[cur];
-  const StatePtrs out = d.S[cur ^ 1u];
+  const StatePtrs out = d.S[nxt];
   uint32_t err = 0;
   const uint32_t lane = threadIdx.x;
+  const uint32_t maxr = d.maxr;
 
   TileWalk walk;
   walk.ntiles = ntiles;
@@ -1666,277 +1934,373 @@ void k_collide(Dev d, uint32_t ntiles, int xcd_remap) {
     walk.stride = gridDim.x / 8;
   }
 
-  // Software pipeline over tiles: offsets are fetched two tiles ahead, the
-  // first pass's perm entries and the cell draws one tile ahead.
+  // Software pipeline over tiles: the run list and the output position are
+  // fetched one tile ahead.
+  struct Ahead {
+    uint32_t nrun, np, base;
+    Run run;
+  };
+  auto fetch = [&](const Tile& T, Ahead& a) {
+    const unsigned long long c = as_const(d.tcnt[cur])[T.tid];
+    a.nrun = (uint32_t)c;
+    a.np = (uint32_t)(c >> 32);
+    a.base = as_const(d.toff)[T.tid];
+    a.run = Run{0u, 0u};
+    if (lane < min(a.nrun, maxr)) a.run = d.runs[cur][(size_t)T.tid * maxr + lane];
+  };
+
   uint32_t it = walk.first;
   uint32_t tcur = walk.tile(it);
-  uint32_t tnext = walk.tile(it + walk.stride);
-  uint32_t off_cur = 0, off_next = 0;
+  Tile T, Tn;
+  Ahead cu, ah;
   if (tcur != 0xffffffffu) {
-    const Tile Tc = load_tile(d.tiles, tcur);
-    if (lane <= Tc.nc) off_cur = d.offset[Tc.c0 + lane];
+    T = load_tile(d.tiles, tcur);
+    fetch(T, cu);
   }
-  if (tnext != 0xffffffffu) {
-    const Tile Tn = load_tile(d.tiles, tnext);
-    if (lane <= Tn.nc) off_next = d.offset[Tn.c0 + lane];
-  }
-  uint32_t perm_cur[NS];
-  CellDraw draw_cur;
-  bool have_pf = false;  // perm_cur / draw_cur hold the current tile's data
-  uint32_t cached_box = 0xffffffffu;
 
-  for (; tcur != 0xffffffffu; it += walk.stride) {
-    const Tile T = load_tile(d.tiles, tcur);
+  while (tcur != 0xffffffffu) {
     BoxRef B = as_const(d.boxes)[T.box];
-    const uint32_t tafter = walk.tile(it + 2 * walk.stride);
-    wave_sync();  // LDS of the previous tile is free
-    if (lane <= T.nc) s_off[lane] = off_cur;
-    if (lane == 0 && T.box != cached_box) {
-      double s0[3], s1[3];
-      shift_of(B, t, s0);
-      shift_of(B, t + 1, s1);
-      s_sh[0] = s0[0];
-      s_sh[1] = s0[1];
-      s_sh[2] = s0[2];
-      s_sh[3] = s1[0];
-      s_sh[4] = s1[1];
-      s_sh[5] = s1[2];
-      s_sh[6] = E ? le_offset(B, t + 1) : 0.0;
-      s_sh[7] = E ? le_offset(B, t + 2) : 0.0;
-    }
-    cached_box = T.box;
+    const MPC_AS4 BoxStep& bs = as_const(d.bstep)[T.box];
+    const uint32_t tnext = walk.tile(it + walk.stride);
     const uint32_t lkey0 = T.c0 - B.cbase;
     // tiles lie inside one row: (x0 .. x0 + nc - 1, y0, z0)
-    const int x0 = (int)T.x0, y0 = (int)T.y0, z0 = (int)T.z0;
-    const int WX = (int)T.nc + 2;
+    const int x0 = (int)T.x0, y0 = (int)T.y0, z0 = (int)T.z0, nc = (int)T.nc;
     const int L0 = B.L[0], L1 = B.L[1], L2 = B.L[2];
-    // offsets of the tile after next (two ahead)
-    uint32_t off_after = 0;
-    if (tafter != 0xffffffffu) {
-      const Tile Ta = load_tile(d.tiles, tafter);
-      if (lane <= Ta.nc) off_after = d.offset[Ta.c0 + lane];
-    }
-    wave_sync();
+    // the tiles before and after it in its row
+    const int xn = x0 + nc >= L0 ? 0 : x0 + nc, ncn = min((int)B.T, L0 - xn);
+    const int xp = x0 == 0 ? (int)((B.ntx - 1) * B.T) : x0 - (int)B.T;
+    const int ncp = min((int)B.T, L0 - xp);
+    const int wy = bs.w[0], wz = bs.w[1];
+    const double snext[3] = {bs.sn[0], bs.sn[1], bs.sn[2]};
+    const double st[3] = {bs.s[0], bs.s[1], bs.s[2]};
+    const double d1 = E ? bs.d1 : 0.0, d2 = E ? bs.d2 : 0.0;
+    bool fetched = tnext == 0xffffffffu;
+    if (lane == 0) d.tcnt[cur][T.tid] = 0ull;  // empty for the step after next
 
-    uint32_t perm_next[NS];
-    CellDraw draw_next;
-    bool issued_next = false;
-
-    uint32_t cs = 0;
-    while (cs < T.nc) {
-      const uint32_t base = s_off[cs];
-      // largest ce in (cs, nc] with s_off[ce] - base <= capacity
-      uint32_t ce;
-      if (s_off[T.nc] - base <= (uint32_t)kTileCap) {
-        ce = T.nc;
-      } else {
-        uint32_t lo = cs + 1, hi = T.nc;
-        while (hi - lo > 1) {
-          const uint32_t mid = (lo + hi) / 2;
-          if (s_off[mid] - base <= (uint32_t)kTileCap) {
-            lo = mid;
-          } else {
-            hi = mid;
-          }
-        }
-        ce = lo;
-      }
-      if (s_off[ce] < base || s_off[ce] > d.ntot) {  // inconsistent offsets: stop
+    // local cell of a streamed particle: its row is known (the tile was found
+    // from the same numbers); out of range only after an error
+    auto local_cell = [&](const typename Fm::P& p) -> uint32_t {
+      const uint32_t lc = (uint32_t)(Fm::cell_x(p, st, B, d1, E && B.le) - x0);
+      if (lc >= (uint32_t)nc) {
         err |= kErrKey;
-        break;
+        return 0u;
       }
-      const uint32_t np = s_off[ce] - base;
-      const bool use_pf = have_pf && cs == 0;
+      return lc;
+    };
 
-      if (np > (uint32_t)kTileCap) {
-        // one cell beyond capacity: stream and re-bin its particles unchanged
-        err |= kErrCellOverflow;
-        const double snx[3] = {s_sh[3], s_sh[4], s_sh[5]};
-        for (uint32_t q0 = 0; q0 < np; q0 += NT) {
-          const uint32_t q = q0 + lane;
-          const uint32_t i = q < np ? d.perm[base + q] : d.ntot;
-          const bool live = i < d.ntot;
-          uint32_t kn = 0;
-          if (live) {
+    // a tile of more than one pass, or with chains: particles per cell first
+    const bool slow = cu.np > (uint32_t)kTileCap || cu.nrun > maxr;
+    if (slow) {
+      wave_sync();
+      if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
+      wave_sync();
+      for_each_source(d, cur, T.tid, cu.nrun, lane, [&](uint32_t i, bool on) {
+        if (on) {
+          typename Fm::P p;
+          typename Fm::Vv v;
+          Fm::load(in, i, p, v);
+          Fm::template stream<W>(p, v, B, d1, E && B.le);
+          atomicAdd(&s_cnt[local_cell(p)], 1u);
+        }
+      });
+      wave_sync();
+      const uint32_t n = lane < (uint32_t)kTileMaxCells ? s_cnt[lane] : 0u;
+      const uint32_t inc = wave_scan_dpp(n);
+      if (lane <= (uint32_t)kTileMaxCells) s_tot[lane] = inc - n;
+      wave_sync();
+    }
+
+    uint32_t cs = 0, base = cu.base;
+    do {
+      uint32_t ii[NS], np, ce = (uint32_t)nc;
+      if (slow) {
+        const uint32_t b = s_tot[cs];
+        // largest ce in (cs, nc] with at most one pass of particles
+        if (s_tot[nc] - b > (uint32_t)kTileCap) {
+          uint32_t lo = cs + 1, hi = (uint32_t)nc;
+          while (hi - lo > 1) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (s_tot[mid] - b <= (uint32_t)kTileCap) {
+              lo = mid;
+            } else {
+              hi = mid;
+            }
+          }
+          ce = lo;
+        }
+        np = (uint32_t)__builtin_amdgcn_readfirstlane((int)(s_tot[ce] - b));
+        ce = (uint32_t)__builtin_amdgcn_readfirstlane((int)ce);
+        if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
+        wave_sync();
+        if (np > (uint32_t)kTileCap) {
+          // one cell beyond capacity: its particles are streamed and binned
+          // for the next step, each a run of its own, and do not collide
+          err |= kErrCellOverflow;
+          for_each_source(d, cur, T.tid, cu.nrun, lane, [&](uint32_t i, bool on) {
+            if (on) {
+              typename Fm::P p;
+              typename Fm::Vv v;
+              uint32_t id;
+              Fm::load_all(in, i, p, v, id);
+              Fm::template stream<W>(p, v, B, d1, E && B.le);
+              if (local_cell(p) == cs) {
+                const uint32_t j = base + atomicAdd(&s_cnt[0], 1u);
+                if (j < d.ntot) {
+                  Fm::store_all(out, j, p, v, renumber ? j : id);
+                  Fm::template stream<W>(p, v, B, d2, E && B.le);
+                  int c[3];
+                  Fm::template coords<W>(p, snext, B, c, err, d2, E && B.le);
+                  push_run(d, nxt, tile_of(B, c), j, 1u);
+                }
+              }
+            }
+          });
+          base += np;
+          cs = ce;
+          wave_sync();
+          continue;
+        }
+        // source slots of the pass, cell by cell
+        for_each_source(d, cur, T.tid, cu.nrun, lane, [&](uint32_t i, bool on) {
+          if (on) {
             typename Fm::P p;
             typename Fm::Vv v;
-            uint32_t id;
-            Fm::load_all(in, i, p, v, id);
-            Fm::template stream<W>(p, v, B, s_sh[6], E && B.le);
-            const uint32_t j = base + q;
-            Fm::store_all(out, j, p, v, renumber ? j : id);
-            Fm::template stream<W>(p, v, B, s_sh[7], E && B.le);
-            kn = B.cbase + Fm::template key<W>(p, snx, B, err, s_sh[7], E && B.le);
-            d.key[j] = kn;
+            Fm::load(in, i, p, v);
+            Fm::template stream<W>(p, v, B, d1, E && B.le);
+            const uint32_t lc = local_cell(p);
+            if (lc >= cs && lc < ce) {
+              const uint32_t q = s_tot[lc] - b + atomicAdd(&s_cnt[lc], 1u);
+              if (q < (uint32_t)kTileCap) s_id[q] = i;
+            }
           }
-          const uint32_t rk = wave_hist_rank(d.hist, kn, live);
-          if (live) d.rank[base + q] = (uint16_t)min(rk, 0xffffu);
-        }
-        cs = ce;
+        });
         wave_sync();
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          ii[k] = q < np ? s_id[q] : 0u;
+        }
+        wave_sync();
+      } else {
+        // slots of the runs, one after the other: a mark at the first entry
+        // of each run, and per run the distance from entry to slot
+        const uint32_t inc = wave_scan_dpp(cu.run.count);
+        const uint32_t pre = inc - cu.run.count;
+        np = min((uint32_t)__builtin_amdgcn_readlane((int)inc, 63), (uint32_t)kTileCap);
+        if (np != cu.np) err |= kErrKey;
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < NS; ++k) s_id[lane + k * NT] = 0u;
+        wave_sync();
+        if (cu.run.count && pre < (uint32_t)kTileCap) {
+          s_id[pre] = 1u;
+          s_delta[lane] = cu.run.start - pre;
+        }
+        wave_sync();
+        uint32_t before = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          const bool mk = s_id[q] != 0u;
+          const uint64_t m = __ballot(mk);
+          const uint32_t r = before + lanes_below(m) + (mk ? 1u : 0u);
+          before += (uint32_t)__popcll(m);
+          ii[k] = q < np ? s_delta[r - 1u] + q : 0u;
+        }
+        wave_sync();
+      }
+
+      if (np == 0u) {
+        cs = ce;
         continue;
       }
 
-      // Phase A: segment entries (prefetched for the first pass) and their
-      // cell
+      // gather (one memory round trip), stream, local cells
+      typename Fm::P p[NS];
+      typename Fm::Vv v[NS];
+      uint32_t idk[NS], meta[NS];
+      // issue the gathers ahead of other waves' arithmetic
+      __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * NT;
-        if (q < np) s_idx[q] = use_pf ? perm_cur[k] : d.perm[base + q];
+        idk[k] = 0u;
+        if (q < np) Fm::load_all(in, ii[k] < d.ntot ? ii[k] : 0u, p[k], v[k], idk[k]);
       }
-      if (cs + lane < ce) {
-        const uint32_t c = cs + lane;
-        const uint32_t b = s_off[c] - base, e = s_off[c + 1] - base;
-        for (uint32_t q = b; q < e; ++q) s_lc[q] = (uint8_t)(c - cs);
-      }
-      wave_sync();
-
-      // Phase B: gather, canonical position (rank by logical index inside
-      // the cell), stream of step t, park in LDS.
+      // with the gather: the draws of cell cs + j, by lanes 2j and 2j + 1
+      double axis[3], z0g;
+      uint32_t least;
       {
-        // the logical indices are gathered with the state (one memory round
-        // trip per pass), then put in LDS for the in-cell ranking
-        typename Fm::P p[NS];
-        typename Fm::Vv v[NS];
-        uint32_t ii[NS], idk[NS];
-        // issue the gathers ahead of other waves' arithmetic
-        __builtin_amdgcn_s_setprio(2);
+        const uint32_t c = T.c0 + min(cs + (lane >> 1), (uint32_t)nc - 1u);
+        const double2* r = (const double2*)d.draws + 2 * (size_t)c;
+        const double2 r0 = r[0], r1 = r[1];
+        axis[0] = r0.x;
+        axis[1] = r0.y;
+        axis[2] = r1.x;
+        z0g = r1.y;
+        least = M ? d.least[c] : 0u;
+      }
+      if (!fetched) {
+        fetched = true;
+        Tn = load_tile(d.tiles, tnext);
+        fetch(Tn, ah);
+      }
+      __builtin_amdgcn_s_setprio(0);
+      if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
+      if (lane < (uint32_t)kGroups + 1u) s_grp[lane] = 0u;
+      for (uint32_t q = lane; q < (uint32_t)kIds / 4; q += NT)
+        ((uint4*)s_id)[q] = make_uint4(kNoSlot, kNoSlot, kNoSlot, kNoSlot);
+      wave_sync();
 #pragma unroll
-        for (int k = 0; k < NS; ++k) {
-          const uint32_t q = lane + k * NT;
-          ii[k] = 0;
-          idk[k] = 0;
-          if (q < np) {
-            ii[k] = s_idx[q] < d.ntot ? s_idx[q] : 0u;
-            Fm::load_all(in, ii[k], p[k], v[k], idk[k]);
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * NT;
+        meta[k] = 0u;
+        if (q < np) {
+          Fm::template stream<W>(p[k], v[k], B, d1, E && B.le);
+          const uint32_t lc = local_cell(p[k]);
+          meta[k] = lc | atomicAdd(&s_cnt[lc], 1u) << 8;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wave_sync();
+      {
+        const uint32_t n = lane < (uint32_t)kTileMaxCells ? s_cnt[lane] : 0u;
+        const uint32_t w = n | ((n + 3u) & ~3u) << 16;
+        const uint32_t inc = wave_scan_dpp(w);
+        if (lane <= (uint32_t)kTileMaxCells) s_off[lane] = inc - w;
+      }
+      wave_sync();
+      // canonical position: rank by logical index inside the cell
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * NT;
+        if (q < np) s_id[(s_off[meta[k] & 0xffu] >> 16) + (meta[k] >> 8)] = idk[k];
+      }
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * NT;
+        if (q < np) {
+          const uint32_t lc = meta[k] & 0xffu;
+          const uint32_t o = s_off[lc], o1 = s_off[lc + 1];
+          const uint32_t b = o & 0xffffu;
+          uint32_t r = 0;
+          for (uint32_t a = o >> 16; a < o1 >> 16; a += 4) {
+            const uint4 w = *(const uint4*)&s_id[a];
+            r += (w.x < idk[k] ? 1u : 0u) + (w.y < idk[k] ? 1u : 0u) + (w.z < idk[k] ? 1u : 0u) +
+                 (w.w < idk[k] ? 1u : 0u);
           }
-        }
-        // prefetch the next tile's first-pass perm entries and cell draws
-        if (!issued_next && tnext != 0xffffffffu) {
-          issued_next = true;
-          const Tile Tn = load_tile(d.tiles, tnext);
-          const uint32_t nb = (uint32_t)__builtin_amdgcn_readfirstlane((int)off_next);
-          const uint32_t ne = (uint32_t)__builtin_amdgcn_readlane((int)off_next, Tn.nc);
-          const uint32_t nn = ne >= nb ? ne - nb : 0u;
-#pragma unroll
-          for (int k = 0; k < NS; ++k) {
-            const uint32_t q = lane + k * NT;
-            perm_next[k] = (q < nn && nb + q < d.ntot) ? d.perm[nb + q] : 0u;
-          }
-          if (lane < Tn.nc) draw_next = d.draws[Tn.c0 + lane];
-        }
-        __builtin_amdgcn_s_setprio(0);
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-          const uint32_t q = lane + k * NT;
-          if (q < np) s_rk[q] = idk[k];
-        }
-        wave_sync();
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-          const uint32_t q = lane + k * NT;
-          __builtin_amdgcn_sched_barrier(0);
-          if (q < np) {
-            const uint32_t c = cs + s_lc[q];
-            const uint32_t b = s_off[c] - base, e = s_off[c + 1] - base;
-            const uint32_t id = s_rk[q];
-            const uint32_t qc = b + rank_in_segment(s_rk, b, e, id);
-            Fm::template stream<W>(p[k], v[k], B, s_sh[6], E && B.le);
-            if constexpr (E) {
-              const int side = B.le ? Fm::le_side(p[k], s_sh[2], B) : 0;
-              s_side[qc] = (int8_t)side;
-              if (e - b >= 2u) {
-                // a colliding cell across a z face: its image's velocity frame
-                if (side < 0) v[k].v[0] = (Vs)((double)v[k].v[0] - B.leu);
-                if (side > 0) v[k].v[0] = (Vs)((double)v[k].v[0] + B.leu);
-              }
+          const uint32_t qc = min(b + r, (uint32_t)kTileCap - 1u);
+          if constexpr (E) {
+            const int side = B.le ? Fm::le_side(p[k], st[2], B) : 0;
+            if ((o1 & 0xffffu) - b >= 2u) {
+              // a colliding cell across a z face: its image's velocity frame
+              if (side < 0) v[k].v[0] = (Vs)((double)v[k].v[0] - B.leu);
+              if (side > 0) v[k].v[0] = (Vs)((double)v[k].v[0] + B.leu);
             }
-            Fm::to_lds(p[k], s_x[0], s_x[1], s_x[2], s_c, qc);
-            s_v[0][qc] = v[k].v[0];
-            s_v[1][qc] = v[k].v[1];
-            s_v[2][qc] = v[k].v[2];
-            s_idc[qc] = id;
+            if constexpr (A) s_side[qc] = (int8_t)side;
           }
+          s_v[0][qc] = v[k].v[0];
+          s_v[1][qc] = v[k].v[1];
+          s_v[2][qc] = v[k].v[2];
+          if constexpr (A) {
+            s_x[0][qc] = Fm::pos(p[k], 0);
+            s_x[1][qc] = Fm::pos(p[k], 1);
+            s_x[2][qc] = Fm::pos(p[k], 2);
+          }
+          meta[k] = lc | qc << 8;
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
       wave_sync();
 
-      // Phase C: two lanes per cell (lanes 2j and 2j + 1 for cell cs + j); the
-      // first pass uses the prefetched draws, which lane j holds
+      // cell sums: two lanes per cell (lanes 2j and 2j + 1 for cell cs + j)
       {
         const uint32_t j = lane >> 1;
         const uint32_t c = cs + j;
         const bool valid = c < ce;
-        const uint32_t b = valid ? s_off[c] - base : 0u, e = valid ? s_off[c + 1] - base : 0u;
-        CellDraw cd;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) cd.n[k] = __shfl(draw_cur.n[k], (int)j, 64);
-        cd.Ek = __shfl(draw_cur.Ek, (int)j, 64);
-        if (!use_pf) {
-          if (valid && e > b) {
-            cd = d.draws[T.c0 + c];
-          } else {
-            cd.n[0] = cd.n[1] = cd.n[2] = 0.0;
-            cd.Ek = 0.0;
+        const uint32_t b = valid ? s_off[c] & 0xffffu : 0u, e = valid ? s_off[c + 1] & 0xffffu : 0u;
+        // thermostat: target energy E_k = kT * Gamma(3 (n - 1) / 2), n with
+        // phantoms; 0 means "no scaling"
+        double Ek = 0.0;
+        if constexpr (M) {
+          uint32_t n = e - b;
+          if (W && !B.slip && valid && n > 0) {
+            if (wall_fraction(st[2], z0 - 1, L2) > 0.0) n += (uint32_t)d.phs[T.c0 + c].n;
+          }
+          const bool draw = e > b && n >= 2u;
+          if (draw) {
+            double z = z0g;
+            bool ok = n >= (least & 0xffffu);
+            if (!ok) {  // the first listed attempt that n accepts
+              const Attempt* seg = d.later + (size_t)((T.c0 + c) / d.drawb) * (d.drawb / 4);
+              uint32_t a = least >> 16;
+              while (a && !ok) {
+                const Attempt at = seg[a];
+                z = at.z;
+                ok = n >= at.least;
+                a = at.next;
+              }
+            }
+            const GammaDC g = gamma_dc(n);
+            const double vv = 1.0 + g.c * z;
+            if (ok) Ek = B.kT * (g.d * (vv * vv * vv));
           }
         }
-        const double s_t[3] = {s_sh[0], s_sh[1], s_sh[2]};
-        cell_work<F, W, M, A, X>(B, lkey0 + c, s_sh[2], cd,
+        cell_work<F, W, M, A, X>(B, lkey0 + c, st[2], axis, Ek,
                                  W ? d.phs + T.c0 + (valid ? c : 0u) : nullptr, s_v[0], s_v[1],
-                                 s_v[2], s_x[0], s_x[1], s_x[2], s_t, b, e, lane & 1u, valid,
-                                 &s_cell[j], err, E ? s_side : nullptr, s_sh[6]);
+                                 s_v[2], s_x[0], s_x[A ? 1 : 0], s_x[A ? 2 : 0], st, b, e,
+                                 lane & 1u, valid, &s_cell[valid ? c : 0u], err,
+                                 (E && A) ? s_side : nullptr, d1);
       }
       wave_sync();
 
-      // Phase D1: rotate + scale, gravity; the next step's cell of each
-      // particle and its rank among the pass's particles going there
-      for (int i = (int)lane; i < 9 * WX + 1; i += NT) s_pc[i] = 0u;
-      wave_sync();
-      const double snext[3] = {s_sh[3], s_sh[4], s_sh[5]};
+      // rotate + scale, gravity; the group of each particle: the next step's
+      // tile, one of three in each of nine rows, or "far"; its place there
+      uint32_t gk[NS];
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * NT;
+        gk[k] = 0u;
         __builtin_amdgcn_sched_barrier(0);
         if (q < np) {
-          typename Fm::P p;
-          typename Fm::Vv v;
-          Fm::from_lds(p, s_x[0], s_x[1], s_x[2], s_c, q);
-          v.v[0] = s_v[0][q];
-          v.v[1] = s_v[1][q];
-          v.v[2] = s_v[2][q];
-          const auto& C = s_cell[s_lc[q]];
+          const uint32_t lc = meta[k] & 0xffu;
+          const auto& C = s_cell[lc];
+          int side = 0;
+          if constexpr (E) side = B.le ? Fm::le_side(p[k], st[2], B) : 0;
+          auto& vv = v[k].v;
           if constexpr (F == kFormSplit) {
             if (C.coll != 0.0f) {
-              const float u[3] = {v.v[0] - C.V[0], v.v[1] - C.V[1], v.v[2] - C.V[2]};
+              const float u[3] = {vv[0] - C.V[0], vv[1] - C.V[1], vv[2] - C.V[2]};
 #pragma unroll
               for (int a = 0; a < 3; ++a)
-                v.v[a] = C.V[a] + fmaf(C.R[3 * a], u[0], fmaf(C.R[3 * a + 1], u[1], C.R[3 * a + 2] * u[2]));
+                vv[a] = C.V[a] + fmaf(C.R[3 * a], u[0], fmaf(C.R[3 * a + 1], u[1], C.R[3 * a + 2] * u[2]));
               if constexpr (A) {
                 // omega x r_ic in FP64 (|omega| is large in ill-conditioned
                 // cells), added to the FP32 rotation result with one rounding
-                double xq = (double)s_x[0][q];
+                double xq = (double)Fm::pos(p[k], 0);
                 if constexpr (E) {
-                  if (s_side[q] < 0) xq = xq - s_sh[6];
-                  if (s_side[q] > 0) xq = xq + s_sh[6];
+                  if (side < 0) xq = xq - d1;
+                  if (side > 0) xq = xq + d1;
                 }
-                const double r[3] = {frame_pos(xq, s_sh[0]) - C.rc[0],
-                                     frame_pos(s_x[1][q], s_sh[1]) - C.rc[1],
-                                     frame_pos(s_x[2][q], s_sh[2]) - C.rc[2]};
-                v.v[0] = (float)((double)v.v[0] + (C.om[1] * r[2] - C.om[2] * r[1]));
-                v.v[1] = (float)((double)v.v[1] + (C.om[2] * r[0] - C.om[0] * r[2]));
-                v.v[2] = (float)((double)v.v[2] + (C.om[0] * r[1] - C.om[1] * r[0]));
+                const double r[3] = {frame_pos(xq, st[0]) - C.rc[0],
+                                     frame_pos(Fm::pos(p[k], 1), st[1]) - C.rc[1],
+                                     frame_pos(Fm::pos(p[k], 2), st[2]) - C.rc[2]};
+                vv[0] = (float)((double)vv[0] + (C.om[1] * r[2] - C.om[2] * r[1]));
+                vv[1] = (float)((double)vv[1] + (C.om[2] * r[0] - C.om[0] * r[2]));
+                vv[2] = (float)((double)vv[2] + (C.om[0] * r[1] - C.om[1] * r[0]));
               }
               if constexpr (E) {  // leave the Lees-Edwards image frame
-                if (s_side[q] < 0) v.v[0] = (float)((double)v.v[0] + B.leu);
-                if (s_side[q] > 0) v.v[0] = (float)((double)v.v[0] - B.leu);
+                if (side < 0) vv[0] = (float)((double)vv[0] + B.leu);
+                if (side > 0) vv[0] = (float)((double)vv[0] - B.leu);
               }
             }
             if (B.grav) {
 #pragma unroll
-              for (int a = 0; a < 3; ++a) v.v[a] = v.v[a] + (float)B.gh[a];
+              for (int a = 0; a < 3; ++a) vv[a] = vv[a] + (float)B.gh[a];
             }
           } else {
-            double w[3] = {(double)v.v[0], (double)v.v[1], (double)v.v[2]};
+            double w[3] = {(double)vv[0], (double)vv[1], (double)vv[2]};
             if (C.kappa != 0.0) {
               const double u[3] = {w[0] - C.V[0], w[1] - C.V[1], w[2] - C.V[2]};
               const double nd[3] = {C.n[0], C.n[1], C.n[2]};
@@ -1945,21 +2309,21 @@ void k_collide(Dev d, uint32_t ntiles, int xcd_remap) {
 #pragma unroll
               for (int a = 0; a < 3; ++a) w[a] = C.V[a] + C.kappa * r[a];
               if constexpr (A) {
-                double xq = (double)s_x[0][q];
+                double xq = (double)Fm::pos(p[k], 0);
                 if constexpr (E) {
-                  if (s_side[q] < 0) xq = xq - s_sh[6];
-                  if (s_side[q] > 0) xq = xq + s_sh[6];
+                  if (side < 0) xq = xq - d1;
+                  if (side > 0) xq = xq + d1;
                 }
-                const double rr[3] = {frame_pos(xq, s_sh[0]) - C.rc[0],
-                                      frame_pos(s_x[1][q], s_sh[1]) - C.rc[1],
-                                      frame_pos(s_x[2][q], s_sh[2]) - C.rc[2]};
+                const double rr[3] = {frame_pos(xq, st[0]) - C.rc[0],
+                                      frame_pos(Fm::pos(p[k], 1), st[1]) - C.rc[1],
+                                      frame_pos(Fm::pos(p[k], 2), st[2]) - C.rc[2]};
                 w[0] = w[0] + (C.om[1] * rr[2] - C.om[2] * rr[1]);
                 w[1] = w[1] + (C.om[2] * rr[0] - C.om[0] * rr[2]);
                 w[2] = w[2] + (C.om[0] * rr[1] - C.om[1] * rr[0]);
               }
               if constexpr (E) {  // leave the Lees-Edwards image frame
-                if (s_side[q] < 0) w[0] = w[0] + B.leu;
-                if (s_side[q] > 0) w[0] = w[0] - B.leu;
+                if (side < 0) w[0] = w[0] + B.leu;
+                if (side > 0) w[0] = w[0] - B.leu;
               }
             }
             if (B.grav) {
@@ -1967,131 +2331,142 @@ void k_collide(Dev d, uint32_t ntiles, int xcd_remap) {
               for (int a = 0; a < 3; ++a) w[a] = w[a] + B.gh[a];
             }
 #pragma unroll
-            for (int a = 0; a < 3; ++a) v.v[a] = (Vs)w[a];
+            for (int a = 0; a < 3; ++a) vv[a] = (Vs)w[a];
           }
-          // v' back in place; the next step's cell and its window entry
-          s_v[0][q] = v.v[0];
-          s_v[1][q] = v.v[1];
-          s_v[2][q] = v.v[2];
-          Fm::template stream<W>(p, v, B, s_sh[7], E && B.le);
+          typename Fm::P pn = p[k];
+          typename Fm::Vv vn = v[k];
+          Fm::template stream<W>(pn, vn, B, d2, E && B.le);
           int c[3];
-          Fm::template coords<W>(p, snext, B, c, err, s_sh[7], E && B.le);
-          const uint32_t kn = B.cbase + linear_key(c, B);
-          int r, dx;
-          uint32_t e = (uint32_t)(9 * WX);  // outside the window: counted in D2
-          if (win_entry<W>(c, x0, y0, z0, WX, L0, L1, L2, r, dx)) e = (uint32_t)(r * WX + dx);
-          const uint32_t rank = atomicAdd(&s_pc[e], 1u);
-          s_idx[q] = e << 16 | rank;
-          s_rk[q] = kn;
+          Fm::template coords<W>(pn, snext, B, c, err, d2, E && B.le);
+          const int seg = (unsigned)(c[0] - x0) < (unsigned)nc    ? 1
+                          : (unsigned)(c[0] - xp) < (unsigned)ncp ? 0
+                          : (unsigned)(c[0] - xn) < (unsigned)ncn ? 2
+                                                                  : 3;
+          const int ry = wrap1(c[1] - y0 - wy, L1);
+          const int rz = W ? c[2] - z0 - wz : wrap1(c[2] - z0 - wz, L2);
+          uint32_t g = (uint32_t)((rz * 3 + ry) * 3 + seg);
+          if (!((unsigned)ry < 3u && (unsigned)rz < 3u && seg < 3)) {
+            g = (uint32_t)kGroups;
+            s_id[q] = tile_of(B, c);
+          }
+          gk[k] = g | atomicAdd(&s_grp[g], 1u) << 8;
         }
       }
       wave_sync();
-      // Per window entry (5 per lane): add the pass's count to the next
-      // step's histogram, whose old value is the rank base of these particles
-      // in their cell (used after D2, so that the atomics' latency overlaps
-      // the stores); and the exclusive prefix of the counts, which orders the
-      // pass's output.
-      uint32_t rb5[5];
+      // the groups one after the other in the pass's output; a run for each
+      uint32_t far0, nfar;
+      uint32_t gn = 0, gpre, gdest = kNoSlot;
       {
-        const int ne = 9 * WX + 1;
-        const int i0 = (int)lane * 5;
-        uint32_t cnt5[5];
-        uint32_t sum = 0;
+        gn = lane < (uint32_t)kGroups + 1u ? s_grp[lane] : 0u;
+        gpre = wave_scan_dpp(gn) - gn;
+        if (lane < (uint32_t)kGroups + 1u) s_grp[lane] = gpre;
+        far0 = (uint32_t)__builtin_amdgcn_readlane((int)gpre, kGroups);
+        nfar = (uint32_t)__builtin_amdgcn_readlane((int)gn, kGroups);
+        if (lane < (uint32_t)kGroups && gn) {
+          const int row = (int)lane / 3, seg = (int)lane - 3 * row;
+          const int rz = row / 3, ry = row - 3 * rz;
+          const int y = wrap1(y0 + wy + ry, L1);
+          const int z = W ? z0 + wz + rz : wrap1(z0 + wz + rz, L2);
+          const int xs = seg == 0 ? xp : (seg == 1 ? x0 : xn);
+          gdest = B.tbase + ((uint32_t)z * (uint32_t)L1 + (uint32_t)y) * B.ntx +
+                  (uint32_t)xs / B.T;
+        }
+      }
+      wave_sync();
+      if (__builtin_expect(nfar != 0u, 0)) {
+        // far particles: one run per destination, found one by one
+        uint32_t fd[NS], fpos[NS];
+        uint64_t left[NS];
 #pragma unroll
-        for (int m = 0; m < 5; ++m) {
-          const int i = i0 + m;
-          cnt5[m] = i < ne ? s_pc[i] : 0u;
-          sum += cnt5[m];
-          rb5[m] = 0u;
-          if (i < ne - 1 && cnt5[m]) {
-            const int rr = i / WX, dx = i - rr * WX;
-            int c[3] = {x0 - 1 + dx, y0 + rr % 3 - 1, z0 + rr / 3 - 1};
-            c[0] = wrap1(c[0], L0);
-            c[1] = wrap1(c[1], L1);
-            if (!W) c[2] = wrap1(c[2], L2);
-            rb5[m] = atomicAdd(&d.hist[B.cbase + linear_key(c, B)], cnt5[m]);
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          const bool far = q < np && (gk[k] & 0xffu) == (uint32_t)kGroups;
+          fd[k] = far ? s_id[q] : kNoSlot;
+          left[k] = __ballot(far);
+          fpos[k] = 0u;
+        }
+        uint32_t done = 0, ng = 0, rd = kNoSlot, rs = 0, rn = 0;
+        while (done < nfar) {
+          uint32_t dest = 0;
+          bool found = false;
+#pragma unroll
+          for (int k = 0; k < NS; ++k)
+            if (!found && left[k]) {
+              dest = (uint32_t)__builtin_amdgcn_readlane((int)fd[k], __ffsll((unsigned long long)left[k]) - 1);
+              found = true;
+            }
+          if (!found) break;
+          uint32_t n = 0;
+#pragma unroll
+          for (int k = 0; k < NS; ++k) {
+            const bool same = (left[k] >> lane & 1ull) && fd[k] == dest;
+            const uint64_t m = __ballot(same);
+            if (same) fpos[k] = done + n + lanes_below(m);
+            n += (uint32_t)__popcll(m);
+            left[k] &= ~m;
+          }
+          if (lane == (ng & 63u)) {
+            rd = dest;
+            rs = done;
+            rn = n;
+          }
+          done += n;
+          if ((++ng & 63u) == 0u || done >= nfar) {
+            if (rn) push_run(d, nxt, rd, base + far0 + rs, rn);
+            rn = 0u;
           }
         }
-        const uint32_t incl = wave_inclusive_scan(sum);
-        uint32_t run = incl - sum;
 #pragma unroll
-        for (int m = 0; m < 5; ++m) {
-          if (i0 + m < ne) s_pc[i0 + m] = run;
-          run += cnt5[m];
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          if (q < np && (gk[k] & 0xffu) == (uint32_t)kGroups)
+            gk[k] = (uint32_t)kGroups | fpos[k] << 8;
         }
       }
-      wave_sync();
-      // D2: the pass's particles, grouped by next-step cell, into its slots;
+      if (gdest != kNoSlot) push_run(d, nxt, gdest, base + gpre, gn);
+      // the pass's particles, grouped by next-step tile, into its slots;
       // logical indices: the canonical (cell, index) position on reorder steps
       __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * NT;
-        __builtin_amdgcn_sched_barrier(0);
         if (q < np) {
-          const uint32_t pk = s_idx[q];
-          const uint32_t j = base + s_pc[pk >> 16] + (pk & 0xffffu);
-          const uint32_t kn = s_rk[q];
-          s_rk[q] = j;
-          if (j < d.ntot && j < base + np) {
-            typename Fm::P p;
-            typename Fm::Vv v;
-            Fm::from_lds(p, s_x[0], s_x[1], s_x[2], s_c, q);
-            v.v[0] = s_v[0][q];
-            v.v[1] = s_v[1][q];
-            v.v[2] = s_v[2][q];
-            Fm::store_all(out, j, p, v, renumber ? base + q : s_idc[q]);
-            d.key[j] = kn;
-            // leaving the window: counted one by one
-            if ((pk >> 16) == (uint32_t)(9 * WX))
-              d.rank[j] = (uint16_t)min(atomicAdd(&d.hist[kn], 1u), 0xffffu);
+          const uint32_t j = base + s_grp[gk[k] & 0xffu] + (gk[k] >> 8);
+          if (j < d.ntot) {
+            Fm::store_all(out, j, p[k], v[k], renumber ? base + (meta[k] >> 8) : idk[k]);
           } else {
             err |= kErrKey;
           }
         }
       }
       __builtin_amdgcn_s_setprio(0);
-      // D3: ranks inside the next-step cells (rank base of the entry + place)
-      wave_sync();
-      {
-        const int ne = 9 * WX + 1;
-#pragma unroll
-        for (int m = 0; m < 5; ++m) {
-          const int i = (int)lane * 5 + m;
-          if (rb5[m] > 0xffffu) {
-            err |= kErrCellOverflow;
-            rb5[m] = 0xffffu;
-          }
-          if (i < ne) s_pc[i] = rb5[m];
-        }
-      }
-      wave_sync();
-#pragma unroll
-      for (int k = 0; k < NS; ++k) {
-        const uint32_t q = lane + k * NT;
-        if (q < np) {
-          const uint32_t pk = s_idx[q];
-          const uint32_t j = s_rk[q];
-          if ((pk >> 16) != (uint32_t)(9 * WX) && j < d.ntot && j < base + np)
-            d.rank[j] = (uint16_t)min(s_pc[pk >> 16] + (pk & 0xffffu), 0xffffu);
-        }
-      }
+      base += np;
       cs = ce;
       wave_sync();
-    }
+    } while (cs < (uint32_t)nc);
+    if (slow && lane < maxr) d.rhead[cur][(size_t)T.tid * maxr + lane] = kNoSlot;
     // advance the pipeline
+    it += walk.stride;
     tcur = tnext;
-    tnext = tafter;
-    off_cur = off_next;
-    off_next = off_after;
-    have_pf = issued_next;
-    if (issued_next) {
-#pragma unroll
-      for (int k = 0; k < NS; ++k) perm_cur[k] = perm_next[k];
-      draw_cur = draw_next;
+    if (tnext != 0xffffffffu) {
+      if (!fetched) {
+        Tn = load_tile(d.tiles, tnext);
+        fetch(Tn, ah);
+      }
+      T = Tn;
+      cu = ah;
     }
   }
   if (err) atomicOr(&d.ctrl->err, err);
+  // the last workgroup to finish moves on to the next step (every other one
+  // has read the step and the buffer index before)
+  if (lane == 0) {
+    if (atomicAdd(&d.ctrl->done, 1u) == gridDim.x - 1u) {
+      d.ctrl->done = 0u;
+      d.ctrl->cur = nxt;
+      d.ctrl->step = t + 1;
+    }
+  }
 }
 
 // Runtime flags (form, walls, thermostat, SRD+a, fixed-point sums,
@@ -2385,19 +2760,169 @@ __device__ __forceinline__ double block_sum_d(double x, double* s_red) {
   return r;
 }
 
+// Order in which the observables of an FP64 box add its particles after a
+// step: by obs tile (To cells of a row), in it by pass (as many whole cells as
+// kObsPass particles allow), in a pass by the particle's cell of the next step
+// (rows y +- 1, z +- 1 around the tile, cells x0 - 1 .. x0 + nc of each row;
+// all others last), then by cell and logical index.  The slots themselves
+// depend on the order in which runs were appended; a total momentum is a sum
+// of rounding errors, and in slot order its digits would change from run to
+// run.  One wavefront per obs tile; the particles of its cells lie in the
+// output of one to three collide tiles, which it reads twice (3 ms at 256^3
+// with the sums, against 100 ms for 20 steps).
+template <bool W>
+__global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t cur, uint32_t To,
+                                                  uint32_t* __restrict__ order) {
+  using Fm = Form<kFormF64>;
+  constexpr int kWin = 9 * (kTileMaxCells + 2) + 1;
+  constexpr int NS = kObsPass / 64;
+  static_assert(kWin <= 5 * 64, "five window entries per lane");
+  __shared__ uint32_t s_cnt[kTileMaxCells], s_off[kTileMaxCells + 1], s_before;
+  __shared__ uint32_t s_id[kObsPass], s_slot[kObsPass], s_can[kObsPass], s_pc[kWin];
+  __shared__ uint8_t s_lc[kObsPass];
+  const uint32_t lane = threadIdx.x;
+  BoxRef B = as_const(d.boxes)[box];
+  const MPC_AS4 BoxStep& bs = as_const(d.bstep)[box];
+  const StatePtrs S = d.S[cur];
+  const int L0 = B.L[0], L1 = B.L[1], L2 = B.L[2];
+  const uint32_t nx = ((uint32_t)L0 + To - 1) / To;
+  const uint32_t row = blockIdx.x / nx;
+  const int x0 = (int)((blockIdx.x - row * nx) * To);
+  const int y0 = (int)(row % (uint32_t)L1), z0 = (int)(row / (uint32_t)L1);
+  const int nc = min((int)To, L0 - x0), WX = nc + 2;
+  const uint32_t t0 = B.tbase + row * B.ntx + (uint32_t)x0 / B.T;
+  const uint32_t t1 = B.tbase + row * B.ntx + (uint32_t)(x0 + nc - 1) / B.T;
+  const uint32_t i0 = d.toff[t0];
+  const uint32_t i1 = min(t1 + 1u < d.ntile ? d.toff[t1 + 1] : d.ntot, d.ntot);
+  const double st[3] = {bs.s[0], bs.s[1], bs.s[2]};
+  const double sn[3] = {bs.sn[0], bs.sn[1], bs.sn[2]};
+  const bool le = !W && B.le;
+  uint32_t err = 0;
+  // stored positions are those of the last step's collision
+  auto local = [&](uint32_t i) -> int {
+    typename Fm::P p;
+    typename Fm::Vv v;
+    Fm::load(S, i, p, v);
+    return Fm::cell_x(p, st, B, bs.d1, le) - x0;
+  };
+  if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
+  if (lane == 0) s_before = 0u;
+  wave_sync();
+  for (uint32_t i = i0 + lane; i < i1; i += 64) {
+    const int c = local(i);
+    if (c < 0) {
+      atomicAdd(&s_before, 1u);
+    } else if (c < nc) {
+      atomicAdd(&s_cnt[c], 1u);
+    }
+  }
+  wave_sync();
+  {
+    const uint32_t n = lane < (uint32_t)kTileMaxCells ? s_cnt[lane] : 0u;
+    const uint32_t inc = wave_scan_dpp(n);
+    if (lane <= (uint32_t)kTileMaxCells) s_off[lane] = inc - n;
+  }
+  wave_sync();
+  uint32_t base = i0 + s_before;
+  for (int cs = 0; cs < nc;) {
+    const uint32_t b = s_off[cs];
+    int ce = cs + 1;
+    while (ce < nc && s_off[ce + 1] - b <= (uint32_t)kObsPass) ++ce;
+    const uint32_t np = s_off[ce] - b;
+    if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
+    for (uint32_t q = lane; q < (uint32_t)kWin; q += 64) s_pc[q] = 0u;
+    wave_sync();
+    for (uint32_t i = i0 + lane; i < i1; i += 64) {
+      const int c = local(i);
+      if (c < cs || c >= ce) continue;
+      const uint32_t q = s_off[c] - b + atomicAdd(&s_cnt[c], 1u);
+      if (np > (uint32_t)kObsPass) {  // a cell that did not collide
+        if (base + q < d.ntot) order[base + q] = i;
+      } else if (q < (uint32_t)kObsPass) {
+        s_id[q] = S.id[i];
+        s_slot[q] = i;
+        s_lc[q] = (uint8_t)c;
+      }
+    }
+    wave_sync();
+    if (np <= (uint32_t)kObsPass) {
+      for (uint32_t q = lane; q < np; q += 64) {
+        const uint32_t c = s_lc[q], e = s_off[c + 1] - b, id = s_id[q];
+        uint32_t r = s_off[c] - b;
+        for (uint32_t k = r; k < e; ++k) r += s_id[k] < id ? 1u : 0u;
+        s_can[min(r, (uint32_t)kObsPass - 1u)] = s_slot[q];
+      }
+      wave_sync();
+      uint32_t place[NS];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * 64;
+        place[k] = 0u;
+        __builtin_amdgcn_sched_barrier(0);
+        if (q < np) {
+          typename Fm::P p;
+          typename Fm::Vv v;
+          Fm::load(S, s_can[q], p, v);
+          Fm::template stream<W>(p, v, B, bs.d2, le);
+          int c[3];
+          Fm::template coords<W>(p, sn, B, c, err, bs.d2, le);
+          const int dx = wrap1(c[0] - x0 + 1, L0);
+          int dy = c[1] - y0, dz = c[2] - z0;
+          dy += L1 & -(int)(dy < -1);
+          dy -= L1 & -(int)(dy > 1);
+          if (!W) {
+            dz += L2 & -(int)(dz < -1);
+            dz -= L2 & -(int)(dz > 1);
+          }
+          const bool near = (unsigned)dx < (unsigned)WX && (unsigned)(dy + 1) < 3u &&
+                            (unsigned)(dz + 1) < 3u;
+          const uint32_t e = near ? (uint32_t)(((dz + 1) * 3 + dy + 1) * WX + dx) : (uint32_t)(9 * WX);
+          place[k] = e << 16 | atomicAdd(&s_pc[e], 1u);
+        }
+      }
+      wave_sync();
+      uint32_t n5[5], sum = 0;
+#pragma unroll
+      for (int m = 0; m < 5; ++m) {
+        const int i = (int)lane * 5 + m;
+        n5[m] = i < kWin ? s_pc[i] : 0u;
+        sum += n5[m];
+      }
+      uint32_t run = wave_scan_dpp(sum) - sum;
+#pragma unroll
+      for (int m = 0; m < 5; ++m) {
+        if ((int)lane * 5 + m < kWin) s_pc[lane * 5 + m] = run;
+        run += n5[m];
+      }
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * 64;
+        const uint32_t j = base + s_pc[place[k] >> 16] + (place[k] & 0xffffu);
+        if (q < np && j < d.ntot) order[j] = s_can[q];
+      }
+    }
+    base += np;
+    cs = ce;
+    wave_sync();
+  }
+}
+
 template <int F>
-__global__ __launch_bounds__(kThreads) void k_obs_pass1(Dev d) {
+__global__ __launch_bounds__(kThreads) void k_obs_pass1(Dev d, uint32_t pb0, uint32_t cur,
+                                                        const uint32_t* __restrict__ order) {
   __shared__ double s_red[kThreads];
-  const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
+  const uint32_t blk = pb0 + blockIdx.x;
+  const PBlock pb = load_pblock(d.pblocks, blk);
   BoxRef B = as_const(d.boxes)[pb.box];
-  const StatePtrs S = d.S[d.ctrl->cur];
+  const StatePtrs S = d.S[cur];
   const uint32_t pend = B.pbase + B.np;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   for (int s = 0; s < kPartBlock / kThreads; ++s) {
     const uint32_t i = pb.p0 + s * kThreads + threadIdx.x;
     if (i >= pend) continue;
     double v[3];
-    load_vel_d<F>(S, i, v);
+    load_vel_d<F>(S, order ? min(order[i], d.ntot - 1u) : i, v);
     acc[0] += B.mass * v[0];
     acc[1] += B.mass * v[1];
     acc[2] += B.mass * v[2];
@@ -2405,16 +2930,18 @@ __global__ __launch_bounds__(kThreads) void k_obs_pass1(Dev d) {
   }
   for (int k = 0; k < 4; ++k) {
     const double r = block_sum_d(acc[k], s_red);
-    if (threadIdx.x == 0) d.partials[(uint64_t)blockIdx.x * 4 + k] = r;
+    if (threadIdx.x == 0) d.partials[(uint64_t)blk * 4 + k] = r;
   }
 }
 
 template <int F>
-__global__ __launch_bounds__(kThreads) void k_obs_pass2(Dev d, const double* vmean) {
+__global__ __launch_bounds__(kThreads) void k_obs_pass2(Dev d, uint32_t pb0, uint32_t cur,
+                                                        const double* vmean) {
   __shared__ double s_red[kThreads];
-  const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
+  const uint32_t blk = pb0 + blockIdx.x;
+  const PBlock pb = load_pblock(d.pblocks, blk);
   BoxRef B = as_const(d.boxes)[pb.box];
-  const StatePtrs S = d.S[d.ctrl->cur];
+  const StatePtrs S = d.S[cur];
   const uint32_t pend = B.pbase + B.np;
   const double V[3] = {vmean[3 * pb.box], vmean[3 * pb.box + 1], vmean[3 * pb.box + 2]};
   double acc = 0.0;
@@ -2427,7 +2954,7 @@ __global__ __launch_bounds__(kThreads) void k_obs_pass2(Dev d, const double* vme
     acc += B.mass * (dx * dx + dy * dy + dz * dz);
   }
   const double r = block_sum_d(acc, s_red);
-  if (threadIdx.x == 0) d.partials[(uint64_t)blockIdx.x * 4] = r;
+  if (threadIdx.x == 0) d.partials[(uint64_t)blk * 4] = r;
 }
 
 template <int F>
@@ -2468,12 +2995,15 @@ __global__ __launch_bounds__(kThreads) void k_remove_mean(Dev d, const double* v
     }                                                                        \
   } while (0)
 
-hipError_t launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s) {
+hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s) {
   uint64_t blocks = (n + kThreads - 1) / kThreads;
   if (blocks > 65536) blocks = 65536;
   if (blocks == 0) blocks = 1;
-  hipLaunchKernelGGL(k_zero_u32, dim3((uint32_t)blocks), dim3(kThreads), 0, s, p, n);
+  hipLaunchKernelGGL(k_fill_u32, dim3((uint32_t)blocks), dim3(kThreads), 0, s, p, n, value);
   return hipGetLastError();
+}
+hipError_t launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s) {
+  return launch_fill_u32(p, n, 0u, s);
 }
 
 hipError_t launch_set_ctrl(const Dev& d, const Launch& l, uint64_t step, uint32_t cur,
@@ -2483,52 +3013,92 @@ hipError_t launch_set_ctrl(const Dev& d, const Launch& l, uint64_t step, uint32_
   return hipGetLastError();
 }
 
-hipError_t launch_advance(const Dev& d, const Launch& l) {
-  hipLaunchKernelGGL(k_advance, dim3(1), dim3(1), 0, l.stream, d.ctrl);
-  return hipGetLastError();
-}
-
-hipError_t launch_key_hist(const Dev& d, const Launch& l) {
+// Binning export: cell keys, ranks, offsets and slots of step t for buffer S.
+hipError_t launch_binning(const Dev& d, const Launch& l, const StatePtrs& S, uint64_t t) {
+  hipError_t e = launch_zero_u32(d.hist, (uint64_t)l.nscan * kScanBlock, l.stream);
+  if (e != hipSuccess) return e;
   if (l.npblocks == 0) return hipSuccess;
   const dim3 g(l.npblocks), b(kThreads);
   switch (l.form * 2 + (l.walls ? 1 : 0)) {
-    case 0: hipLaunchKernelGGL((k_key_hist<kFormF64, false>), g, b, 0, l.stream, d); break;
-    case 1: hipLaunchKernelGGL((k_key_hist<kFormF64, true>), g, b, 0, l.stream, d); break;
-    case 2: hipLaunchKernelGGL((k_key_hist<kFormF32, false>), g, b, 0, l.stream, d); break;
-    case 3: hipLaunchKernelGGL((k_key_hist<kFormF32, true>), g, b, 0, l.stream, d); break;
-    case 4: hipLaunchKernelGGL((k_key_hist<kFormSplit, false>), g, b, 0, l.stream, d); break;
-    default: hipLaunchKernelGGL((k_key_hist<kFormSplit, true>), g, b, 0, l.stream, d); break;
+    case 0: hipLaunchKernelGGL((k_key_hist<kFormF64, false>), g, b, 0, l.stream, d, S, t); break;
+    case 1: hipLaunchKernelGGL((k_key_hist<kFormF64, true>), g, b, 0, l.stream, d, S, t); break;
+    case 2: hipLaunchKernelGGL((k_key_hist<kFormF32, false>), g, b, 0, l.stream, d, S, t); break;
+    case 3: hipLaunchKernelGGL((k_key_hist<kFormF32, true>), g, b, 0, l.stream, d, S, t); break;
+    case 4: hipLaunchKernelGGL((k_key_hist<kFormSplit, false>), g, b, 0, l.stream, d, S, t); break;
+    default: hipLaunchKernelGGL((k_key_hist<kFormSplit, true>), g, b, 0, l.stream, d, S, t); break;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_scan(const Dev& d, const Launch& l) {
   hipLaunchKernelGGL(k_scan_reduce, dim3(l.nscan), dim3(kThreads), 0, l.stream, d.hist,
                      d.scan_blk);
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, l.stream, d.scan_blk, l.nscan);
-  const dim3 g(l.nscan), b(kThreads);
-  const uint32_t nb = l.nscan, nx = l.nbox, ct = (uint32_t)l.ctot;
-  switch ((l.walls ? 2 : 0) + (l.mbs ? 1 : 0)) {
-    case 0: hipLaunchKernelGGL((k_scan_down<false, false>), g, b, 0, l.stream, d, nb, nx, ct); break;
-    case 1: hipLaunchKernelGGL((k_scan_down<false, true>), g, b, 0, l.stream, d, nb, nx, ct); break;
-    case 2: hipLaunchKernelGGL((k_scan_down<true, false>), g, b, 0, l.stream, d, nb, nx, ct); break;
-    default: hipLaunchKernelGGL((k_scan_down<true, true>), g, b, 0, l.stream, d, nb, nx, ct); break;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_phantoms(const Dev& d, const Launch& l) {
-  if (!l.walls || l.wcells == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_phantom_sums, dim3((l.wcells + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                     l.stream, d, l.nbox, l.wcells, l.round_phantoms);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter(const Dev& d, const Launch& l) {
-  if (l.ntot == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_scan_down, dim3(l.nscan), dim3(kThreads), 0, l.stream, d, l.nscan);
   const uint32_t blocks = (uint32_t)((l.ntot + kThreads * 4 - 1) / (kThreads * 4));
   hipLaunchKernelGGL(k_scatter, dim3(blocks), dim3(kThreads), 0, l.stream, d.key, d.rank,
                      d.offset, d.perm, (uint32_t)l.ntot, (uint32_t)l.ctot, d.ctrl);
+  return hipGetLastError();
+}
+
+// Sort of the state in buffer `from` into buffer `to` by tile of the next
+// step, and the run lists of `to`.
+template <int F>
+static void launch_sort_form(const Dev& d, const Launch& l, uint32_t from, uint32_t to,
+                             bool scatter) {
+  const dim3 g(l.npblocks), b(kThreads);
+  if (scatter) {
+    if (l.walls) {
+      hipLaunchKernelGGL((k_tile_scatter<F, true>), g, b, 0, l.stream, d, from, to);
+    } else {
+      hipLaunchKernelGGL((k_tile_scatter<F, false>), g, b, 0, l.stream, d, from, to);
+    }
+  } else {
+    if (l.walls) {
+      hipLaunchKernelGGL((k_tile_count<F, true>), g, b, 0, l.stream, d, from, to);
+    } else {
+      hipLaunchKernelGGL((k_tile_count<F, false>), g, b, 0, l.stream, d, from, to);
+    }
+  }
+}
+hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to) {
+  if (l.npblocks == 0) return hipSuccess;
+  hipError_t e;
+  for (int k = 0; k < 2; ++k) {
+    if ((e = launch_zero_u32((uint32_t*)d.tcnt[k], 2ull * d.ntile, l.stream)) != hipSuccess)
+      return e;
+    if ((e = launch_fill_u32(d.rhead[k], (uint64_t)d.ntile * d.maxr, kNoSlot, l.stream)) !=
+        hipSuccess)
+      return e;
+  }
+  const uint32_t nts = (d.ntile + kTileBlock - 1) / kTileBlock;
+  for (int pass = 0; pass < 2; ++pass) {
+    switch (l.form) {
+      case kFormF64: launch_sort_form<kFormF64>(d, l, from, to, pass == 1); break;
+      case kFormF32: launch_sort_form<kFormF32>(d, l, from, to, pass == 1); break;
+      default: launch_sort_form<kFormSplit>(d, l, from, to, pass == 1); break;
+    }
+    if (pass == 0) {
+      if (d.ntile > kTileDirect)
+        hipLaunchKernelGGL(k_tile_reduce, dim3(nts), dim3(kThreads), 0, l.stream, d, (int)to);
+      hipLaunchKernelGGL(k_tile_scan, dim3(nts), dim3(kThreads), 0, l.stream, d, to);
+    }
+  }
+  hipLaunchKernelGGL(k_tile_runs, dim3((d.ntile + kThreads - 1) / kThreads), dim3(kThreads), 0,
+                     l.stream, d, to);
+  return hipGetLastError();
+}
+
+hipError_t launch_prepare(const Dev& d, const Launch& l) {
+  const uint32_t nts = (d.ntile + kTileBlock - 1) / kTileBlock;
+  if (d.ntile > kTileDirect)
+    hipLaunchKernelGGL(k_tile_reduce, dim3(nts), dim3(kThreads), 0, l.stream, d, -1);
+  const uint32_t wc = l.walls ? l.wcells : 0u;
+  const uint32_t grid = (wc + kThreads - 1) / kThreads + nts + (l.nbox + kThreads - 1) / kThreads +
+                        (uint32_t)((l.ctot + d.drawb - 1) / d.drawb);
+  if (l.mbs) {
+    hipLaunchKernelGGL((k_prepare<true>), dim3(grid), dim3(kThreads), 0, l.stream, d, l.nbox,
+                       (uint32_t)l.ctot, wc, l.round_phantoms);
+  } else {
+    hipLaunchKernelGGL((k_prepare<false>), dim3(grid), dim3(kThreads), 0, l.stream, d, l.nbox,
+                       (uint32_t)l.ctot, wc, l.round_phantoms);
+  }
   return hipGetLastError();
 }
 
@@ -2584,15 +3154,29 @@ hipError_t launch_init_state(const Dev& d, const Launch& l, uint64_t seed) {
   return hipGetLastError();
 }
 
-hipError_t launch_obs_pass1(const Dev& d, const Launch& l) {
-  if (l.npblocks == 0) return hipSuccess;
-  MPC_FORM_DISPATCH(l.form, k_obs_pass1, dim3(l.npblocks), dim3(kThreads), 0, l.stream, d);
+hipError_t launch_obs_order(const Dev& d, const Launch& l, uint32_t box, uint32_t nrows,
+                            uint32_t l0, uint32_t cur, uint32_t To, uint32_t* order) {
+  const uint32_t grid = nrows * ((l0 + To - 1) / To);
+  if (l.walls) {
+    hipLaunchKernelGGL(k_obs_order<true>, dim3(grid), dim3(64), 0, l.stream, d, box, cur, To, order);
+  } else {
+    hipLaunchKernelGGL(k_obs_order<false>, dim3(grid), dim3(64), 0, l.stream, d, box, cur, To, order);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_obs_pass2(const Dev& d, const Launch& l, const double* vmean) {
-  if (l.npblocks == 0) return hipSuccess;
-  MPC_FORM_DISPATCH(l.form, k_obs_pass2, dim3(l.npblocks), dim3(kThreads), 0, l.stream, d,
+hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
+                            const uint32_t* order) {
+  if (npb == 0) return hipSuccess;
+  MPC_FORM_DISPATCH(l.form, k_obs_pass1, dim3(npb), dim3(kThreads), 0, l.stream, d, pb0, cur,
+                    order);
+  return hipGetLastError();
+}
+
+hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
+                            const double* vmean) {
+  if (npb == 0) return hipSuccess;
+  MPC_FORM_DISPATCH(l.form, k_obs_pass2, dim3(npb), dim3(kThreads), 0, l.stream, d, pb0, cur,
                     vmean);
   return hipGetLastError();
 }
