@@ -31,13 +31,20 @@ struct BoxPlan {
   int nlz;
 };
 
-// Cells per tile: the mean particle count of a tile is at most 84 % of the
+// Cells per tile.  The mean particle count of a tile is at most 84 % of the
 // capacity of one collide pass, so that about one tile in 400 at 10 particles
-// per cell needs a second pass; the tiles of a row are of about equal length.
-int auto_tile_cells(double density, int l0) {
+// per cell needs a second pass.  With fewer than 2048 such tiles in all boxes
+// (`rows`: their rows of cells), shorter ones down to 80 particles put more
+// wavefronts to work: 24^3 with the thermostat 25.9 us a step with tiles of 8
+// cells, 27.2 with 12, 29.9 with 20 (and 29.7 with 4); 41 x 33 x 27 35.1 with
+// 14, 43.2 with 21; 64^3 (4096 rows) 109 with 16, 127 with 11.  The tiles of a
+// row are of about equal length: 75^3 158 us with 19, 182 with 21.
+int auto_tile_cells(double density, int l0, uint64_t rows) {
   const double target = 0.84 * kTileCap / density;
   const int most = (int)std::max(1.0, std::min<double>(kTileMaxCells, floor(target)));
-  const int per_row = (l0 + most - 1) / most;
+  const int least = (int)std::max(1.0, std::min<double>(most, ceil(80.0 / density)));
+  const int want = (int)std::min<uint64_t>((2048 + rows - 1) / rows, (uint64_t)(l0 / least));
+  const int per_row = std::max((l0 + most - 1) / most, want);
   return (l0 + per_row - 1) / per_row;
 }
 
@@ -46,6 +53,8 @@ struct Plan {
   uint64_t ntot = 0, ctot = 0, cpad = 0;
   uint32_t nscan = 0;
   uint64_t max_tiles = 0, npblocks = 0;
+  uint64_t rows = 0;      // rows of cells in all boxes
+  uint32_t drawb = 0;     // cells per draw block
   uint64_t run_pool = 0;  // runs of all tiles' tables per state buffer
   size_t charge = 0;      // bytes the static scratch is checked against
   size_t rec = 0;  // bytes per particle record
@@ -53,12 +62,12 @@ struct Plan {
   // byte offsets in the workspace: records of the two state buffers and, for
   // FP64 and FP32, their logical-index arrays (the split record holds its id)
   size_t off_rec[2] = {}, off_id[2] = {};
-  size_t off_rank = 0, off_phs = 0, off_least = 0, off_later = 0, off_bstep = 0;
-  size_t off_tcnt[2] = {}, off_runs[2] = {}, off_rhead[2] = {}, off_rnext[2] = {}, off_toff = 0,
+  size_t off_rank = 0, off_phs[2] = {}, off_least[2] = {}, off_later[2] = {}, off_bstep[2] = {};
+  size_t off_tcnt[3] = {}, off_runs[2] = {}, off_rhead[2] = {}, off_rnext[2] = {}, off_toff = 0,
          off_tblk = 0;
   size_t off_key = 0, off_perm = 0, off_hist = 0, off_offset = 0, off_scan = 0, off_ctrl = 0,
          off_boxes = 0, off_tiles = 0, off_pblocks = 0, off_partials = 0, off_vmean = 0,
-         off_draws = 0;
+         off_draws[2] = {};
   size_t total = 0;
 };
 
@@ -148,6 +157,8 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   int rc = validate(p, nbox, why);
   if (rc) return rc;
   P.box.resize(nbox);
+  for (int32_t b = 0; b < nbox; ++b)
+    P.rows += (uint64_t)p[b].L[1] * ((uint64_t)p[b].L[2] + ((p[b].flags & MPC_WALLS_Z) ? 2 : 0));
   for (int32_t b = 0; b < nbox; ++b) {
     const mpc_params& q = p[b];
     const bool walls = q.flags & MPC_WALLS_Z;
@@ -169,7 +180,7 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
     P.ntot += P.box[b].n;
     P.ctot += P.box[b].ncell;
     const uint64_t rows = (uint64_t)q.L[1] * nlz;
-    const int ta = auto_tile_cells(q.density, q.L[0]);
+    const int ta = auto_tile_cells(q.density, q.L[0], P.rows);
     const uint64_t auto_tiles = rows * ((q.L[0] + ta - 1) / ta);
     P.max_tiles += std::max(auto_tiles, rows * ((q.L[0] + kMinTileCells - 1) / kMinTileCells));
     P.run_pool += auto_tiles * kMaxRuns;
@@ -209,8 +220,8 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   // a tiling with more tiles than the automatic one has shorter run tables,
   // of at least one run a tile
   P.run_pool = std::max<uint64_t>(P.run_pool, P.max_tiles);
+  for (int k = 0; k < 3; ++k) P.off_tcnt[k] = take(8 * P.max_tiles);
   for (int k = 0; k < 2; ++k) {
-    P.off_tcnt[k] = take(8 * P.max_tiles);
     P.off_runs[k] = take(sizeof(Run) * P.run_pool);
     P.off_rhead[k] = take(4 * P.run_pool);
     P.off_rnext[k] = take(4 * P.ntot);
@@ -220,17 +231,24 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   P.off_toff = take(4 * P.max_tiles);
   P.off_ctrl = take(sizeof(Ctrl));
   P.off_boxes = take(sizeof(BoxDev) * nbox);
-  P.off_bstep = take(sizeof(BoxStep) * nbox);
   P.off_tiles = take(sizeof(Tile) * P.max_tiles);
   P.off_pblocks = take(sizeof(PBlock) * P.npblocks);
   P.off_partials = take(sizeof(double) * 4 * P.npblocks);
   P.off_vmean = take(sizeof(double) * 3 * nbox);
-  P.off_draws = take(sizeof(double4) * P.cpad);
-  if (p[0].flags & MPC_MBS) {
-    P.off_least = take(4 * P.cpad);
-    P.off_later = take(sizeof(Attempt) * (P.cpad / 4));
+  // draw blocks of one wavefront each: about 1024 of them if the box is small,
+  // so that they run beside each other, else as long as their lists allow
+  P.drawb = (uint32_t)std::min<uint64_t>(
+      kMaxDrawBlock, std::max<uint64_t>(kMinDrawBlock, (P.ctot + 65535) / 65536 * 64));
+  const uint64_t ndraw = (P.ctot + P.drawb - 1) / P.drawb;
+  for (int k = 0; k < 2; ++k) {
+    P.off_bstep[k] = take(sizeof(BoxStep) * nbox);
+    P.off_draws[k] = take(sizeof(double4) * P.cpad);
+    if (p[0].flags & MPC_MBS) {
+      P.off_least[k] = take(4 * P.cpad);
+      P.off_later[k] = take(sizeof(Attempt) * later_seg(P.drawb) * ndraw);
+    }
+    if (p[0].flags & MPC_WALLS_Z) P.off_phs[k] = take(sizeof(PhantomSums) * P.cpad);
   }
-  P.off_phs = (p[0].flags & MPC_WALLS_Z) ? take(sizeof(PhantomSums) * P.cpad) : 0;
   P.charge = scratch_charge(p, P);
   P.total = off;
   return MPC_OK;
@@ -241,9 +259,9 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
 // process end; host code reaches it only through the address that
 // hipGetSymbolAddress returns for the current device.
 constexpr size_t kScratchLimit = (size_t)256 << 20;  // see scratch_charge
-// the workspace of a call within the limit: at most 5/3 of its charge (sparse
-// boxes, where the cells' draws and the tiles' tables dominate)
-constexpr size_t kScratchBytes = (size_t)432 << 20;
+// the workspace of a call within the limit: up to 3.3 times its charge in a
+// sparse box, where the cells' draws and the tiles' tables dominate
+constexpr size_t kScratchBytes = (size_t)896 << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex scratch_mu;
@@ -299,8 +317,7 @@ struct mpc_sim {
   bool use_graph = true;
   int32_t graph_steps = 1;         // steps per replay of the chunk graph
   bool graph_ready = false;
-  hipGraphExec_t gexec = nullptr;  // one step
-  hipGraphExec_t gexec_k = nullptr;  // graph_steps steps (graph_steps > 1)
+  hipGraphExec_t gexec = nullptr;  // graph_chunk() steps
   hipStream_t capture_stream = nullptr;
   int tile_override = 0, grid_override = 0, yblock = 8;
   int order = 0;  // tile order: 0 = row by row inside a block of rows, 1 = x-segment major
@@ -344,7 +361,7 @@ void build_tiles(mpc_sim* s) {
   const int yb = std::max(1, s->yblock);
   for (size_t b = 0; b < s->boxes.size(); ++b) {
     BoxDev& B = s->boxes[b];
-    const int T = s->tile_override ? s->tile_override : auto_tile_cells(B.density, B.L[0]);
+    const int T = s->tile_override ? s->tile_override : auto_tile_cells(B.density, B.L[0], s->plan.rows);
     B.T = (uint32_t)T;
     B.ntx = (uint32_t)((B.L[0] + T - 1) / T);
     B.tbase = (uint32_t)keyed.size();
@@ -429,18 +446,23 @@ int check_sticky(mpc_sim* s) {
   return MPC_OK;
 }
 
-// One step's launches on `st`.
-hipError_t enqueue_step(mpc_sim* s, hipStream_t st) {
+// The launches of n steps on `st`.
+hipError_t enqueue_steps(mpc_sim* s, hipStream_t st, int64_t n) {
   Launch l = s->L;
   l.stream = st;
-  const hipError_t e = launch_prepare(s->dev, l);
-  return e != hipSuccess ? e : launch_collide(s->dev, l);
+  for (l.seq = 0; l.seq < (uint32_t)n; ++l.seq) {
+    hipError_t e = launch_prefix(s->dev, l);
+    if (e == hipSuccess) e = launch_collide(s->dev, l);
+    if (e != hipSuccess) return e;
+  }
+  return launch_advance(s->dev, l, (uint32_t)n);
 }
 
 // A state set from outside (or a binning export, which takes the memory of
 // the run lists): sort by tile of the next step into the other buffer.
 int ensure_keys(mpc_sim* s) {
   if (s->keys_valid) return MPC_OK;
+  HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   HIPCHK(s, launch_sort(s->dev, s->L, s->cur, s->cur ^ 1u));
   s->cur ^= 1u;
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
@@ -459,23 +481,23 @@ int drop_graph(mpc_sim* s) {
     HIPCHK(s, hipGraphExecDestroy(s->gexec));
     s->gexec = nullptr;
   }
-  if (s->gexec_k) {
-    HIPCHK(s, hipGraphExecDestroy(s->gexec_k));
-    s->gexec_k = nullptr;
-  }
   s->graph_ready = false;
   return MPC_OK;
 }
 
+// Steps per graph.  Without a wish of the caller 16: a graph of one step took
+// 21.0 us a step at 16^3, single launches 15.4, graphs of 10 steps 14.8 and of
+// 50 steps 14.2 (before the tiles of small boxes got shorter).
+int64_t graph_chunk(const mpc_sim* s) { return s->graph_steps > 1 ? s->graph_steps : 16; }
+
 // One executable graph of `steps` consecutive steps (every step reads the
 // step counter and the state buffer index from device memory, so one graph
 // serves every replay).
-int capture_steps(mpc_sim* s, int32_t steps, hipGraphExec_t* out) {
+int capture_steps(mpc_sim* s, int64_t steps, hipGraphExec_t* out) {
   if (!s->capture_stream) HIPCHK(s, hipStreamCreateWithFlags(&s->capture_stream, hipStreamNonBlocking));
   hipGraph_t g = nullptr;
   HIPCHK(s, hipStreamBeginCapture(s->capture_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = hipSuccess;
-  for (int32_t k = 0; k < steps && e == hipSuccess; ++k) e = enqueue_step(s, s->capture_stream);
+  hipError_t e = enqueue_steps(s, s->capture_stream, steps);
   hipError_t e2 = hipStreamEndCapture(s->capture_stream, &g);
   if (e != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
@@ -490,8 +512,7 @@ int capture_steps(mpc_sim* s, int32_t steps, hipGraphExec_t* out) {
 
 int capture_graph(mpc_sim* s) {
   if (s->graph_ready) return MPC_OK;
-  int rc = capture_steps(s, 1, &s->gexec);
-  if (!rc && s->graph_steps > 1) rc = capture_steps(s, s->graph_steps, &s->gexec_k);
+  const int rc = capture_steps(s, graph_chunk(s), &s->gexec);
   if (rc) return rc;
   s->graph_ready = true;
   return MPC_OK;
@@ -640,15 +661,14 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->dev.hist = (uint32_t*)(ws + P.off_hist);
   s->dev.offset = (uint32_t*)(ws + P.off_offset);
   s->dev.scan_blk = (uint32_t*)(ws + P.off_scan);
+  for (int k = 0; k < 3; ++k) s->dev.tcnt[k] = (unsigned long long*)(ws + P.off_tcnt[k]);
   for (int k = 0; k < 2; ++k) {
-    s->dev.tcnt[k] = (unsigned long long*)(ws + P.off_tcnt[k]);
     s->dev.runs[k] = (Run*)(ws + P.off_runs[k]);
     s->dev.rhead[k] = (uint32_t*)(ws + P.off_rhead[k]);
     s->dev.rnext[k] = (uint32_t*)(ws + P.off_rnext[k]);
   }
   s->dev.toff = (uint32_t*)(ws + P.off_toff);
   s->dev.tblk = (uint32_t*)(ws + P.off_tblk);
-  s->dev.bstep = (BoxStep*)(ws + P.off_bstep);
   s->dev.ctrl = (Ctrl*)(ws + P.off_ctrl);
   s->dev.boxes = (BoxDev*)(ws + P.off_boxes);
   s->dev.tiles = (Tile*)(ws + P.off_tiles);
@@ -656,16 +676,14 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->dev.partials = (double*)(ws + P.off_partials);
   s->dev.ntot = (uint32_t)P.ntot;
   s->vmean = (double*)(ws + P.off_vmean);
-  s->dev.draws = (double4*)(ws + P.off_draws);
-  if (p[0].flags & MPC_MBS) {
-    s->dev.least = (uint32_t*)(ws + P.off_least);
-    s->dev.later = (Attempt*)(ws + P.off_later);
+  s->dev.drawb = P.drawb;
+  for (int k = 0; k < 2; ++k) {
+    s->dev.bstep[k] = (BoxStep*)(ws + P.off_bstep[k]);
+    s->dev.draws[k] = (double4*)(ws + P.off_draws[k]);
+    s->dev.least[k] = (p[0].flags & MPC_MBS) ? (uint32_t*)(ws + P.off_least[k]) : nullptr;
+    s->dev.later[k] = (p[0].flags & MPC_MBS) ? (Attempt*)(ws + P.off_later[k]) : nullptr;
+    s->dev.phs[k] = (p[0].flags & MPC_WALLS_Z) ? (PhantomSums*)(ws + P.off_phs[k]) : nullptr;
   }
-  // blocks of the draws: large ones let one wavefront make the chains of many
-  // cells, small ones keep a small box on many compute units
-  s->dev.drawb = kMinDrawBlock;
-  while (s->dev.drawb < kMaxDrawBlock && P.ctot / (2 * s->dev.drawb) >= 1024) s->dev.drawb *= 2;
-  s->dev.phs = (p[0].flags & MPC_WALLS_Z) ? (PhantomSums*)(ws + P.off_phs) : nullptr;
 
   // boxes
   uint64_t pb = 0, cb = 0, wcb = 0;
@@ -809,15 +827,16 @@ int mpc_step(mpc_sim* s, int64_t nsteps) {
   if (nsteps == 0) return MPC_OK;
   int rc = ensure_keys(s);
   if (rc) return rc;
-  if (s->use_graph) {
+  int64_t k = 0;
+  const int64_t chunk = graph_chunk(s);
+  if (s->use_graph && nsteps >= chunk) {
     if ((rc = capture_graph(s))) return rc;
-    int64_t k = 0;
-    if (s->gexec_k)
-      for (; k + s->graph_steps <= nsteps; k += s->graph_steps)
-        HIPCHK(s, hipGraphLaunch(s->gexec_k, s->L.stream));
-    for (; k < nsteps; ++k) HIPCHK(s, hipGraphLaunch(s->gexec, s->L.stream));
-  } else {
-    for (int64_t k = 0; k < nsteps; ++k) HIPCHK(s, enqueue_step(s, s->L.stream));
+    for (; k + chunk <= nsteps; k += chunk) HIPCHK(s, hipGraphLaunch(s->gexec, s->L.stream));
+  }
+  while (k < nsteps) {
+    const int64_t n = std::min<int64_t>(nsteps - k, kMaxGraphSteps);
+    HIPCHK(s, enqueue_steps(s, s->L.stream, n));
+    k += n;
   }
   advance_mirror(s, nsteps);
   s->have_binning = true;
@@ -846,10 +865,14 @@ int mpc_step_profiled(mpc_sim* s, int64_t nsteps, mpc_kernel_times* acc) {
     HIPCHK(s, mark());
     kinds_prologue = 1;
   }
+  Launch l = s->L;
   for (int64_t k = 0; k < nsteps; ++k) {
-    HIPCHK(s, launch_prepare(s->dev, s->L));
+    l.seq = (uint32_t)(k % kMaxGraphSteps);
+    HIPCHK(s, launch_prefix(s->dev, l));
     HIPCHK(s, mark());
-    HIPCHK(s, launch_collide(s->dev, s->L));
+    HIPCHK(s, launch_collide(s->dev, l));
+    if (k + 1 == nsteps || l.seq + 1 == (uint32_t)kMaxGraphSteps)
+      HIPCHK(s, launch_advance(s->dev, l, l.seq + 1));
     HIPCHK(s, mark());
   }
   HIPCHK(s, hipStreamSynchronize(st));
@@ -1291,11 +1314,11 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
     if (r) return r;
     if ((r = restore())) return r;
     if ((r = ensure_keys(s))) return r;
-    HIPCHK(s, enqueue_step(s, st));
+    HIPCHK(s, enqueue_steps(s, st, 1));
     advance_mirror(s, 1);
     HIPCHK(s, hipEventRecord(ev[0], st));
     for (int32_t k = 0; k < trial_steps; ++k) {
-      HIPCHK(s, enqueue_step(s, st));
+      HIPCHK(s, enqueue_steps(s, st, 1));
       HIPCHK(s, hipEventRecord(ev[(size_t)k + 1], st));
     }
     HIPCHK(s, hipEventSynchronize(ev[(size_t)trial_steps]));

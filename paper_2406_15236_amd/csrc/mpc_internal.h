@@ -17,8 +17,10 @@ constexpr int kPartBlock = kThreads * 4;    // particles per block of per-partic
 constexpr int kMaxRuns = 32;                // runs in a tile's table (more go to chains)
 constexpr int kGroups = 27;                 // next-step tiles of a pass: 3 per row, 9 rows
 constexpr int kTileBlock = kThreads * 4;    // tiles per block of the tile prefix
-constexpr uint32_t kTileDirect = 16384;     // most tiles with a prefix in one launch
-constexpr uint32_t kMinDrawBlock = 256, kMaxDrawBlock = 2048;  // cells per block of the draws
+constexpr uint32_t kTileOne = 16384;        // most tiles with a prefix in one launch
+constexpr uint32_t kTileDirect = 2048;      // most tiles with a prefix inside the collide
+constexpr uint32_t kMinDrawBlock = 64, kMaxDrawBlock = 1024;  // cells per block of the draws
+constexpr int kDrawList = 256;              // cells listed for repeated draws at a time
 constexpr uint32_t kNeverAccepted = 1024;   // more particles than a cell can hold
 constexpr uint32_t kNoSlot = 0xffffffffu;
 
@@ -87,9 +89,9 @@ struct PBlock {        // one block of a per-particle kernel
 struct Ctrl {          // device-resident step state, read by every kernel
   uint64_t step;       // step index t of the next step
   uint32_t cur;        // which state buffer holds the current state (flips every step)
+  uint32_t tri;        // which set of tile counters belongs to it (of three, in turn)
   uint32_t err;        // sticky error bits
   int32_t reorder;     // R
-  uint32_t done;       // workgroups of the running collide that have finished
   uint32_t pad[2];
 };
 
@@ -103,6 +105,9 @@ struct Attempt {        // of a cell's gamma draw
   uint16_t next;       // the cell's next attempt in the segment; 0: none
   uint32_t pad;
 };
+
+// Attempts that a draw block of b cells can list: 0.028 b on average.
+__host__ __device__ constexpr uint32_t later_seg(uint32_t b) { return b / 4 + 48; }
 
 struct PhantomSums {   // phantom particles of an occupied wall-cut cell
   double v[3];         // sum of their velocities
@@ -158,27 +163,36 @@ struct Dev {           // device pointers carved from the workspace
   uint32_t* offset;    // exclusive prefix, ncell + 1
   uint32_t* scan_blk;  // per scan-block totals
   // run lists of the tiles, one set per state buffer
-  unsigned long long* tcnt[2];  // particles << 32 | runs
+  unsigned long long* tcnt[3];  // particles << 32 | runs; sets in turn (Ctrl::tri)
   Run* runs[2];        // maxr per tile
   uint32_t* rhead[2];  // maxr chain heads per tile (tiles with more runs)
   uint32_t* rnext[2];  // next slot of a chain, per slot
   uint32_t* toff;      // first output slot of each tile
   uint32_t* tblk;      // particles per block of tiles
   uint32_t maxr, ntile;
-  BoxStep* bstep;
+  // what a step reads besides the particles, one set per state buffer
+  BoxStep* bstep[2];
   Ctrl* ctrl;
   BoxDev* boxes;
   Tile* tiles;
   PBlock* pblocks;
   double* partials;    // per-block observable partial sums
-  double4* draws;      // per cell: rotation axis, z of attempt 0 of the gamma draw
+  double4* draws[2];      // per cell: rotation axis, z of attempt 0 of the gamma draw
   // thermostat: per cell, the least count that accepts attempt 0 and the first
-  // of its later attempts << 16 in the block's segment of drawb / 4 attempts
-  uint32_t* least;
-  Attempt* later;
+  // of its later attempts << 16 in the block's segment of later_seg(drawb) attempts
+  uint32_t* least[2];
+  Attempt* later[2];
   uint32_t drawb;      // cells per block of the draws
-  PhantomSums* phs;    // walls only: phantom sums of wall-cut cells
+  PhantomSums* phs[2];  // walls only: phantom sums of wall-cut cells
   uint32_t ntot;       // particles over all boxes (bound of every particle index)
+};
+
+struct Side {          // side work of a collide (see k_collide)
+  uint32_t nbox, ctot, wcells;
+  int round32;
+  uint32_t blocks;     // workgroups that do nothing else
+  uint32_t inloop;     // the draws are made between the tiles
+  uint32_t direct;     // every wavefront sums the tiles before its own
 };
 
 struct Launch {
@@ -193,6 +207,7 @@ struct Launch {
   uint32_t collide_grid;
   uint32_t wcells;         // walls: cells of the wall-cut layers over all boxes
   int xcd_remap;
+  uint32_t seq;            // number of the step in its launch sequence (see Ctrl)
   hipStream_t stream;
 };
 
@@ -201,7 +216,8 @@ hipError_t launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s);
 hipError_t launch_binning(const Dev& d, const Launch& l, const StatePtrs& S, uint64_t t);
 hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to);
-hipError_t launch_prepare(const Dev& d, const Launch& l);
+hipError_t launch_prefix(const Dev& d, const Launch& l);
+hipError_t launch_advance(const Dev& d, const Launch& l, uint32_t n);
 hipError_t launch_collide(const Dev& d, const Launch& l);
 hipError_t launch_set_ctrl(const Dev& d, const Launch& l, uint64_t step, uint32_t cur,
                            int32_t reorder, int clear_err);
