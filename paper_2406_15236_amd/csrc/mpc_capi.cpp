@@ -1125,31 +1125,34 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
   int rc = mpc_sync(s);
   if (rc || m == 0) return rc;
   const StatePtrs& S = s->dev.S[s->cur];
-  uint32_t* dinv = nullptr;
-  uint32_t* dl = nullptr;
-  double* dout = nullptr;
+  // one allocation: the sample's states, indices, and the table that finds
+  // their slots (see k_sample_find)
+  uint32_t mask = 0;
+  if ((uint64_t)m * 16 <= B.np) {
+    mask = 1024;
+    while (mask < 8 * (uint64_t)m) mask *= 2;
+    mask -= 1;
+  }
+  const size_t o_sel = align256(sizeof(double) * 6 * (size_t)m);
+  const size_t o_tab = o_sel + align256(sizeof(uint32_t) * (size_t)m);
+  const size_t n_tab = mask ? 2 * ((size_t)mask + 1) : (size_t)B.np;
+  char* dbuf = nullptr;
   std::vector<double> out(6 * (size_t)m);
   hipError_t e = hipSuccess;
   const char* where = "";
   do {
-    if (S.id) {
-      where = "hipMalloc (inverse index)";
-      if ((e = hipMalloc(&dinv, sizeof(uint32_t) * (size_t)B.np)) != hipSuccess) break;
-      where = "hipMemsetAsync";
-      if ((e = hipMemsetAsync(dinv, 0xff, sizeof(uint32_t) * (size_t)B.np, s->L.stream)) !=
-          hipSuccess)
-        break;
-    }
     where = "hipMalloc (sample)";
-    if ((e = hipMalloc(&dl, sizeof(uint32_t) * (size_t)m)) != hipSuccess) break;
-    if ((e = hipMalloc(&dout, sizeof(double) * 6 * (size_t)m)) != hipSuccess) break;
+    if ((e = hipMalloc(&dbuf, o_tab + sizeof(uint32_t) * n_tab)) != hipSuccess) break;
+    double* dout = (double*)dbuf;
+    uint32_t* dl = (uint32_t*)(dbuf + o_sel);
+    uint32_t* tab = (uint32_t*)(dbuf + o_tab);
     where = "copy of the sample indices";
     if ((e = hipMemcpyAsync(dl, lidx.data(), sizeof(uint32_t) * (size_t)m,
                             hipMemcpyHostToDevice, s->L.stream)) != hipSuccess)
       break;
     where = "gather kernels";
-    if ((e = launch_gather_particles(s->dev, s->L, S, dinv, B.pbase, B.np, dl, (uint32_t)m,
-                                     dout)) != hipSuccess)
+    if ((e = launch_gather_particles(s->dev, s->L, S, mask ? nullptr : tab, mask ? tab : nullptr,
+                                     mask, B.pbase, B.np, dl, (uint32_t)m, dout)) != hipSuccess)
       break;
     where = "copy of the sample";
     if ((e = hipMemcpyAsync(out.data(), dout, sizeof(double) * 6 * (size_t)m,
@@ -1158,9 +1161,7 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
     where = "hipStreamSynchronize";
     e = hipStreamSynchronize(s->L.stream);
   } while (false);
-  if (dinv) (void)hipFree(dinv);
-  if (dl) (void)hipFree(dl);
-  if (dout) (void)hipFree(dout);
+  if (dbuf) (void)hipFree(dbuf);
   if (e != hipSuccess) return hip_fail(s, e, where);
   const double a = s->params[box].a;
   for (int64_t k = 0; k < m; ++k) {

@@ -11,6 +11,7 @@ constexpr int kCollideThreads = 64;         // collide workgroup: one wave64
 constexpr int kTileCap = 256;               // particles held in LDS per tile pass
 constexpr int kTileMaxCells = 32;           // cells per collide tile (< kCollideThreads)
 constexpr int kObsPass = 256;               // particles per pass of the observables' order
+constexpr int kObsList = 320;               // particles of an obs tile listed in LDS
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
 constexpr int kPartBlock = kThreads * 4;    // particles per block of per-particle kernels
@@ -231,11 +232,11 @@ hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_
 hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
                             const double* vmean_dev);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
-// inv: np entries filled with 0xffffffff by the caller (null: slots are the
-// logical order); lidx: box-local logical indices; out: [6][m] FP64
+// sel: box-local logical indices, overwritten; keys: 2 (mask + 1) entries of a
+// hash table, or null and inv: np entries; out: [6][m] FP64
 hipError_t launch_gather_particles(const Dev& d, const Launch& l, const StatePtrs& S,
-                                  uint32_t* inv, uint32_t pbase, uint32_t np,
-                                  const uint32_t* lidx, uint32_t m, double* out);
+                                  uint32_t* inv, uint32_t* keys, uint32_t mask, uint32_t pbase,
+                                  uint32_t np, uint32_t* sel, uint32_t m, double* out);
 // box 0, FP64 form: caller's device arrays (physical units) <-> state buffer cur
 hipError_t launch_load_f64(const Dev& d, const Launch& l, const double* x, const double* v,
                            uint32_t n, double a, uint32_t cur);

@@ -23,6 +23,8 @@
 // steps can be replayed.
 #include <math.h>
 
+#include <algorithm>
+
 #include "mpc_internal.h"
 #include "philox_dev.h"
 
@@ -2634,11 +2636,74 @@ __global__ void k_canon_perm(uint32_t* __restrict__ perm, const uint32_t* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Sampled state: the inverse of one box's logical-index array, then a gather
-// of selected logical particles as FP64 in cell units (the split form's
-// cell + offset is exact in FP64).  A logical index with no stored slot
-// yields NaN.
+// Sampled state: the stored slots of selected logical particles, then a gather
+// of their records as FP64 in cell units (the split form's cell + offset is
+// exact in FP64).  A logical index with no stored slot yields NaN.  A sample
+// of at most a sixteenth of the box goes into a hash table of eight entries
+// per particle, and every slot looks its index up there; a larger one uses the
+// inverse of the whole index array, four bytes written at random per particle
+// of the box (24 ms at 384^3, where the table of 32768 takes 1 ms).
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ uint32_t sample_hash(uint32_t key, uint32_t mask) {
+  return ((key * 0x9E3779B1u) >> 7) & mask;
+}
+// keys: mask + 1 entries, kNoSlot = free
+__global__ __launch_bounds__(kThreads) void k_sample_insert(const uint32_t* __restrict__ lidx,
+                                                            uint32_t m, uint32_t* keys,
+                                                            uint32_t mask) {
+  const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
+  if (k >= m) return;
+  const uint32_t key = lidx[k];
+  uint32_t h = sample_hash(key, mask);
+  for (;;) {  // at most m of 8 m entries are taken
+    const uint32_t old = atomicCAS(&keys[h], kNoSlot, key);
+    if (old == kNoSlot || old == key) return;
+    h = (h + 1u) & mask;
+  }
+}
+__global__ __launch_bounds__(kThreads) void k_sample_find(const uint32_t* __restrict__ id,
+                                                          uint32_t id_stride, uint32_t pbase,
+                                                          uint32_t np,
+                                                          const uint32_t* __restrict__ keys,
+                                                          uint32_t* __restrict__ slots,
+                                                          uint32_t mask) {
+  const uint32_t stride = gridDim.x * kThreads * 4u;
+  for (uint64_t q0 = (uint64_t)blockIdx.x * kThreads * 4u; q0 < np; q0 += stride) {
+    uint32_t l[4], h[4], kk[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t q = q0 + k * kThreads + threadIdx.x;
+      l[k] = q < np ? id[(size_t)(pbase + (uint32_t)q) * id_stride] - pbase : kNoSlot;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      h[k] = sample_hash(l[k], mask);
+      kk[k] = keys[h[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      while (kk[k] != kNoSlot && kk[k] != l[k]) {
+        h[k] = (h[k] + 1u) & mask;
+        kk[k] = keys[h[k]];
+      }
+      if (kk[k] != kNoSlot && l[k] < np)
+        slots[h[k]] = pbase + (uint32_t)(q0 + k * kThreads + threadIdx.x);
+    }
+  }
+}
+// slot of each sampled particle (kNoSlot: none)
+__global__ __launch_bounds__(kThreads) void k_sample_slots(uint32_t* __restrict__ lidx, uint32_t m,
+                                                           const uint32_t* __restrict__ keys,
+                                                           const uint32_t* __restrict__ slots,
+                                                           uint32_t mask) {
+  const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
+  if (k >= m) return;
+  const uint32_t key = lidx[k];
+  uint32_t h = sample_hash(key, mask);
+  while (keys[h] != key) h = (h + 1u) & mask;  // every key was inserted
+  lidx[k] = slots[h];
+}
+
 __global__ void k_invert_ids(const uint32_t* __restrict__ id, uint32_t id_stride, uint32_t pbase,
                              uint32_t np, uint32_t* __restrict__ inv) {
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -2649,19 +2714,19 @@ __global__ void k_invert_ids(const uint32_t* __restrict__ id, uint32_t id_stride
   }
 }
 
+// slot of particle k: sel[k], or with inv the slot inv[sel[k]]
 template <int F>
 __global__ __launch_bounds__(kThreads) void k_gather_particles(StatePtrs S,
                                                                 const uint32_t* __restrict__ inv,
                                                                 uint32_t pbase, uint32_t np,
-                                                                const uint32_t* __restrict__ lidx,
+                                                                const uint32_t* __restrict__ sel,
                                                                 uint32_t m, double* __restrict__ out) {
   const uint32_t k = blockIdx.x * kThreads + threadIdx.x;
   if (k >= m) return;
-  const uint32_t l = lidx[k];
-  uint32_t j = 0xffffffffu;
-  if (l < np) j = inv ? inv[l] : pbase + l;
+  uint32_t j = sel[k];
+  if (inv) j = j < np ? inv[j] : kNoSlot;
   double r[6];
-  if (j == 0xffffffffu || j - pbase >= np) {
+  if (j == kNoSlot || j - pbase >= np) {
 #pragma unroll
     for (int c = 0; c < 6; ++c) r[c] = __builtin_nan("");
   } else if constexpr (F == kFormF64) {
@@ -2848,8 +2913,9 @@ __device__ __forceinline__ double block_sum_d(double x, double* s_red) {
 // depend on the order in which runs were appended; a total momentum is a sum
 // of rounding errors, and in slot order its digits would change from run to
 // run.  One wavefront per obs tile; the particles of its cells lie in the
-// output of one to three collide tiles, which it reads twice (3 ms at 256^3
-// with the sums, against 100 ms for 20 steps).
+// output of one to three collide tiles.  Their cells and ids are read once, four slots
+// per lane in flight; a crowded neighbourhood (more than kObsList particles)
+// is read again for each pass.
 template <bool W>
 __global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t cur, uint32_t To,
                                                   uint32_t* __restrict__ order) {
@@ -2860,6 +2926,8 @@ __global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t 
   __shared__ uint32_t s_cnt[kTileMaxCells], s_off[kTileMaxCells + 1], s_before;
   __shared__ uint32_t s_id[kObsPass], s_slot[kObsPass], s_can[kObsPass], s_pc[kWin];
   __shared__ uint8_t s_lc[kObsPass];
+  __shared__ uint32_t s_lid[kObsList], s_lslot[kObsList], s_n;
+  __shared__ uint8_t s_llc[kObsList];
   const uint32_t lane = threadIdx.x;
   BoxRef B = as_const(d.boxes)[box];
   const MPC_AS4 BoxStep& bs = as_const(d.bstep[cur ^ 1u])[box];  // of the last step
@@ -2878,24 +2946,42 @@ __global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t 
   const double sn[3] = {bs.sn[0], bs.sn[1], bs.sn[2]};
   const bool le = !W && B.le;
   uint32_t err = 0;
-  // stored positions are those of the last step's collision
-  auto local = [&](uint32_t i) -> int {
-    typename Fm::P p;
-    typename Fm::Vv v;
-    Fm::load(S, i, p, v);
-    return Fm::cell_x(p, st, B, bs.d1, le) - x0;
+  // cells (stored positions are those of the last step's collision) and ids of
+  // slots i0 .. i1: f(cell, id, slot)
+  auto sweep = [&](auto f) {
+    for (uint32_t q0 = i0; q0 < i1; q0 += 256) {
+      typename Fm::P p[4];
+      uint32_t id[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t i = q0 + k * 64 + lane;
+        typename Fm::Vv v;
+        id[k] = 0u;
+        if (i < i1) Fm::load_all(S, i, p[k], v, id[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t i = q0 + k * 64 + lane;
+        if (i < i1) f(Fm::cell_x(p[k], st, B, bs.d1, le) - x0, id[k], i);
+      }
+    }
   };
   if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
-  if (lane == 0) s_before = 0u;
+  if (lane == 0) s_before = s_n = 0u;
   wave_sync();
-  for (uint32_t i = i0 + lane; i < i1; i += 64) {
-    const int c = local(i);
+  sweep([&](int c, uint32_t id, uint32_t i) {
     if (c < 0) {
       atomicAdd(&s_before, 1u);
     } else if (c < nc) {
       atomicAdd(&s_cnt[c], 1u);
+      const uint32_t q = atomicAdd(&s_n, 1u);
+      if (q < (uint32_t)kObsList) {
+        s_lid[q] = id;
+        s_lslot[q] = i;
+        s_llc[q] = (uint8_t)c;
+      }
     }
-  }
+  });
   wave_sync();
   {
     const uint32_t n = lane < (uint32_t)kTileMaxCells ? s_cnt[lane] : 0u;
@@ -2912,17 +2998,21 @@ __global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t 
     if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
     for (uint32_t q = lane; q < (uint32_t)kWin; q += 64) s_pc[q] = 0u;
     wave_sync();
-    for (uint32_t i = i0 + lane; i < i1; i += 64) {
-      const int c = local(i);
-      if (c < cs || c >= ce) continue;
+    auto place_in_pass = [&](int c, uint32_t id, uint32_t i) {
+      if (c < cs || c >= ce) return;
       const uint32_t q = s_off[c] - b + atomicAdd(&s_cnt[c], 1u);
       if (np > (uint32_t)kObsPass) {  // a cell that did not collide
         if (base + q < d.ntot) order[base + q] = i;
       } else if (q < (uint32_t)kObsPass) {
-        s_id[q] = S.id[i];
+        s_id[q] = id;
         s_slot[q] = i;
         s_lc[q] = (uint8_t)c;
       }
+    };
+    if (s_n <= (uint32_t)kObsList) {
+      for (uint32_t q = lane; q < s_n; q += 64) place_in_pass(s_llc[q], s_lid[q], s_lslot[q]);
+    } else {
+      sweep(place_in_pass);
     }
     wave_sync();
     if (np <= (uint32_t)kObsPass) {
@@ -2934,18 +3024,22 @@ __global__ __launch_bounds__(64) void k_obs_order(Dev d, uint32_t box, uint32_t 
       }
       wave_sync();
       uint32_t place[NS];
+      typename Fm::P p[NS];
+      typename Fm::Vv v[NS];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const uint32_t q = lane + k * 64;
+        if (q < np) Fm::load(S, s_can[q], p[k], v[k]);
+      }
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * 64;
         place[k] = 0u;
         __builtin_amdgcn_sched_barrier(0);
         if (q < np) {
-          typename Fm::P p;
-          typename Fm::Vv v;
-          Fm::load(S, s_can[q], p, v);
-          Fm::template stream<W>(p, v, B, bs.d2, le);
+          Fm::template stream<W>(p[k], v[k], B, bs.d2, le);
           int c[3];
-          Fm::template coords<W>(p, sn, B, c, err, bs.d2, le);
+          Fm::template coords<W>(p[k], sn, B, c, err, bs.d2, le);
           const int dx = wrap1(c[0] - x0 + 1, L0);
           int dy = c[1] - y0, dz = c[2] - z0;
           dy += L1 & -(int)(dy < -1);
@@ -3202,18 +3296,31 @@ hipError_t launch_canon_perm(const Dev& d, const Launch& l, const StatePtrs& ids
 }
 
 hipError_t launch_gather_particles(const Dev& d, const Launch& l, const StatePtrs& S,
-                                  uint32_t* inv, uint32_t pbase, uint32_t np,
-                                  const uint32_t* lidx, uint32_t m, double* out) {
+                                  uint32_t* inv, uint32_t* keys, uint32_t mask, uint32_t pbase,
+                                  uint32_t np, uint32_t* sel, uint32_t m, double* out) {
   if (m == 0 || np == 0) return hipSuccess;
   (void)d;
-  if (inv) {
+  const dim3 gm((m + kThreads - 1) / kThreads), b(kThreads);
+  if (keys) {
+    uint32_t* slots = keys + (size_t)mask + 1;
+    const hipError_t e = launch_fill_u32(keys, 2ull * ((uint64_t)mask + 1), kNoSlot, l.stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sample_insert, gm, b, 0, l.stream, sel, m, keys, mask);
+    const uint32_t blocks =
+        (uint32_t)std::min<uint64_t>(8192, ((uint64_t)np + 4 * kThreads - 1) / (4 * kThreads));
+    hipLaunchKernelGGL(k_sample_find, dim3(blocks), b, 0, l.stream, (const uint32_t*)S.id,
+                       S.id_stride, pbase, np, keys, slots, mask);
+    hipLaunchKernelGGL(k_sample_slots, gm, b, 0, l.stream, sel, m, keys, slots, mask);
+  } else {
+    const hipError_t e = launch_fill_u32(inv, np, kNoSlot, l.stream);
+    if (e != hipSuccess) return e;
     uint64_t blocks = ((uint64_t)np + kThreads - 1) / kThreads;
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_invert_ids, dim3((uint32_t)blocks), dim3(kThreads), 0, l.stream,
                        (const uint32_t*)S.id, S.id_stride, pbase, np, inv);
   }
-  MPC_FORM_DISPATCH(l.form, k_gather_particles, dim3((m + kThreads - 1) / kThreads),
-                    dim3(kThreads), 0, l.stream, S, inv, pbase, np, lidx, m, out);
+  MPC_FORM_DISPATCH(l.form, k_gather_particles, gm, b, 0, l.stream, S, inv, pbase, np, sel, m,
+                    out);
   return hipGetLastError();
 }
 
