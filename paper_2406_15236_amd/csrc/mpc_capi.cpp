@@ -20,6 +20,8 @@ namespace {
 
 constexpr uint64_t kMaxIndex = 0x7fffffffull;  // particle and cell indices stay below 2^31
 constexpr int64_t kStateChunk = int64_t(1) << 22;  // particles per host staging chunk
+constexpr size_t kKeepStage = (size_t)64 << 20;    // largest device staging a handle keeps
+constexpr size_t kMaxStage = (size_t)1 << 30;      // and largest of one call
 constexpr int kMinTileCells = 4;
 constexpr int32_t kMaxGraphSteps = 1000;  // steps captured in one graph
 static_assert(MPC_MAX_CELL_PARTICLES == kTileCap, "the ABI's cell limit is one collide pass");
@@ -55,6 +57,7 @@ struct Plan {
   uint64_t max_tiles = 0, npblocks = 0;
   uint64_t rows = 0;      // rows of cells in all boxes
   uint32_t drawb = 0;     // cells per draw block
+  size_t off_shared = 0, shared = 0;  // run lists or binning export
   uint64_t run_pool = 0;  // runs of all tiles' tables per state buffer
   size_t charge = 0;      // bytes the static scratch is checked against
   size_t rec = 0;  // bytes per particle record
@@ -228,6 +231,8 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   }
   P.off_tblk = take(4 * (P.max_tiles / kTileBlock + 1));
   off = std::max(off, shared1);
+  P.off_shared = shared0;
+  P.shared = off - shared0;
   P.off_toff = take(4 * P.max_tiles);
   P.off_ctrl = take(sizeof(Ctrl));
   P.off_boxes = take(sizeof(BoxDev) * nbox);
@@ -323,6 +328,9 @@ struct mpc_sim {
   int order = 0;  // tile order: 0 = row by row inside a block of rows, 1 = x-segment major
   int num_cu = 256, occupancy = 4;
   double* vmean = nullptr;
+  char* ws = nullptr;
+  char* stage = nullptr;  // device staging of set_state and get_state, kept up to kKeepStage
+  size_t stage_bytes = 0;
   std::string err;
 };
 
@@ -556,6 +564,66 @@ int read_ids(mpc_sim* s, const StatePtrs& S, uint64_t p0, std::vector<uint32_t>&
   return MPC_OK;
 }
 
+// Device staging for up to n particles (48 bytes each) and a flag before them.
+// Small ones stay with the handle; without device memory the run lists' part
+// of the workspace serves, and the next step sorts the state again.
+struct Stage {
+  mpc_sim* s = nullptr;
+  char* own = nullptr;
+  uint32_t* flag = nullptr;
+  double* data = nullptr;
+  int64_t cap = 0;  // particles
+  ~Stage() {
+    if (own) (void)hipFree(own);
+  }
+};
+void get_stage(mpc_sim* s, int64_t n, Stage* st) {
+  st->s = s;
+  const size_t want = std::min<size_t>(kMaxStage, 256 + 48 * (size_t)n);
+  char* p = nullptr;
+  size_t bytes = want;
+  if (want <= s->stage_bytes) {
+    p = s->stage;
+    bytes = s->stage_bytes;
+  } else if (hipMalloc((void**)&p, want) == hipSuccess) {
+    if (want <= kKeepStage) {
+      if (s->stage) (void)hipFree(s->stage);
+      s->stage = p;
+      s->stage_bytes = want;
+    } else {
+      st->own = p;
+    }
+  } else {
+    (void)hipGetLastError();
+    p = s->ws + s->plan.off_shared;
+    bytes = s->plan.shared;
+    s->keys_valid = false;
+    s->binning_ready = false;
+  }
+  st->flag = (uint32_t*)p;
+  st->data = (double*)(p + 256);
+  st->cap = (int64_t)((bytes - 256) / 48);
+}
+
+// Rows k of host arrays x[3][n], v[3][n], particles i0 .. i0 + m - 1 <-> the
+// staged arrays x[3][m], v[3][m].
+int stage_copy(mpc_sim* s, double* dx, double* dv, const double* x, const double* v, int64_t n,
+               int64_t i0, int64_t m, bool in) {
+  for (int a = 0; a < 2; ++a) {
+    double* d = a ? dv : dx;
+    double* h = const_cast<double*>(a ? v : x);
+    const int rows = m == n ? 1 : 3;  // whole arrays are contiguous
+    for (int k = 0; k < rows; ++k) {
+      double* dk = d + (size_t)k * m;
+      double* hk = h + (size_t)k * n + i0;
+      const size_t bytes = sizeof(double) * (size_t)m * (rows == 1 ? 3 : 1);
+      HIPCHK(s, in ? hipMemcpyAsync(dk, hk, bytes, hipMemcpyHostToDevice, s->L.stream)
+                   : hipMemcpyAsync(hk, dk, bytes, hipMemcpyDeviceToHost, s->L.stream));
+    }
+  }
+  return MPC_OK;
+}
+
 // Cells per tile of the order of the observables' sums: a mean of 95 % of its
 // passes' capacity.
 uint32_t obs_tile_cells(double density) {
@@ -649,7 +717,7 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->form = p[0].form;
   s->R = p[0].reorder_every;
   const Plan& P = s->plan;
-  char* ws = (char*)workspace;
+  char* ws = s->ws = (char*)workspace;
   for (int b = 0; b < 2; ++b) {
     s->dev.S[b].rec = ws + P.off_rec[b];
     s->dev.S[b].id = P.split ? &((RecSplit*)(ws + P.off_rec[b]))->id : (uint32_t*)(ws + P.off_id[b]);
@@ -778,6 +846,7 @@ int mpc_destroy(mpc_sim* s) {
   (void)hipStreamSynchronize(s->L.stream);
   drop_graph(s);
   if (s->capture_stream) (void)hipStreamDestroy(s->capture_stream);
+  if (s->stage) (void)hipFree(s->stage);
   delete s;
   return MPC_OK;
 }
@@ -970,74 +1039,33 @@ int mpc_set_state(mpc_sim* s, int32_t box, const double* x, const double* v, int
     return MPC_EINVAL;
   }
   const double a = s->params[box].a;
-  const bool walls = B.walls;
-  // validate positions (internal units)
-  for (int k = 0; k < 3; ++k) {
-    const double Lk = B.Ld[k];
-    for (int64_t i = 0; i < n; ++i) {
-      const double xi = x[k * n + i] / a;
-      const bool ok = (walls && k == 2) ? (xi >= 0.0 && xi <= Lk) : (xi >= 0.0 && xi < Lk);
-      if (!ok || !isfinite(v[k * n + i])) {
+  HIPCHK(s, hipStreamSynchronize(s->L.stream));
+  Stage st;
+  get_stage(s, n, &st);
+  const int64_t chunk = std::min(n, st.cap);
+  if (chunk < 1) return hip_fail(s, hipErrorOutOfMemory, "staging");
+  HIPCHK(s, launch_zero_u32(st.flag, 1, s->L.stream));
+  // everything is checked before anything is changed: one chunk stays on the
+  // device in between, several are copied twice
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int64_t i0 = 0; i0 < n; i0 += chunk) {
+      const int64_t m = std::min(chunk, n - i0);
+      double* dx = st.data;
+      double* dv = st.data + 3 * m;
+      int rc;
+      if ((pass == 0 || chunk < n) && (rc = stage_copy(s, dx, dv, x, v, n, i0, m, true))) return rc;
+      HIPCHK(s, launch_state_in(s->dev, s->L, s->dev.S[s->cur], (uint32_t)box, (uint32_t)i0, dx, dv,
+                                (uint32_t)m, a, pass == 0 ? st.flag : nullptr));
+    }
+    if (pass == 0) {
+      uint32_t bad = 0;
+      HIPCHK(s, hipMemcpyAsync(&bad, st.flag, sizeof bad, hipMemcpyDeviceToHost, s->L.stream));
+      HIPCHK(s, hipStreamSynchronize(s->L.stream));
+      if (bad) {
         s->err = "position outside the box or non-finite velocity";
         return MPC_EINVAL;
       }
     }
-  }
-  HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  // records (and ids) of the box, packed on the host a chunk at a time
-  const StatePtrs& S = s->dev.S[s->cur];
-  const size_t rb = s->plan.rec;
-  const int64_t chunk = std::min<int64_t>(n, kStateChunk);
-  std::vector<unsigned char> rbuf((size_t)chunk * rb);
-  std::vector<uint32_t> ibuf(s->plan.split ? 0 : (size_t)chunk);
-  for (int64_t i0 = 0; i0 < n; i0 += chunk) {
-    const int64_t m = std::min(chunk, n - i0);
-    for (int64_t i = 0; i < m; ++i) {
-      const int64_t g = i0 + i;
-      const uint32_t id = B.pbase + (uint32_t)g;
-      if (s->form == MPC_FP64) {
-        RecF64& r = ((RecF64*)rbuf.data())[i];
-        for (int k = 0; k < 3; ++k) {
-          r.x[k] = x[k * n + g] / a;
-          r.v[k] = v[k * n + g] / a;
-        }
-        ibuf[i] = id;
-      } else if (s->form == MPC_FP32) {
-        RecF32& r = ((RecF32*)rbuf.data())[i];
-        for (int k = 0; k < 3; ++k) {
-          float f = (float)(x[k * n + g] / a);
-          if (!(walls && k == 2) && f >= B.Lf[k]) f = nextafterf(B.Lf[k], 0.0f);
-          r.x[k] = f;
-          r.v[k] = (float)(v[k * n + g] / a);
-        }
-        ibuf[i] = id;
-      } else {
-        RecSplit& r = ((RecSplit*)rbuf.data())[i];
-        r.cell = 0u;
-        for (int k = 0; k < 3; ++k) {
-          const uint32_t shift = k == 0 ? 0 : (k == 1 ? kSplitXBits : kSplitXBits + kSplitYBits);
-          const double xi = x[k * n + g] / a;
-          double fl = floor(xi);
-          float o = (float)(xi - fl);
-          if (o >= 1.0f) {
-            o = 0.0f;
-            fl += 1.0;
-          }
-          int c = (int)fl;
-          if (!(walls && k == 2) && c >= B.L[k]) c -= B.L[k];
-          r.cell |= (uint32_t)c << shift;
-          r.o[k] = o;
-          r.v[k] = (float)(v[k * n + g] / a);
-        }
-        r.id = id;
-      }
-    }
-    HIPCHK(s, hipMemcpyAsync((char*)S.rec + (B.pbase + (uint64_t)i0) * rb, rbuf.data(),
-                             (size_t)m * rb, hipMemcpyHostToDevice, s->L.stream));
-    if (!s->plan.split)
-      HIPCHK(s, hipMemcpyAsync(S.id + B.pbase + i0, ibuf.data(), sizeof(uint32_t) * (size_t)m,
-                               hipMemcpyHostToDevice, s->L.stream));
-    HIPCHK(s, hipStreamSynchronize(s->L.stream));  // the staging buffers are reused
   }
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 1));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
@@ -1055,51 +1083,23 @@ int mpc_get_state(mpc_sim* s, int32_t box, double* x, double* v, int64_t n) {
   int rc = mpc_sync(s);
   if (rc) return rc;
   const double a = s->params[box].a;
-  const StatePtrs& S = s->dev.S[s->cur];
-  // records (and ids) of the box, a chunk at a time, each written to the
-  // caller's order given by its logical index
-  const size_t rb = s->plan.rec;
-  const int64_t chunk = std::min<int64_t>(n, kStateChunk);
-  std::vector<unsigned char> rbuf((size_t)chunk * rb);
-  std::vector<uint32_t> ibuf(s->plan.split ? 0 : (size_t)chunk);
-  std::vector<uint8_t> seen(n, 0);
+  Stage st;
+  get_stage(s, n, &st);
+  const int64_t chunk = std::min(n, st.cap);
+  if (chunk < 1) return hip_fail(s, hipErrorOutOfMemory, "staging");
   for (int64_t i0 = 0; i0 < n; i0 += chunk) {
     const int64_t m = std::min(chunk, n - i0);
-    HIPCHK(s, hipMemcpyAsync(rbuf.data(), (const char*)S.rec + (B.pbase + (uint64_t)i0) * rb,
-                             (size_t)m * rb, hipMemcpyDeviceToHost, s->L.stream));
-    if (!s->plan.split)
-      HIPCHK(s, hipMemcpyAsync(ibuf.data(), S.id + B.pbase + i0, sizeof(uint32_t) * (size_t)m,
-                               hipMemcpyDeviceToHost, s->L.stream));
+    double* dx = st.data;
+    double* dv = st.data + 3 * m;
+    HIPCHK(s, launch_state_out(s->L, s->dev.S[s->cur], B.pbase, B.np, (uint32_t)i0, dx, dv,
+                               (uint32_t)m, a, st.flag));
+    if ((rc = stage_copy(s, dx, dv, x, v, n, i0, m, false))) return rc;
+    uint32_t bad = 0;
+    HIPCHK(s, hipMemcpyAsync(&bad, st.flag, sizeof bad, hipMemcpyDeviceToHost, s->L.stream));
     HIPCHK(s, hipStreamSynchronize(s->L.stream));
-    for (int64_t i = 0; i < m; ++i) {
-      const uint32_t id = s->plan.split ? ((const RecSplit*)rbuf.data())[i].id : ibuf[i];
-      const uint32_t q = id - B.pbase;
-      if (id < B.pbase || q >= (uint64_t)n || seen[q]) {
-        s->err = "logical particle indices are not a permutation";
-        return MPC_ESTATE;
-      }
-      seen[q] = 1;
-      if (s->form == MPC_FP64) {
-        const RecF64& r = ((const RecF64*)rbuf.data())[i];
-        for (int k = 0; k < 3; ++k) {
-          x[k * n + q] = r.x[k] * a;
-          v[k * n + q] = r.v[k] * a;
-        }
-      } else if (s->form == MPC_FP32) {
-        const RecF32& r = ((const RecF32*)rbuf.data())[i];
-        for (int k = 0; k < 3; ++k) {
-          x[k * n + q] = (double)r.x[k] * a;
-          v[k * n + q] = (double)r.v[k] * a;
-        }
-      } else {
-        const RecSplit& r = ((const RecSplit*)rbuf.data())[i];
-        for (int k = 0; k < 3; ++k) {
-          const uint32_t shift = k == 0 ? 0 : (k == 1 ? kSplitXBits : kSplitXBits + kSplitYBits);
-          const uint32_t mask = k == 2 ? ((1u << kSplitZBits) - 1) : ((1u << kSplitXBits) - 1);
-          x[k * n + q] = ((double)((r.cell >> shift) & mask) + (double)r.o[k]) * a;
-          v[k * n + q] = (double)r.v[k] * a;
-        }
-      }
+    if (bad) {
+      s->err = "logical particle indices are not a permutation";
+      return MPC_ESTATE;
     }
   }
   return MPC_OK;

@@ -237,6 +237,14 @@ hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean
 hipError_t launch_gather_particles(const Dev& d, const Launch& l, const StatePtrs& S,
                                   uint32_t* inv, uint32_t* keys, uint32_t mask, uint32_t pbase,
                                   uint32_t np, uint32_t* sel, uint32_t m, double* out);
+// FP64 arrays x[3][m], v[3][m] on the device <-> records of particles i0 ..
+// i0 + m - 1 of a box; in: checked if bad is given, else packed
+hipError_t launch_state_in(const Dev& d, const Launch& l, const StatePtrs& S, uint32_t box,
+                           uint32_t i0, const double* x, const double* v, uint32_t m, double a,
+                           uint32_t* bad);
+hipError_t launch_state_out(const Launch& l, const StatePtrs& S, uint32_t pbase, uint32_t np,
+                            uint32_t i0, double* x, double* v, uint32_t m, double a,
+                            uint32_t* bad);
 // box 0, FP64 form: caller's device arrays (physical units) <-> state buffer cur
 hipError_t launch_load_f64(const Dev& d, const Launch& l, const double* x, const double* v,
                            uint32_t n, double a, uint32_t cur);
