@@ -234,6 +234,19 @@ __device__ __forceinline__ float wrap32(float x, float L) {
   return x;
 }
 
+// Whether x may lie outside [0, L), from the high words: a negative x, a NaN
+// and an infinity have larger ones than any L, and so has x >= L (for x < L
+// they can be equal only if L > 2^21).  Of a wavefront's particles most stay
+// inside, and then one 32-bit comparison per axis stands for the wraps (ten
+// instructions each) and for the range checks of the cell coordinates.
+__device__ __forceinline__ bool maybe_outside(double x, double L) {
+  return (uint32_t)((uint64_t)__double_as_longlong(x) >> 32) >=
+         (uint32_t)((uint64_t)__double_as_longlong(L) >> 32);
+}
+__device__ __forceinline__ bool maybe_outside(float x, float L) {
+  return __float_as_uint(x) >= __float_as_uint(L);
+}
+
 // Lees-Edwards shear of a periodic box (Sec. II, boundary conditions): at
 // time tau = t_end h the image above the box (z + L_z) is displaced by
 // d = (U tau) mod L_x along x and moves with U.  A particle through a z face
@@ -282,10 +295,15 @@ __device__ __forceinline__ void stream_f64(double (&x)[3], double (&v)[3], BoxRe
         v[0] = v[0] + B.leu;
       }
     }
-    ze = wrap64(ze, B.Ld[2]);
   }
-  x[0] = wrap64(xe, B.Ld[0]);
-  x[1] = wrap64(ye, B.Ld[1]);
+  if (maybe_outside(xe, B.Ld[0]) || maybe_outside(ye, B.Ld[1]) ||
+      (!W && maybe_outside(ze, B.Ld[2]))) {
+    xe = wrap64(xe, B.Ld[0]);
+    ye = wrap64(ye, B.Ld[1]);
+    if (!W) ze = wrap64(ze, B.Ld[2]);
+  }
+  x[0] = xe;
+  x[1] = ye;
   x[2] = ze;
 }
 
@@ -325,10 +343,15 @@ __device__ __forceinline__ void stream_f32(float (&x)[3], float (&v)[3], BoxRef 
         v[0] = v[0] + B.leuf;
       }
     }
-    ze = wrap32(ze, B.Lf[2]);
   }
-  x[0] = wrap32(xe, B.Lf[0]);
-  x[1] = wrap32(ye, B.Lf[1]);
+  if (maybe_outside(xe, B.Lf[0]) || maybe_outside(ye, B.Lf[1]) ||
+      (!W && maybe_outside(ze, B.Lf[2]))) {
+    xe = wrap32(xe, B.Lf[0]);
+    ye = wrap32(ye, B.Lf[1]);
+    if (!W) ze = wrap32(ze, B.Lf[2]);
+  }
+  x[0] = xe;
+  x[1] = ye;
   x[2] = ze;
 }
 
@@ -426,10 +449,13 @@ __device__ __forceinline__ void stream_split(uint32_t& cell, float (&o)[3], floa
       split_from_double(xd, cn[0], on[0]);
       v[0] = (float)(up ? (double)v[0] - B.leu : (double)v[0] + B.leu);
     }
-    cn[2] = wrap_cell(cn[2], B.L[2]);
   }
-  cn[0] = wrap_cell(cn[0], B.L[0]);
-  cn[1] = wrap_cell(cn[1], B.L[1]);
+  if ((unsigned)cn[0] >= (unsigned)B.L[0] || (unsigned)cn[1] >= (unsigned)B.L[1] ||
+      (!W && (unsigned)cn[2] >= (unsigned)B.L[2])) {
+    cn[0] = wrap_cell(cn[0], B.L[0]);
+    cn[1] = wrap_cell(cn[1], B.L[1]);
+    if (!W) cn[2] = wrap_cell(cn[2], B.L[2]);
+  }
   o[0] = on[0];
   o[1] = on[1];
   o[2] = on[2];
@@ -446,6 +472,19 @@ __device__ __forceinline__ int wrap1(int c, int L) {
 // Shifted cell coordinates c_k = floor(x_k + s_k) of a position given as
 // integer part ci_k plus fraction xf_k in double (exact), with periodic wrap
 // (walls: z becomes the layer index c_z + 1 in [0, H+1]).  Invalid -> err.
+//
+// coords_fast: the same for a position whose shifted coordinates all lie in
+// [0, L); false if that is not certain.
+__device__ __forceinline__ bool coords_fast(const double (&x)[3], const double (&s)[3], BoxRef B,
+                                            bool walls, int (&c)[3]) {
+  const double y[3] = {x[0] + s[0], x[1] + s[1], x[2] + s[2]};
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c[k] = (int)floor(y[k]);
+  if (walls) c[2] += 1;
+  return !(maybe_outside(y[0], B.Ld[0]) || maybe_outside(y[1], B.Ld[1]) ||
+           maybe_outside(y[2], B.Ld[2]));
+}
+
 template <bool W>
 __device__ __forceinline__ bool coords_of(const int (&ci)[3], const double (&xf)[3],
                                           const double (&s)[3], BoxRef B, int (&c)[3],
@@ -578,8 +617,9 @@ struct Form<kFormF64> {
   template <bool W>
   __device__ static void coords(const P& p, const double (&s)[3], BoxRef B, int (&c)[3],
                                 uint32_t& err, double dle, bool le) {
-    const int ci[3] = {0, 0, 0};
     const double xf[3] = {p.x[0], p.x[1], p.x[2]};
+    if (coords_fast(xf, s, B, W, c)) return;
+    const int ci[3] = {0, 0, 0};
     coords_of<W>(ci, xf, s, B, c, err, dle, le);
   }
   // Lees-Edwards side of the collision cell: +1 below the lower z face,
@@ -587,6 +627,7 @@ struct Form<kFormF64> {
   // x coordinate of the collision cell (as coords)
   __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
     const double y = (double)p.x[0] + s[0];
+    if (!le && !maybe_outside(y, B.Ld[0])) return (int)floor(y);
     int c = (int)floor(y >= -2.0 && y < B.Ld[0] + 2.0 ? y : 0.0);
     if (le) {
       const double cz = floor((double)p.x[2] + s[2]);
@@ -650,13 +691,15 @@ struct Form<kFormF32> {
   template <bool W>
   __device__ static void coords(const P& p, const double (&s)[3], BoxRef B, int (&c)[3],
                                 uint32_t& err, double dle, bool le) {
-    const int ci[3] = {0, 0, 0};
     const double xf[3] = {(double)p.x[0], (double)p.x[1], (double)p.x[2]};
+    if (coords_fast(xf, s, B, W, c)) return;
+    const int ci[3] = {0, 0, 0};
     coords_of<W>(ci, xf, s, B, c, err, dle, le);
   }
   // x coordinate of the collision cell (as coords)
   __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
     const double y = (double)p.x[0] + s[0];
+    if (!le && !maybe_outside(y, B.Ld[0])) return (int)floor(y);
     int c = (int)floor(y >= -2.0 && y < B.Ld[0] + 2.0 ? y : 0.0);
     if (le) {
       const double cz = floor((double)p.x[2] + s[2]);
@@ -721,7 +764,16 @@ struct Form<kFormSplit> {
     int ci[3];
     split_decode(p.cell, ci);
     if (!le) {
-      coords_split<W>(ci, p.o, s, B, c, err);
+      // inside without a wrap (|y| < 2 also excludes NaN), else the full rule
+      const float y[3] = {p.o[0] + (float)s[0], p.o[1] + (float)s[1], p.o[2] + (float)s[2]};
+      bool in = true;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        c[k] = ci[k] + (int)floorf(y[k]);
+        in = in && fabsf(y[k]) < 2.0f && (unsigned)c[k] < (unsigned)B.L[k];
+      }
+      if (W) c[2] += 1;
+      if (!in) coords_split<W>(ci, p.o, s, B, c, err);
       return;
     }
     // Lees-Edwards: the image offset is applied in FP64
@@ -2179,8 +2231,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       typename Fm::P p[NS];
       typename Fm::Vv v[NS];
       uint32_t idk[NS], meta[NS];
-      // issue the gathers ahead of other waves' arithmetic
-      __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * NT;
@@ -2205,7 +2255,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
         Tn = load_tile(d.tiles, tnext);
         fetch(Tn, ah);
       }
-      __builtin_amdgcn_s_setprio(0);
       if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
       if (lane < (uint32_t)kGroups + 1u) s_grp[lane] = 0u;
       for (uint32_t q = lane; q < (uint32_t)kIds / 4; q += NT)
@@ -2403,8 +2452,11 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
                           : (unsigned)(c[0] - xp) < (unsigned)ncp ? 0
                           : (unsigned)(c[0] - xn) < (unsigned)ncn ? 2
                                                                   : 3;
-          const int ry = wrap1(c[1] - y0 - wy, L1);
-          const int rz = W ? c[2] - z0 - wz : wrap1(c[2] - z0 - wz, L2);
+          int ry = c[1] - y0 - wy, rz = c[2] - z0 - wz;
+          if ((unsigned)ry >= 3u || (!W && (unsigned)rz >= 3u)) {
+            ry = wrap1(ry, L1);
+            if (!W) rz = wrap1(rz, L2);
+          }
           uint32_t g = (uint32_t)((rz * 3 + ry) * 3 + seg);
           if (!((unsigned)ry < 3u && (unsigned)rz < 3u && seg < 3)) {
             g = (uint32_t)kGroups;
@@ -2487,7 +2539,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       if (gdest != kNoSlot) push_run(d, nxt, tnx, gdest, base + gpre, gn);
       // the pass's particles, grouped by next-step tile, into its slots;
       // logical indices: the canonical (cell, index) position on reorder steps
-      __builtin_amdgcn_s_setprio(2);
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
         const uint32_t q = lane + k * NT;
@@ -2500,7 +2551,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
           }
         }
       }
-      __builtin_amdgcn_s_setprio(0);
       base += np;
       cs = ce;
       wave_sync();
