@@ -1499,12 +1499,16 @@ __device__ __forceinline__ void rotate(T ca, T sa, T omc, const T (&n)[3], const
   for (int a = 0; a < 3; ++a) r[a] = ca * u[a] + sa * cx[a] + omc * nu * n[a];
 }
 
-// Sums of one cell by a pair of lanes (lane bit 0 = half): each lane sums
-// half of the cell's fluid particles, sv[k][b..e) in canonical order (first
-// half, then second), and the pair combines the halves in that order, so both
-// lanes hold identical totals.  A wall-cut cell adds its phantoms' sums (ph,
-// drawn by k_phantom_sums).  Every lane of the wavefront calls this (the pair
-// exchanges values); only the first lane of a valid pair writes `out`.
+// The cell sums.  Each half of a cell's fluid particles is summed by one lane
+// in canonical order, and the pair of lanes (lane bit 0 = half) combines first
+// half, then second, so that both hold the same total whatever the tiling.
+// A pair sums the three components of the momentum (and of the centre of mass,
+// SRD+a) together, or, in passes of at most ten cells, one of them: six lanes
+// a cell in place of two (50 particles per cell, four cells a pass: collide
+// 1.52 -> 1.44 ms at 96^3; with 20 cells in two rounds it gained nothing in
+// FP64 and cost 4 % in FP32).  The terms of the kinetic energy come from the
+// lanes that hold the particles, so that its sum is one read and one addition
+// per particle.
 __device__ __forceinline__ double pair_xor(double x) { return __shfl_xor(x, 1, 64); }
 __device__ __forceinline__ float pair_xor(float x) { return __shfl_xor(x, 1, 64); }
 
@@ -1512,47 +1516,47 @@ __device__ __forceinline__ float pair_xor(float x) { return __shfl_xor(x, 1, 64)
 // integer trunc(x 2^80) in 128-bit two's complement; sums are exact, hence
 // independent of the order of the terms, and the value is the integer rounded
 // once to FP64, times 2^-80.  Terms need |x| < 2^37 (no sum of at most 2^10
-// terms can overflow); others (and NaN) set kErrFixRange.
+// terms can overflow); others (and NaN) set kErrFixRange.  While summing, the
+// integer is kept as four signed digits of 32 bits, each an FP64 number: the
+// digits of a term come out by truncation, exactly, and the sums of at most
+// 2^10 of them stay below 2^53.  Fifteen FP64 operations a term; 128-bit
+// shifts, a negation and an addition with carry had taken about forty.
+struct FixSum {
+  double d[4];  // digits of 2^0, 2^32, 2^64, 2^96
+};
 struct Fix {
   uint64_t lo, hi;
 };
-__device__ __forceinline__ void fix_add(Fix& a, double x, uint32_t& err) {
+__device__ __forceinline__ void fix_add(FixSum& a, double x, uint32_t& err) {
   if (!(fabs(x) < 0x1p37)) {
     err |= kErrFixRange;
     return;
   }
-  const uint64_t bits = (uint64_t)__double_as_longlong(x);
-  const uint32_t ex = (uint32_t)(bits >> 52) & 0x7ffu;
-  uint64_t mant = bits & 0x000fffffffffffffull;
-  if (ex) mant |= 0x0010000000000000ull;
-  // |x| 2^80 = mant 2^sh, sh = max(ex, 1) - 1075 + 80 <= 64 in range
-  const int sh = (int)(ex ? ex : 1u) - 995;
-  uint64_t lo, hi;
-  if (sh >= 64) {
-    lo = 0;
-    hi = mant;
-  } else if (sh > 0) {
-    lo = mant << sh;
-    hi = mant >> (64 - sh);
-  } else {
-    lo = -sh < 64 ? mant >> -sh : 0ull;  // truncation of the magnitude
-    hi = 0;
-  }
-  if (bits >> 63) {
-    lo = ~lo + 1ull;
-    hi = ~hi + (lo == 0ull ? 1ull : 0ull);
-  }
-  const uint64_t nlo = a.lo + lo;
-  a.hi = a.hi + hi + (nlo < lo ? 1ull : 0ull);
-  a.lo = nlo;
+  double r = x * 0x1p-16;
+  double w = __builtin_trunc(r);
+  a.d[3] += w;
+  r = (r - w) * 0x1p32;
+  w = __builtin_trunc(r);
+  a.d[2] += w;
+  r = (r - w) * 0x1p32;
+  w = __builtin_trunc(r);
+  a.d[1] += w;
+  a.d[0] += __builtin_trunc((r - w) * 0x1p32);
 }
-// Exact sum over the lane pair (both lanes hold the total).
-__device__ __forceinline__ void fix_pair(Fix& a) {
-  const uint64_t olo = (uint64_t)__shfl_xor((long long)a.lo, 1, 64);
-  const uint64_t ohi = (uint64_t)__shfl_xor((long long)a.hi, 1, 64);
-  const uint64_t nlo = a.lo + olo;
-  a.hi = a.hi + ohi + (nlo < olo ? 1ull : 0ull);
-  a.lo = nlo;
+// Exact sum over the lane pair (both lanes hold the total), as one integer.
+__device__ __forceinline__ Fix fix_pair(const FixSum& a) {
+  Fix f = {0ull, 0ull};
+#pragma unroll
+  for (int k = 3; k >= 0; --k) {
+    const long long t = (long long)(a.d[k] + pair_xor(a.d[k]));
+    // f = f 2^32 + t
+    f.hi = f.hi << 32 | f.lo >> 32;
+    f.lo <<= 32;
+    const uint64_t nlo = f.lo + (uint64_t)t;
+    f.hi += (t < 0 ? ~0ull : 0ull) + (nlo < f.lo ? 1ull : 0ull);
+    f.lo = nlo;
+  }
+  return f;
 }
 // Nearest FP64 of the integer, times 2^-80.  The 128-bit magnitude is
 // normalised so that its top 64 bits carry the rounding position, with the
@@ -1577,63 +1581,73 @@ __device__ __forceinline__ double fix_value(Fix a) {
   return neg ? -d : d;
 }
 
-template <int F, bool W, bool M, bool A, bool X>
-__device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, const double (&axis)[3],
-                          double Ek,
-                          const PhantomSums* __restrict__ ph,
-                          const typename Form<F>::Vs* __restrict__ sv0,
-                          const typename Form<F>::Vs* __restrict__ sv1,
-                          const typename Form<F>::Vs* __restrict__ sv2,
-                          const typename Form<F>::Xs* __restrict__ sx0,
-                          const typename Form<F>::Xs* __restrict__ sx1,
-                          const typename Form<F>::Xs* __restrict__ sx2, const double (&s)[3],
-                          uint32_t b, uint32_t e, uint32_t half, bool valid,
-                          typename CellRec<F, A>::T* out, uint32_t& err,
-                          const int8_t* __restrict__ sside, double dle) {
-  const uint32_t nf = valid ? e - b : 0u;
-  const uint32_t mid = b + (nf + 1) / 2;
-  const uint32_t qb = half ? mid : b, qe = valid ? (half ? e : mid) : b;
-  uint32_t nph = 0;
-  double pv[3] = {0.0, 0.0, 0.0}, pv2 = 0.0;
-  if (W && !B.slip && valid && nf > 0) {
-    const int cz = (int)(lkey / (uint32_t)(B.L[0] * B.L[1])) - 1;
-    if (wall_fraction(sz, cz, B.L[2]) > 0.0) {
-      nph = (uint32_t)ph->n;
-      pv[0] = ph->v[0];
-      pv[1] = ph->v[1];
-      pv[2] = ph->v[2];
-      pv2 = ph->v2;
+template <int N>
+struct Width {
+  static constexpr int value = N;
+};
+
+// Plain or fixed-point FP64 sums of m v[q] (kScale) or of v[q] for N arrays v,
+// one half of the cell, [qb, qe), per lane; both lanes of a pair get the totals.
+template <bool X, bool kScale, int N, typename T>
+__device__ __forceinline__ void half_sums(const T* const (&v)[N], double m, uint32_t qb,
+                                          uint32_t qe, uint32_t half, uint32_t& err,
+                                          double (&out)[N]) {
+  if constexpr (X) {
+    FixSum f[N] = {};
+    for (uint32_t q = qb; q < qe; ++q) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        fix_add(f[k], kScale ? m * (double)v[k][q] : (double)v[k][q], err);
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) out[k] = fix_value(fix_pair(f[k]));
+  } else {
+    double P[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) P[k] = 0.0;
+    if (!kScale || m == 1.0) {  // 1 * v is v
+#pragma unroll 4
+      for (uint32_t q = qb; q < qe; ++q) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) P[k] = P[k] + (double)v[k][q];
+      }
+    } else {
+#pragma unroll 4
+      for (uint32_t q = qb; q < qe; ++q) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) P[k] = P[k] + m * (double)v[k][q];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const double o = pair_xor(P[k]);
+      out[k] = half ? o + P[k] : P[k] + o;
     }
   }
-  const uint32_t ntot = nf + nph;
-  const double m = B.mass;
-  double V[3];
-  if constexpr (X) {
-    // fixed-point momentum sums of the FP64 terms m v_i (every form)
-    Fix fp[3] = {{0ull, 0ull}, {0ull, 0ull}, {0ull, 0ull}};
-    for (uint32_t q = qb; q < qe; ++q) {
-      fix_add(fp[0], m * (double)sv0[q], err);
-      fix_add(fp[1], m * (double)sv1[q], err);
-      fix_add(fp[2], m * (double)sv2[q], err);
-    }
-    double P[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      fix_pair(fp[k]);
-      P[k] = fix_value(fp[k]);
-    }
-    if (W && nph) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) P[k] = P[k] + m * pv[k];
-    }
+}
+
+// Mean velocity of a cell along N axes: its momentum, phantoms included (nph
+// of them with velocity sums pv), by its mass.
+template <int F, bool X, int N>
+__device__ __forceinline__ void mean_velocity(const typename Form<F>::Vs* const (&v)[N], double m,
+                                              uint32_t qb, uint32_t qe, uint32_t half,
+                                              uint32_t ntot, uint32_t nph, const double (&pv)[N],
+                                              uint32_t& err, double (&V)[N]) {
+  if constexpr (X || F != kFormSplit) {
+    // fixed-point or FP64 sums of the FP64 terms m v_i
+    half_sums<X, true>(v, m, qb, qe, half, err, V);
     const double Mtot = (double)(ntot ? ntot : 1u) * m;
-    V[0] = P[0] / Mtot;
-    V[1] = P[1] / Mtot;
-    V[2] = P[2] / Mtot;
-  } else if constexpr (F == kFormSplit) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      if (nph) V[k] = V[k] + m * pv[k];
+      V[k] = V[k] / Mtot;
+    }
+  } else {
     // compensated FP32 momentum sums (Neumaier)
     const float mf = (float)m;
-    float s[3] = {0.f, 0.f, 0.f}, c[3] = {0.f, 0.f, 0.f};
+    float s[N], c[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) s[k] = c[k] = 0.f;
     auto add = [&](int k, float x) {
       const float tt = s[k] + x;
       if (fabsf(s[k]) >= fabsf(x)) {
@@ -1645,12 +1659,12 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
     };
 #pragma unroll 4
     for (uint32_t q = qb; q < qe; ++q) {
-      add(0, mf * sv0[q]);
-      add(1, mf * sv1[q]);
-      add(2, mf * sv2[q]);
-    }
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
+      for (int k = 0; k < N; ++k) add(k, mf * v[k][q]);
+    }
+    const float Mf = (float)(ntot ? ntot : 1u) * mf;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
       const float os = pair_xor(s[k]), oc = pair_xor(c[k]);
       // first half's (s, c), then the second half's s added, then its c
       const float s0 = half ? os : s[k], c0 = half ? oc : c[k];
@@ -1659,58 +1673,42 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
       c[k] = c0;
       add(k, s1);
       c[k] += c1;
+      if (nph) add(k, (float)(m * pv[k]));
+      V[k] = (double)((s[k] + c[k]) / Mf);
     }
-    if (W && nph) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) add(k, (float)(m * pv[k]));
-    }
-    const float Mf = (float)(ntot ? ntot : 1u) * mf;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) V[k] = (double)((s[k] + c[k]) / Mf);
-  } else {
-    double P[3] = {0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (uint32_t q = qb; q < qe; ++q) {
-      P[0] = P[0] + m * (double)sv0[q];
-      P[1] = P[1] + m * (double)sv1[q];
-      P[2] = P[2] + m * (double)sv2[q];
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const double o = pair_xor(P[k]);
-      P[k] = half ? o + P[k] : P[k] + o;
-    }
-    if (W && nph) {
-#pragma unroll
-      for (int k = 0; k < 3; ++k) P[k] = P[k] + m * pv[k];
-    }
-    const double Mtot = (double)(ntot ? ntot : 1u) * m;
-    V[0] = P[0] / Mtot;
-    V[1] = P[1] / Mtot;
-    V[2] = P[2] / Mtot;
   }
+}
+
+// The rest of a cell, by its pair of lanes: V and rc are its mean velocity
+// and (SRD+a) its centre of mass in the cell frame, sk the kinetic-energy
+// terms, sx the cell-frame positions (SRD+a).  Every lane of the wavefront
+// calls this; only the first lane of a valid pair writes `out`.
+template <int F, bool W, bool M, bool A, bool X>
+__device__ __forceinline__ void cell_work(BoxRef B, const double (&axis)[3], double Ek,
+                                          const PhantomSums* __restrict__ ph, uint32_t nph,
+                                          const typename Form<F>::Vs* __restrict__ sv0,
+                                          const typename Form<F>::Vs* __restrict__ sv1,
+                                          const typename Form<F>::Vs* __restrict__ sv2,
+                                          const double* __restrict__ sx0,
+                                          const double* __restrict__ sx1,
+                                          const double* __restrict__ sx2,
+                                          const double* __restrict__ sk, const double (&V)[3],
+                                          const double (&rc)[3], uint32_t b, uint32_t e,
+                                          uint32_t half, bool valid,
+                                          typename CellRec<F, A>::T* out, uint32_t& err) {
+  const uint32_t nf = valid ? e - b : 0u;
+  const uint32_t mid = b + (nf + 1) / 2;
+  const uint32_t qb = half ? mid : b, qe = valid ? (half ? e : mid) : b;
+  const uint32_t ntot = nf + nph;
+  const double m = B.mass;
   double kappa = 1.0, K = 0.0;
   if (M) {
-    if constexpr (X) {
-      Fix fk = {0ull, 0ull};
-      for (uint32_t q = qb; q < qe; ++q) {
-        const double dx = (double)sv0[q] - V[0], dy = (double)sv1[q] - V[1],
-                     dz = (double)sv2[q] - V[2];
-        fix_add(fk, m * (dx * dx + dy * dy + dz * dz), err);
-      }
-      fix_pair(fk);
-      K = fix_value(fk);
-    } else {
-#pragma unroll 4
-      for (uint32_t q = qb; q < qe; ++q) {
-        const double dx = (double)sv0[q] - V[0], dy = (double)sv1[q] - V[1],
-                     dz = (double)sv2[q] - V[2];
-        K = K + m * (dx * dx + dy * dy + dz * dz);
-      }
-      const double oK = pair_xor(K);
-      K = half ? oK + K : K + oK;
-    }
+    const double* const ks[1] = {sk};
+    double Ks[1];
+    half_sums<X, false>(ks, 1.0, qb, qe, half, err, Ks);
+    K = Ks[0];
     if (W && nph) {
+      const double pv[3] = {ph->v[0], ph->v[1], ph->v[2]}, pv2 = ph->v2;
       // sum over phantoms of m |v - V|^2 from their velocity sums
       const double vV = pv[0] * V[0] + pv[1] * V[1] + pv[2] * V[2];
       const double VV = V[0] * V[0] + V[1] * V[1] + V[2] * V[2];
@@ -1725,42 +1723,8 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
   // uses the pseudo-inverse of its singular I (omega = dL / (tr I / 2), since
   // tr I = |r_1 - r_2|^2), three or more Cramer's rule, and det I = 0 gives
   // omega = 0.  Both lanes of the pair build identical totals.
-  double rc[3] = {0.0, 0.0, 0.0}, om[3] = {0.0, 0.0, 0.0};
+  double om[3] = {0.0, 0.0, 0.0};
   if constexpr (A) {
-    // cell-frame x; under Lees-Edwards shear a particle taken as its image
-    // (sside = -1 / +1) sits at x - d / x + d
-    auto fx = [&](uint32_t q) -> double {
-      double xq = (double)sx0[q];
-      if (sside) {
-        if (sside[q] < 0) xq = xq - dle;
-        if (sside[q] > 0) xq = xq + dle;
-      }
-      return frame_pos(xq, s[0]);
-    };
-    if constexpr (X) {
-      Fix fr[3] = {{0ull, 0ull}, {0ull, 0ull}, {0ull, 0ull}};
-      for (uint32_t q = qb; q < qe; ++q) {
-        fix_add(fr[0], fx(q), err);
-        fix_add(fr[1], frame_pos(sx1[q], s[1]), err);
-        fix_add(fr[2], frame_pos(sx2[q], s[2]), err);
-      }
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        fix_pair(fr[k]);
-        rc[k] = fix_value(fr[k]) / (double)(nf ? nf : 1u);
-      }
-    } else {
-      for (uint32_t q = qb; q < qe; ++q) {
-        rc[0] = rc[0] + fx(q);
-        rc[1] = rc[1] + frame_pos(sx1[q], s[1]);
-        rc[2] = rc[2] + frame_pos(sx2[q], s[2]);
-      }
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const double o = pair_xor(rc[k]);
-        rc[k] = (half ? o + rc[k] : rc[k] + o) / (double)(nf ? nf : 1u);
-      }
-    }
     // Moments about the centre of mass: M = sum r_ic u_i^T and S = sum r_ic
     // r_ic^T (15 sums, no per-particle rotation).  Then I = tr(S) 1 - S, the
     // angular momentum before the rotation L0 = eps : M, after it
@@ -1775,11 +1739,10 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
       // sums live at a time
 #pragma unroll 1
       for (int a = 0; a < 3; ++a) {
-        Fix f5[5] = {{0ull, 0ull}, {0ull, 0ull}, {0ull, 0ull}, {0ull, 0ull}, {0ull, 0ull}};
+        FixSum f5[5] = {};
         const int a1 = a == 2 ? 0 : a + 1;
         for (uint32_t q = qb; q < qe; ++q) {
-          const double r[3] = {fx(q) - rc[0], frame_pos(sx1[q], s[1]) - rc[1],
-                               frame_pos(sx2[q], s[2]) - rc[2]};
+          const double r[3] = {sx0[q] - rc[0], sx1[q] - rc[1], sx2[q] - rc[2]};
           const double u[3] = {(double)sv0[q] - V[0], (double)sv1[q] - V[1],
                                (double)sv2[q] - V[2]};
           const double ra = a == 0 ? r[0] : (a == 1 ? r[1] : r[2]);
@@ -1793,8 +1756,7 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
         double v5[5];
 #pragma unroll
         for (int k = 0; k < 5; ++k) {
-          fix_pair(f5[k]);
-          v5[k] = fix_value(f5[k]);
+          v5[k] = fix_value(fix_pair(f5[k]));
         }
         // scatter into mm / ss (ss: xx, yy, zz, xy, xz, yz; a = 2 gives zx = xz)
 #pragma unroll
@@ -1809,8 +1771,7 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
       }
     } else {
     for (uint32_t q = qb; q < qe; ++q) {
-      const double r[3] = {fx(q) - rc[0], frame_pos(sx1[q], s[1]) - rc[1],
-                           frame_pos(sx2[q], s[2]) - rc[2]};
+      const double r[3] = {sx0[q] - rc[0], sx1[q] - rc[1], sx2[q] - rc[2]};
       const double u[3] = {(double)sv0[q] - V[0], (double)sv1[q] - V[1], (double)sv2[q] - V[2]};
 #pragma unroll
       for (int a = 0; a < 3; ++a)
@@ -1897,7 +1858,6 @@ __device__ __forceinline__ void cell_work(BoxRef B, uint32_t lkey, double sz, co
   if constexpr (A) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      out->rc[k] = rc[k];
       out->om[k] = coll ? om[k] : 0.0;
     }
   }
@@ -1974,7 +1934,6 @@ __global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu
 void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   using Fm = Form<F>;
   using Vs = typename Fm::Vs;
-  using Xs = typename Fm::Xs;
   constexpr int NT = kCollideThreads;
   constexpr int NS = kTileCap / kCollideThreads;
   static_assert(kTileMaxCells < NT, "one lane per cell offset (nc + 1) of a tile");
@@ -1990,10 +1949,18 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   __shared__ uint32_t s_delta[kMaxRuns];
   __shared__ uint32_t s_grp[kGroups + 1];
   __shared__ uint32_t s_tot[kTileMaxCells + 1];  // offsets of the whole tile (several passes)
-  __shared__ Vs s_v[3][kTileCap];                // streamed velocities, canonical order
-  __shared__ Xs s_x[A ? 3 : 1][A ? kTileCap : 1];
+  __shared__ __align__(16) Vs s_v[3][kTileCap];  // streamed velocities, canonical order
+  __shared__ double s_x[A ? 3 : 1][A ? kTileCap : 1];  // SRD+a: cell-frame positions, alike
+  // kinetic-energy terms: in the place of the velocities, which only the
+  // moments of SRD+a read after the momentum
+  __shared__ double s_kin[A && M ? kTileCap : 1];
+  static_assert(sizeof(Vs) * 3 * kTileCap >= sizeof(double) * kTileCap, "terms fit");
+  double* const s_k = A ? s_kin : (double*)&s_v[0][0];
+  // mean velocities in FP64 where the cell's record has FP32 but the sums were
+  // not FP32 ones
+  constexpr bool kWide = F == kFormSplit && X;
+  __shared__ double s_mean[kWide ? 3 : 1][kWide ? kTileMaxCells : 1];
   __shared__ typename CellRec<F, A>::T s_cell[kTileMaxCells];
-  __shared__ int8_t s_side[(E && A) ? kTileCap : 1];  // Lees-Edwards side of each slot
 
   __shared__ uint16_t s_dcell[kDrawList];
   __shared__ uint32_t s_dused;
@@ -2074,7 +2041,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
     BoxRef B = as_const(d.boxes)[T.box];
     const MPC_AS4 BoxStep& bs = as_const(d.bstep[cur])[T.box];
     const uint32_t tnext = walk.tile(it + walk.stride);
-    const uint32_t lkey0 = T.c0 - B.cbase;
     // tiles lie inside one row: (x0 .. x0 + nc - 1, y0, z0)
     const int x0 = (int)T.x0, y0 = (int)T.y0, z0 = (int)T.z0, nc = (int)T.nc;
     const int L0 = B.L[0], L1 = B.L[1], L2 = B.L[2];
@@ -2307,15 +2273,22 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
               if (side < 0) v[k].v[0] = (Vs)((double)v[k].v[0] - B.leu);
               if (side > 0) v[k].v[0] = (Vs)((double)v[k].v[0] + B.leu);
             }
-            if constexpr (A) s_side[qc] = (int8_t)side;
           }
           s_v[0][qc] = v[k].v[0];
           s_v[1][qc] = v[k].v[1];
           s_v[2][qc] = v[k].v[2];
           if constexpr (A) {
-            s_x[0][qc] = Fm::pos(p[k], 0);
-            s_x[1][qc] = Fm::pos(p[k], 1);
-            s_x[2][qc] = Fm::pos(p[k], 2);
+            // under Lees-Edwards shear a particle taken as its image (side
+            // -1 / +1) sits at x - d / x + d
+            double xq = (double)Fm::pos(p[k], 0);
+            if constexpr (E) {
+              const int side = B.le ? Fm::le_side(p[k], st[2], B) : 0;
+              if (side < 0) xq = xq - d1;
+              if (side > 0) xq = xq + d1;
+            }
+            s_x[0][qc] = frame_pos(xq, st[0]);
+            s_x[1][qc] = frame_pos(Fm::pos(p[k], 1), st[1]);
+            s_x[2][qc] = frame_pos(Fm::pos(p[k], 2), st[2]);
           }
           meta[k] = lc | qc << 8;
         }
@@ -2323,7 +2296,83 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       }
       wave_sync();
 
-      // cell sums: two lanes per cell (lanes 2j and 2j + 1 for cell cs + j)
+      // mean velocities (and centres of mass): a lane per cell and half for the
+      // three components, or per component too
+      const uint32_t ncp = ce - cs;
+      const bool phantoms = W && !B.slip && wall_fraction(st[2], z0 - 1, L2) > 0.0;
+      auto means = [&](auto width, uint32_t cell, uint32_t k0, bool valid) {
+        constexpr int N = decltype(width)::value;
+        const uint32_t half = lane & 1u, c = valid ? cell : cs;
+        const uint32_t b = s_off[c] & 0xffffu, n = valid ? (s_off[c + 1] & 0xffffu) - b : 0u;
+        const uint32_t mid = b + (n + 1) / 2, qb = half ? mid : b, qe = half ? b + n : mid;
+        uint32_t nph = 0;
+        double pv[N], V[N];
+        const Vs* vs[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) {
+          pv[k] = 0.0;
+          vs[k] = s_v[k0 + k];
+        }
+        if (W && phantoms && n) {
+          const PhantomSums& ph = d.phs[cur][T.c0 + c];
+          nph = (uint32_t)ph.n;
+#pragma unroll
+          for (int k = 0; k < N; ++k) pv[k] = ph.v[k0 + k];
+        }
+        mean_velocity<F, X, N>(vs, B.mass, qb, qe, half, n + nph, nph, pv, err, V);
+        if (valid && !half) {
+#pragma unroll
+          for (int k = 0; k < N; ++k) {
+            if constexpr (kWide) {
+              s_mean[k0 + k][c] = V[k];
+            } else {
+              s_cell[c].V[k0 + k] = (decltype(s_cell[c].V[0] + 0))V[k];
+            }
+          }
+        }
+        if constexpr (A) {
+          const double* xs[N];
+          double rc[N];
+#pragma unroll
+          for (int k = 0; k < N; ++k) xs[k] = s_x[k0 + k];
+          half_sums<X, false>(xs, 1.0, qb, qe, half, err, rc);
+          if (valid && !half) {
+#pragma unroll
+            for (int k = 0; k < N; ++k) s_cell[c].rc[k0 + k] = rc[k] / (double)(n ? n : 1u);
+          }
+        }
+      };
+      if (6u * ncp <= (uint32_t)NT) {
+        const uint32_t u = lane >> 1;
+        const uint32_t k0 = (u >= ncp ? 1u : 0u) + (u >= 2u * ncp ? 1u : 0u);
+        means(Width<1>{}, cs + u - k0 * ncp, k0, u < 3u * ncp);
+      } else {
+        means(Width<3>{}, cs + (lane >> 1), 0u, (lane >> 1) < ncp);
+      }
+      wave_sync();
+      auto mean_of = [&](uint32_t c, int k) -> double {
+        if constexpr (kWide) {
+          return s_mean[k][c];
+        } else {
+          return (double)s_cell[c].V[k];
+        }
+      };
+      if constexpr (M) {
+        // kinetic-energy terms by the particles' lanes
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          if (q < np) {
+            const uint32_t lc = meta[k] & 0xffu;
+            const double dx = (double)v[k].v[0] - mean_of(lc, 0),
+                         dy = (double)v[k].v[1] - mean_of(lc, 1),
+                         dz = (double)v[k].v[2] - mean_of(lc, 2);
+            s_k[meta[k] >> 8] = B.mass * (dx * dx + dy * dy + dz * dz);
+          }
+        }
+        wave_sync();
+      }
+      // the rest: two lanes per cell (lanes 2j and 2j + 1 for cell cs + j)
       {
         const uint32_t j = lane >> 1;
         const uint32_t c = cs + j;
@@ -2331,12 +2380,10 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
         const uint32_t b = valid ? s_off[c] & 0xffffu : 0u, e = valid ? s_off[c + 1] & 0xffffu : 0u;
         // thermostat: target energy E_k = kT * Gamma(3 (n - 1) / 2), n with
         // phantoms; 0 means "no scaling"
+        const uint32_t nph = W && phantoms && e > b ? (uint32_t)d.phs[cur][T.c0 + c].n : 0u;
         double Ek = 0.0;
         if constexpr (M) {
-          uint32_t n = e - b;
-          if (W && !B.slip && valid && n > 0) {
-            if (wall_fraction(st[2], z0 - 1, L2) > 0.0) n += (uint32_t)d.phs[cur][T.c0 + c].n;
-          }
+          const uint32_t n = e - b + nph;
           const bool draw = e > b && n >= 2u;
           if (draw) {
             double z = z0g;
@@ -2357,11 +2404,17 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
             if (ok) Ek = B.kT * (g.d * (vv * vv * vv));
           }
         }
-        cell_work<F, W, M, A, X>(B, lkey0 + c, st[2], axis, Ek,
-                                 W ? d.phs[cur] + T.c0 + (valid ? c : 0u) : nullptr, s_v[0], s_v[1],
-                                 s_v[2], s_x[0], s_x[A ? 1 : 0], s_x[A ? 2 : 0], st, b, e,
-                                 lane & 1u, valid, &s_cell[valid ? c : 0u], err,
-                                 (E && A) ? s_side : nullptr, d1);
+        auto* rec = &s_cell[valid ? c : cs];
+        const uint32_t cv = valid ? c : cs;
+        const double V[3] = {mean_of(cv, 0), mean_of(cv, 1), mean_of(cv, 2)};
+        double rc[3] = {0.0, 0.0, 0.0};
+        if constexpr (A) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) rc[k] = rec->rc[k];
+        }
+        cell_work<F, W, M, A, X>(B, axis, Ek, W ? d.phs[cur] + T.c0 + (valid ? c : 0u) : nullptr,
+                                 nph, s_v[0], s_v[1], s_v[2], s_x[0], s_x[A ? 1 : 0],
+                                 s_x[A ? 2 : 0], s_k, V, rc, b, e, lane & 1u, valid, rec, err);
       }
       wave_sync();
 
