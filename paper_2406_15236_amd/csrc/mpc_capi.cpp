@@ -406,11 +406,16 @@ void build_tiles(mpc_sim* s) {
   s->dev.maxr = (uint32_t)std::min<uint64_t>(kMaxRuns, s->plan.run_pool / s->tiles.size());
   s->keys_valid = false;  // the run lists belong to a tiling
   s->stepped.assign(s->boxes.size(), 0);
-  // default persistent grid: at most 8 one-wave workgroups per CU in flight
-  // (more waves per XCD evict the gathered rows from L2), oversubscribed 2x
-  // so that freed slots take the remaining workgroups (tail balance)
+  // default grid: about four tiles per wavefront.  Short-lived wavefronts keep
+  // the tiles in flight close together in the list, so that the gathered runs
+  // are still in L2 (collide of 384^3 FP64 16.7 ms with 12288 wavefronts of 230
+  // tiles, 15.0 with 12 tiles each, 14.5 with two to six; 256^3 4.79, 4.50 and
+  // 4.4; split with the thermostat 3.58, 3.46 and 3.50); one tile each leaves
+  // nothing to fetch ahead (256^3 with the thermostat 5.2 against 4.6 ms)
+  const uint32_t full = (uint32_t)(s->num_cu * std::max(1, s->occupancy));
   uint32_t g = s->grid_override ? (uint32_t)s->grid_override
-                                : (uint32_t)(4 * s->num_cu * std::max(1, s->occupancy));
+                                : std::max(4 * full, (s->L.ntiles / 4 + 7) / 8 * 8);
+  s->L.resident = full;
   g = std::max<uint32_t>(1, std::min<uint32_t>(g, s->L.ntiles));
   s->L.collide_grid = g;
 }
@@ -1340,11 +1345,9 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
   double best = 1e300;
   // coordinate search: tile size, then the persistent grid, then the row block
   const int Ts[] = {0, 8, 12, 16, 20, 22, 24, 28, 32};
-  // grids: the resident maximum (0), fixed workgroups per CU (fewer waves
-  // in flight per XCD can keep the gathered rows in L2), and oversubscribed
-  // grids (freed slots take the remaining workgroups: better tail balance)
+  // grids: the default (0) and multiples of the resident workgroups
   const int full = s->num_cu * std::max(1, s->occupancy);
-  const int gs[] = {0, 6 * s->num_cu, 8 * s->num_cu, 10 * s->num_cu, 2 * full, 16 * s->num_cu};
+  const int gs[] = {0, 2 * full, 4 * full, 16 * full, 32 * full, 64 * full};
   const int ys[] = {8, 4, 16};
   for (int T : Ts) {
     double ms;

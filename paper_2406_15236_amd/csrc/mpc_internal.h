@@ -192,7 +192,7 @@ struct Side {          // side work of a collide (see k_collide)
   uint32_t nbox, ctot, wcells;
   int round32;
   uint32_t blocks;     // workgroups that do nothing else
-  uint32_t inloop;     // the draws are made between the tiles
+  uint32_t period;     // every so many groups of 8 workgroups one of them
   uint32_t direct;     // every wavefront sums the tiles before its own
 };
 
@@ -206,6 +206,7 @@ struct Launch {
   uint64_t ntot, ctot;     // particles, cells over all boxes
   uint32_t ntiles, npblocks, nscan;
   uint32_t collide_grid;
+  uint32_t resident;       // collide workgroups that fit the chip at once
   uint32_t wcells;         // walls: cells of the wall-cut layers over all boxes
   int xcd_remap;
   uint32_t seq;            // number of the step in its launch sequence (see Ctrl)

@@ -1970,12 +1970,15 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   const uint32_t tcu = counter_set(d, j), tnx = tcu == 2u ? 0u : tcu + 1u,
                  tcl = tnx == 2u ? 0u : tnx + 1u;
   const int32_t R = as_const(d.ctrl)->reorder;
-  DrawList dl{s_dcell, &s_dused, 0u};
-  if (blockIdx.x < w.blocks) {
-    side_work<W, M>(d, w, blockIdx.x, t + 1, cur ^ 1u, dl);
+  // side work: every w.period-th group of eight workgroups (one per XCD) until
+  // it is done
+  const uint32_t group = blockIdx.x / 8u, turn = group / w.period;
+  if (turn * 8u < w.blocks && group - turn * w.period == w.period - 1u) {
+    DrawList dl{s_dcell, &s_dused, 0u};
+    side_work<W, M>(d, w, turn * 8u + blockIdx.x % 8u, t + 1, cur ^ 1u, dl);
     return;
   }
-  const uint32_t block = blockIdx.x - w.blocks, blocks = gridDim.x - w.blocks;
+  const uint32_t block = blockIdx.x - min(turn * 8u, w.blocks), blocks = gridDim.x - w.blocks;
   // the state is always written into the other buffer; logical indices are
   // renumbered to the canonical (cell, index) order on reorder steps
   const bool renumber = R > 0 && (t + 1) % (uint64_t)R == 0;
@@ -2021,12 +2024,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
     a.run = Run{0u, 0u};
     if (lane < min(a.nrun, maxr)) a.run = d.runs[cur][(size_t)T.tid * maxr + lane];
   };
-
-  // draw blocks of this wavefront, 64 cells after each tile (w.inloop): at
-  // that point it holds no particles, and the arithmetic of the draws runs
-  // beside other wavefronts' memory traffic
-  const uint32_t ndraw = w.inloop ? (w.ctot + d.drawb - 1u) / d.drawb : 0u;
-  uint32_t dblk = block, dk = 0;
 
   uint32_t it = walk.first;
   uint32_t tcur = walk.tile(it);
@@ -2609,14 +2606,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       wave_sync();
     } while (cs < (uint32_t)nc);
     if (slow && lane < maxr) d.rhead[cur][(size_t)T.tid * maxr + lane] = kNoSlot;
-    if (dblk < ndraw) {
-      draw_cells<M>(d, w.nbox, w.ctot, dblk, dk, t + 1, nxt, dl);
-      dk += 64;
-      if (dk >= d.drawb) {
-        dk = 0;
-        dblk += blocks;
-      }
-    }
     // advance the pipeline
     it += walk.stride;
     tcur = tnext;
@@ -2628,10 +2617,6 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       T = Tn;
       cu = ah;
     }
-  }
-  for (; dblk < ndraw; dblk += blocks) {
-    for (; dk < d.drawb; dk += 64) draw_cells<M>(d, w.nbox, w.ctot, dblk, dk, t + 1, nxt, dl);
-    dk = 0;
   }
   if (err) atomicOr(&d.ctrl->err, err);
 }
@@ -2652,13 +2637,16 @@ struct CollideLaunchOp {
   template <int F, bool W, bool M, bool A, bool X, bool E>
   static hipError_t run(const Dev& d, const Launch& l, int*) {
     Side w = side_of(l);
-    const uint32_t parts = (w.nbox + 63u) / 64u + (w.wcells + 63u) / 64u;
-    const uint32_t draws = (w.ctot + d.drawb - 1u) / d.drawb;
-    // between the tiles where there are enough of them: 2.07 against 2.12 ms at
-    // 192^3, but 316 against 311 us at 100^3 (four tiles per wavefront)
-    w.inloop = l.ntiles > 4 * l.collide_grid;
+    const uint32_t side = (w.nbox + 63u) / 64u + (w.wcells + 63u) / 64u +
+                          (w.ctot + d.drawb - 1u) / d.drawb;
     w.direct = d.ntile <= kTileDirect && l.ntiles <= l.collide_grid;
-    w.blocks = (parts + (w.inloop ? 0u : draws) + 7u) / 8u * 8u;
+    w.blocks = (side + 7u) / 8u * 8u;
+    // spread over the launch where there are several times as many collide
+    // workgroups as fit the chip (its arithmetic runs beside their memory
+    // traffic), else first (it takes the longest)
+    w.period = l.collide_grid > 4u * l.resident && l.collide_grid % 8u == 0u
+                   ? std::max(1u, (w.blocks + l.collide_grid) / w.blocks)
+                   : 1u;
     hipLaunchKernelGGL((k_collide<F, W, M, A, X, E>), dim3(w.blocks + l.collide_grid),
                        dim3(kCollideThreads), 0, l.stream, d, w, l.seq, (uint32_t)l.ntiles,
                        l.xcd_remap);
