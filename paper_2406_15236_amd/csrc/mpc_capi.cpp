@@ -70,7 +70,7 @@ struct Plan {
          off_tblk = 0;
   size_t off_key = 0, off_perm = 0, off_hist = 0, off_offset = 0, off_scan = 0, off_ctrl = 0,
          off_boxes = 0, off_tiles = 0, off_pblocks = 0, off_partials = 0, off_vmean = 0,
-         off_draws[2] = {};
+         off_draws[2] = {}, off_obs = 0;
   size_t total = 0;
 };
 
@@ -240,6 +240,7 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   P.off_pblocks = take(sizeof(PBlock) * P.npblocks);
   P.off_partials = take(sizeof(double) * 4 * P.npblocks);
   P.off_vmean = take(sizeof(double) * 3 * nbox);
+  P.off_obs = take(sizeof(double) * 8 * kObsSums);
   // draw blocks of one wavefront each: about 1024 of them if the box is small,
   // so that they run beside each other, else as long as their lists allow
   P.drawb = (uint32_t)std::min<uint64_t>(
@@ -361,46 +362,49 @@ int hip_fail(mpc_sim* s, hipError_t e, const char* where) {
 // flight together.
 void build_tiles(mpc_sim* s) {
   s->tiles.clear();
-  struct Keyed {
-    uint64_t k;
-    Tile t;
-  };
-  std::vector<Keyed> keyed;
-  const int yb = std::max(1, s->yblock);
+  const uint64_t yb = (uint64_t)std::max(1, s->yblock);
+  uint32_t tbase = 0;
   for (size_t b = 0; b < s->boxes.size(); ++b) {
     BoxDev& B = s->boxes[b];
-    const int T = s->tile_override ? s->tile_override : auto_tile_cells(B.density, B.L[0], s->plan.rows);
+    const int T = s->tile_override ? s->tile_override
+                                   : auto_tile_cells(B.density, B.L[0], s->plan.rows);
     B.T = (uint32_t)T;
     B.ntx = (uint32_t)((B.L[0] + T - 1) / T);
-    B.tbase = (uint32_t)keyed.size();
-    const uint64_t L0 = (uint64_t)B.L[0], L1 = (uint64_t)B.L[1];
-    for (uint64_t cz = 0; cz < (uint64_t)B.nlz; ++cz) {
-      for (uint64_t cy = 0; cy < L1; ++cy) {
-        for (uint64_t cx = 0; cx < L0; cx += T) {
-          Tile t;
-          t.c0 = B.cbase + (uint32_t)((cz * L1 + cy) * L0 + cx);
-          t.tid = (uint32_t)keyed.size();
-          t.nc = (uint16_t)std::min<uint64_t>(T, L0 - cx);
-          t.box = (uint16_t)b;
-          t.x0 = (uint32_t)cx;
-          t.y0 = (uint32_t)cy;
-          t.z0 = (uint32_t)cz;
-          const uint64_t slab = cz * 8 / (uint64_t)B.nlz;
-          const uint64_t head = ((uint64_t)b * 8 + slab) << 12 | (cy / yb);
-          // order 0: the rows of a block one after the other; order 1: the
-          // same x segment of every row of the block, then the next segment
-          // (the rows that exchange particles are in flight together)
-          const uint64_t k =
-              s->order == 0 ? (((head << 11 | cz) << 11 | cy) << 12) | (cx & 0xfff)
-                            : (((head << 12 | (cx / (uint64_t)T)) << 11 | cz) << 11) | cy;
-          keyed.push_back({k, t});
-        }
+    B.tbase = tbase;
+    const uint64_t L0 = (uint64_t)B.L[0], L1 = (uint64_t)B.L[1], nz = (uint64_t)B.nlz;
+    const uint64_t ntx = B.ntx;
+    tbase += (uint32_t)(nz * L1 * ntx);
+    s->tiles.reserve(tbase);
+    auto add = [&](uint64_t cz, uint64_t cy, uint64_t tx) {
+      const uint64_t row = cz * L1 + cy, cx = tx * (uint64_t)T;
+      Tile t;
+      t.c0 = B.cbase + (uint32_t)(row * L0 + cx);
+      t.tid = B.tbase + (uint32_t)(row * ntx + tx);
+      t.nc = (uint16_t)std::min<uint64_t>((uint64_t)T, L0 - cx);
+      t.box = (uint16_t)b;
+      t.x0 = (uint32_t)cx;
+      t.y0 = (uint32_t)cy;
+      t.z0 = (uint32_t)cz;
+      s->tiles.push_back(t);
+    };
+    for (uint64_t slab = 0; slab < 8; ++slab) {
+      const uint64_t z0 = (slab * nz + 7) / 8, z1 = ((slab + 1) * nz + 7) / 8;  // cz * 8 / nz == slab
+      for (uint64_t y0 = 0; y0 < L1; y0 += yb) {
+        const uint64_t y1 = std::min(L1, y0 + yb);
+        // order 0: the rows of a block one after the other; order 1: the same
+        // x segment of every row of the block, then the next segment
+        for (uint64_t seg = 0; seg < (s->order == 0 ? 1 : ntx); ++seg)
+          for (uint64_t cz = z0; cz < z1; ++cz)
+            for (uint64_t cy = y0; cy < y1; ++cy) {
+              if (s->order == 0) {
+                for (uint64_t tx = 0; tx < ntx; ++tx) add(cz, cy, tx);
+              } else {
+                add(cz, cy, seg);
+              }
+            }
       }
     }
   }
-  std::stable_sort(keyed.begin(), keyed.end(),
-                   [](const Keyed& a, const Keyed& b) { return a.k < b.k; });
-  for (const Keyed& kt : keyed) s->tiles.push_back(kt.t);
   s->L.ntiles = (uint32_t)s->tiles.size();
   s->dev.ntile = s->L.ntiles;
   s->dev.maxr = (uint32_t)std::min<uint64_t>(kMaxRuns, s->plan.run_pool / s->tiles.size());
@@ -636,11 +640,30 @@ uint32_t obs_tile_cells(double density) {
   return (uint32_t)std::max<double>(kMinTileCells, std::min<double>(kTileMaxCells, floor(target)));
 }
 
+// Sums of the first nv of the four partial sums of particle blocks [pb0, pb0 +
+// npb), compensated.  Of many blocks the device first makes kObsSums sums of
+// twice the precision each (copied and added here, the 553 000 blocks of a
+// 384^3 box had taken 4 ms per pass).
+int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, int nv, Neumaier* a) {
+  const bool many = npb > 1024;
+  const size_t rows = many ? kObsSums : npb, width = many ? 8 : 4;
+  std::vector<double> part(rows * width);
+  if (many) HIPCHK(s, launch_obs_sums(s->dev, s->L, pb0, npb));
+  HIPCHK(s, hipMemcpyAsync(part.data(), many ? s->dev.obs : s->dev.partials + 4 * (size_t)pb0,
+                           sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
+  HIPCHK(s, hipStreamSynchronize(s->L.stream));
+  for (size_t q = 0; q < rows; ++q)
+    for (int k = 0; k < nv; ++k) {
+      a[k].add(part[q * width + k]);
+      if (many) a[k].add(part[q * width + 4 + k]);
+    }
+  return MPC_OK;
+}
+
 // Momentum P[3], kinetic energy E and relative kinetic energy K of one box.
 int obs_box(mpc_sim* s, int32_t box, double* P, double* E, double* K) {
   const BoxDev& B = s->boxes[box];
   const uint32_t pb0 = s->box_pb0[box], npb = s->box_pb0[box + 1] - pb0;
-  std::vector<double> part(4 * (size_t)npb);
   uint32_t* order = nullptr;
   if (s->form == MPC_FP64 && s->stepped[box]) {
     // the chains of the buffer that the next step writes are free until then
@@ -650,12 +673,9 @@ int obs_box(mpc_sim* s, int32_t box, double* P, double* E, double* K) {
                                (uint32_t)B.L[0], s->cur, obs_tile_cells(B.density), order));
   }
   HIPCHK(s, launch_obs_pass1(s->dev, s->L, pb0, npb, s->cur, order));
-  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials + 4 * (size_t)pb0,
-                           sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
-  HIPCHK(s, hipStreamSynchronize(s->L.stream));
   Neumaier a[4];
-  for (uint32_t q = 0; q < npb; ++q)
-    for (int k = 0; k < 4; ++k) a[k].add(part[4 * (size_t)q + k]);
+  int rc = sum_partials(s, pb0, npb, 4, a);
+  if (rc) return rc;
   const double M = (double)B.np * B.mass;
   double vm[3];
   for (int k = 0; k < 3; ++k) {
@@ -666,12 +686,9 @@ int obs_box(mpc_sim* s, int32_t box, double* P, double* E, double* K) {
   HIPCHK(s, hipMemcpyAsync(s->vmean + 3 * (size_t)box, vm, sizeof vm, hipMemcpyHostToDevice,
                            s->L.stream));
   HIPCHK(s, launch_obs_pass2(s->dev, s->L, pb0, npb, s->cur, s->vmean));
-  HIPCHK(s, hipMemcpyAsync(part.data(), s->dev.partials + 4 * (size_t)pb0,
-                           sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
-  HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  Neumaier k2;
-  for (uint32_t q = 0; q < npb; ++q) k2.add(part[4 * (size_t)q]);
-  *K = k2.val();
+  Neumaier k2[1];
+  if ((rc = sum_partials(s, pb0, npb, 1, k2))) return rc;
+  *K = k2[0].val();
   return MPC_OK;
 }
 
@@ -747,6 +764,7 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
   s->dev.tiles = (Tile*)(ws + P.off_tiles);
   s->dev.pblocks = (PBlock*)(ws + P.off_pblocks);
   s->dev.partials = (double*)(ws + P.off_partials);
+  s->dev.obs = (double*)(ws + P.off_obs);
   s->dev.ntot = (uint32_t)P.ntot;
   s->vmean = (double*)(ws + P.off_vmean);
   s->dev.drawb = P.drawb;

@@ -11,6 +11,7 @@ constexpr int kCollideThreads = 64;         // collide workgroup: one wave64
 constexpr int kTileCap = 256;               // particles held in LDS per tile pass
 constexpr int kTileMaxCells = 32;           // cells per collide tile (< kCollideThreads)
 constexpr int kObsPass = 256;               // particles per pass of the observables' order
+constexpr int kObsSums = 128;               // sums left of the observables' partial sums
 constexpr int kObsList = 320;               // particles of an obs tile listed in LDS
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
@@ -178,6 +179,7 @@ struct Dev {           // device pointers carved from the workspace
   Tile* tiles;
   PBlock* pblocks;
   double* partials;    // per-block observable partial sums
+  double* obs;         // kObsSums rows of their sums: high parts [4], low parts [4]
   double4* draws[2];      // per cell: rotation axis, z of attempt 0 of the gamma draw
   // thermostat: per cell, the least count that accepts attempt 0 and the first
   // of its later attempts << 16 in the block's segment of later_seg(drawb) attempts
@@ -232,6 +234,7 @@ hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_
                             const uint32_t* order);
 hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
                             const double* vmean_dev);
+hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
 // sel: box-local logical indices, overwritten; keys: 2 (mask + 1) entries of a
 // hash table, or null and inv: np entries; out: [6][m] FP64

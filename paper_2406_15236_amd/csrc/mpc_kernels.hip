@@ -3343,6 +3343,43 @@ __global__ __launch_bounds__(kThreads) void k_obs_pass2(Dev d, uint32_t pb0, uin
   if (threadIdx.x == 0) d.partials[(uint64_t)blk * 4] = r;
 }
 
+// Sums of many blocks' partials: each thread adds a stride of them and the
+// block its threads, as pairs (high, low) with the rounding error of every
+// addition kept (Knuth's two-sum), about 106 bits.
+struct Pair {
+  double hi, lo;
+};
+__device__ __forceinline__ Pair pair_add(Pair a, double x, double xlo) {
+  const double t = a.hi + x, z = t - a.hi;
+  const double e = (a.hi - (t - z)) + (x - z);
+  const double lo = a.lo + (e + xlo);
+  const double hi = t + lo;
+  return Pair{hi, lo - (hi - t)};
+}
+__global__ __launch_bounds__(kThreads) void k_obs_sums(Dev d, uint32_t pb0, uint32_t npb) {
+  __shared__ Pair s_p[kThreads];
+  const uint32_t per = (npb + kObsSums - 1) / kObsSums;
+  const uint32_t q0 = blockIdx.x * per, q1 = min(npb, q0 + per);
+  for (int k = 0; k < 4; ++k) {
+    Pair a{0.0, 0.0};
+    for (uint32_t q = q0 + threadIdx.x; q < q1; q += kThreads)
+      a = pair_add(a, d.partials[4 * (size_t)(pb0 + q) + k], 0.0);
+    s_p[threadIdx.x] = a;
+    __syncthreads();
+    for (int w = kThreads / 2; w > 0; w >>= 1) {
+      if ((int)threadIdx.x < w)
+        s_p[threadIdx.x] =
+            pair_add(s_p[threadIdx.x], s_p[threadIdx.x + w].hi, s_p[threadIdx.x + w].lo);
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+      d.obs[8 * blockIdx.x + k] = s_p[0].hi;
+      d.obs[8 * blockIdx.x + 4 + k] = s_p[0].lo;
+    }
+    __syncthreads();
+  }
+}
+
 template <int F>
 __global__ __launch_bounds__(kThreads) void k_remove_mean(Dev d, const double* vmean) {
   const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
@@ -3606,6 +3643,11 @@ hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_
   if (npb == 0) return hipSuccess;
   MPC_FORM_DISPATCH(l.form, k_obs_pass2, dim3(npb), dim3(kThreads), 0, l.stream, d, pb0, cur,
                     vmean);
+  return hipGetLastError();
+}
+
+hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb) {
+  hipLaunchKernelGGL(k_obs_sums, dim3(kObsSums), dim3(kThreads), 0, l.stream, d, pb0, npb);
   return hipGetLastError();
 }
 
