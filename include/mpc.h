@@ -158,10 +158,12 @@ typedef struct {
 
 /* Per-kernel device time accumulated by mpc_step_profiled (milliseconds,
  * from HIP events recorded on the handle's stream around each launch):
- * scan = prefix sum of the cell counts, per-cell random draws and (walls)
- * phantom sums; scatter = the sort permutation; collide = the collision,
- * the next step's streaming and binning and the state write; prologue = the
- * binning of a state set from outside; other = the step-counter advance. */
+ * scan = output positions of the tiles (prefix of their particle counts; part
+ * of the collide for few tiles); collide = the collision, the next step's
+ * streaming and binning, the state write, and the random draws and (walls)
+ * phantom sums of the next step, with the step-counter advance after the last
+ * step; prologue = the sort of a state set from outside; scatter and other
+ * stay 0 (no such launches). */
 typedef struct {
   double scan_ms, scatter_ms, collide_ms, prologue_ms, other_ms;
   uint64_t scan_launches, scatter_launches, collide_launches, prologue_launches;
@@ -170,8 +172,9 @@ typedef struct {
 typedef struct mpc_sim mpc_sim;
 
 /* Bytes of device workspace needed for nbox boxes with parameters p[0..nbox).
- * The workspace holds the double-buffered particle state, keys, permutation,
- * cell histogram and offsets, and small tables.  Errors: MPC_EINVAL,
+ * The workspace holds the double-buffered particle state, the run lists of the
+ * tiles (or, in their place, keys, permutation, cell counts and offsets for
+ * mpc_get_binning), the cells' draws and small tables.  Errors: MPC_EINVAL,
  * MPC_ERANGE. */
 int mpc_workspace_bytes(const mpc_params* p, int32_t nbox, size_t* bytes);
 
@@ -197,10 +200,10 @@ int mpc_step(mpc_sim* s, int64_t nsteps);
  * synchronising the stream. */
 int mpc_step_profiled(mpc_sim* s, int64_t nsteps, mpc_kernel_times* acc);
 
-/* Captured hipGraphs for mpc_step: 0 = launch kernel by kernel; 1 = replay
- * a graph of one step per step (the default); K in 2..1000 = also capture K
- * consecutive steps in one graph, so that mpc_step(n) is floor(n / K)
- * launches of that graph plus one-step replays for the rest.  Results do
+/* Captured hipGraphs for mpc_step: 0 = launch kernel by kernel; K in 2..1000
+ * = capture K consecutive steps in one graph, so that mpc_step(n) is
+ * floor(n / K) launches of that graph and single launches for the rest; 1 =
+ * the same with 16 steps per graph (the default).  Results do
  * not depend on this choice.  A new K drops the captured graphs (they are
  * captured again at the next mpc_step; synchronises).  Errors: MPC_EINVAL
  * (enable outside 0..1000), MPC_EHIP. */
@@ -254,7 +257,9 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
  *   key[n]:  cell key of each particle, indexed by that same order.
  * Keys are x-fastest: ((c_z' * L1) + c_y) * L0 + c_x with c_z' = c_z (periodic)
  * or c_z + 1 (walls).  Any pointer may be NULL.  MPC_EINVAL if no step has
- * run since the state was set. */
+ * run since the state was set.  The binning is formed from the last step's
+ * input on the first call after a step; the next step then sorts the particles
+ * by tile again (results do not change). */
 int mpc_get_binning(mpc_sim* s, int32_t box, uint32_t* key, uint32_t* perm, uint32_t* offset);
 
 /* Autotuner: choose the collide tiling (cells per tile, persistent grid size,
@@ -297,11 +302,11 @@ int mpc_destroy(mpc_sim* s);
  * mpc_get_state would.  x[3][n], v[3][n]: caller-owned device arrays, FP64
  * SoA in physical units as in mpc_set_state; on return they hold the state
  * after the steps in the same particle order.  All working memory (both
- * state buffers, keys, permutation, cell counts, offsets, draws, tables) is
- * a static device array of 256 MiB inside the library, one per device, held
- * until the process ends; no device memory is allocated.  Boxes whose
- * workspace (mpc_workspace_bytes) exceeds 256 MiB -> MPC_ERANGE (about 2e6
- * particles at 10 per cell).  Every call on a device shares that device's
+ * state buffers, run lists, draws, tables) is a static device array of 896 MiB
+ * inside the library, one per device, held until the process ends; no device
+ * memory is allocated.  Boxes of more than 256 MiB, counted as 114 B per
+ * particle, 45 B per cell (93 B with walls) and tables -> MPC_ERANGE (about
+ * 2e6 particles at 10 per cell).  Every call on a device shares that device's
  * array: calls that overlap on one device (other threads, or a stream not
  * drained) race.  Launches kernel by kernel on hip_stream (NULL = default
  * stream) and synchronises it.  Errors: MPC_EINVAL (bad parameters, n not

@@ -258,8 +258,8 @@ class Sim:
         return acc
 
     def set_graph(self, enable):
-        """False/0: kernel by kernel; True/1: one-step graph; K > 1: also a
-        graph of K consecutive steps."""
+        """False/0: kernel by kernel; True/1: graphs of 16 steps; K > 1: graphs
+        of K consecutive steps."""
         self._c(lib().mpc_set_graph(self.h, int(enable)))
 
     def sync(self):
