@@ -69,7 +69,7 @@ struct BoxDev {
   uint32_t pad1;
 };
 
-struct BoxStep {       // per box and step, written by the prepare kernel
+struct BoxStep {       // per box and step, made a step ahead by the side work
   double s[3], sn[3];  // lattice shifts of t and t + 1
   double d1, d2;       // Lees-Edwards offsets at the end of step t and t + 1
   int32_t w[2];        // first row (y, z) of the window of next-step rows

@@ -65,8 +65,8 @@ __device__ __forceinline__ PBlock load_pblock(const PBlock* p, uint32_t i) {
 // ---------------------------------------------------------------------------
 // Angles here are at most 2 pi.  Told so, the compiler drops the reduction of
 // huge arguments from sin and cos (the limit is that of their short branch),
-// which would set the register count of the prepare kernel (109 instead of 81
-// VGPRs) and of the collide with the thermostat.
+// which set the register count of the collide with the thermostat and of the
+// draws (109 instead of 81 VGPRs in a kernel of their own).
 constexpr double kSmallAngle = 0x1p30;
 
 __device__ __forceinline__ Words4 draw(BoxRef B, uint32_t j, uint32_t id, uint64_t t,
@@ -1928,7 +1928,12 @@ __device__ __forceinline__ void for_each_source(const Dev& d, uint32_t in, uint3
 // the ids of each cell for the canonical order, the velocities in that order
 // for the cell sums, the cells' records.  That is 10 KB in FP64 (it was
 // 18.8 KB with the positions and the binning of single cells in LDS), so
-// registers decide the waves per SIMD.
+// registers decide the waves per SIMD.  What bounds it is the chain of one
+// pass (runs, gather, ids, sums, rotation, atomics, stores; the wavefronts wait
+// half of the time) against HBM traffic at 0.8 of the copy rate.  At 256^3
+// cells of 10 particles a step takes 4.4 ms (FP64), 4.6 (thermostat), 3.4
+// (split, thermostat) and 7.0 (SRD+a, thermostat), where a collide of sorted
+// slots with a scan and a scatter beside it took 6.9, 7.3, 6.5 and 8.8.
 template <int F, bool W, bool M, bool A, bool X, bool E>
 __global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu(A ? 2 : (F == kFormF64 ? 3 : 4), F == kFormF64 ? 3 : 8)))
 void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
@@ -3084,8 +3089,8 @@ __global__ __launch_bounds__(kThreads) void k_init_state(Dev d, uint32_t k0, uin
 }
 
 // ---------------------------------------------------------------------------
-// Observables: per-block partial sums (FP64), reduced on the host side of the
-// call in block order.  pass 1: P (3), E; pass 2: sum m |v - vmean|^2.
+// Observables: per-block partial sums (FP64), of many blocks summed further by
+// k_obs_sums, the rest in order on the host.  pass 1: P (3), E; pass 2: sum m |v - vmean|^2.
 // ---------------------------------------------------------------------------
 template <int F>
 __device__ __forceinline__ void load_vel_d(const StatePtrs& S, uint32_t i, double (&v)[3]) {
