@@ -1702,7 +1702,15 @@ __device__ __forceinline__ void cell_work(BoxRef B, const double (&axis)[3], dou
   const uint32_t ntot = nf + nph;
   const double m = B.mass;
   double kappa = 1.0, K = 0.0;
-  if (M) {
+  // kinetic-energy terms: SRD+a adds them here, next to its moments
+  auto term = [&](double u0, double u1, double u2) { return m * (u0 * u0 + u1 * u1 + u2 * u2); };
+  if constexpr (M && A && X) {
+    FixSum f = {};
+    for (uint32_t q = qb; q < qe; ++q)
+      fix_add(f, term((double)sv0[q] - V[0], (double)sv1[q] - V[1], (double)sv2[q] - V[2]), err);
+    K = fix_value(fix_pair(f));
+  }
+  if constexpr (M && !A) {
     const double* const ks[1] = {sk};
     double Ks[1];
     half_sums<X, false>(ks, 1.0, qb, qe, half, err, Ks);
@@ -1773,6 +1781,7 @@ __device__ __forceinline__ void cell_work(BoxRef B, const double (&axis)[3], dou
     for (uint32_t q = qb; q < qe; ++q) {
       const double r[3] = {sx0[q] - rc[0], sx1[q] - rc[1], sx2[q] - rc[2]};
       const double u[3] = {(double)sv0[q] - V[0], (double)sv1[q] - V[1], (double)sv2[q] - V[2]};
+      if (M) K = K + term(u[0], u[1], u[2]);
 #pragma unroll
       for (int a = 0; a < 3; ++a)
 #pragma unroll
@@ -1793,6 +1802,10 @@ __device__ __forceinline__ void cell_work(BoxRef B, const double (&axis)[3], dou
     for (int k = 0; k < 6; ++k) {
       const double o = pair_xor(ss[k]);
       ss[k] = half ? o + ss[k] : ss[k] + o;
+    }
+    if (M) {
+      const double o = pair_xor(K);
+      K = half ? o + K : K + o;
     }
     }
     const double xx = ss[1] + ss[2], yy = ss[0] + ss[2], zz = ss[0] + ss[1];
@@ -1834,7 +1847,6 @@ __device__ __forceinline__ void cell_work(BoxRef B, const double (&axis)[3], dou
       // the thermostat scales the corrected relative velocities D u_i +
       // omega x r_ic to the drawn energy; their kinetic energy is
       // K + m (2 omega . L_D + omega . I omega), K that of the u_i
-      kappa = 1.0;
       if (Ek > 0.0) {
         const double Io[3] = {xx * om[0] + xy * om[1] + xz * om[2],
                               xy * om[0] + yy * om[1] + yz * om[2],
@@ -1932,10 +1944,15 @@ __device__ __forceinline__ void for_each_source(const Dev& d, uint32_t in, uint3
 // pass (runs, gather, ids, sums, rotation, atomics, stores; the wavefronts wait
 // half of the time) against HBM traffic at 0.8 of the copy rate.  At 256^3
 // cells of 10 particles a step takes 4.4 ms (FP64), 4.6 (thermostat), 3.4
-// (split, thermostat) and 7.0 (SRD+a, thermostat), where a collide of sorted
+// (split, thermostat) and 6.2 (SRD+a, thermostat), where a collide of sorted
 // slots with a scan and a scatter beside it took 6.9, 7.3, 6.5 and 8.8.
+// SRD+a is bound by LDS: what shares its place there (ids and positions, the
+// energy terms added along with the moments) took it from 20.4 to 16.3 KB, ten
+// wavefronts per CU instead of eight, and from 7.06 to 6.20 ms (split 17.3 to
+// 13.2 KB, 6.02 to 5.22).  With fixed-point sums it needs the registers of two
+// wavefronts per SIMD (105 spills at three).
 template <int F, bool W, bool M, bool A, bool X, bool E>
-__global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu(A ? 2 : (F == kFormF64 ? 3 : 4), F == kFormF64 ? 3 : 8)))
+__global__ __launch_bounds__(kCollideThreads) __attribute__((amdgpu_waves_per_eu(A && X ? 2 : (A || F == kFormF64 ? 3 : 4), F == kFormF64 ? 3 : 8)))
 void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   using Fm = Form<F>;
   using Vs = typename Fm::Vs;
@@ -1948,26 +1965,31 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   // id segments, each padded to a multiple of four (read four at a time);
   // before the ids: run marks and source slots; after them: far tiles
   constexpr int kIds = kTileCap + 4 * kTileMaxCells;
-  __shared__ __align__(16) uint32_t s_id[kIds];
+  // (SRD+a: in the place of the positions, which come after the ids and go
+  // before the far tiles)
+  __shared__ __align__(16) uint32_t s_ids[A ? 4 : kIds];
   __shared__ uint32_t s_cnt[kTileMaxCells];
   __shared__ uint32_t s_off[kTileMaxCells + 1];  // offsets: plain | padded << 16
   __shared__ uint32_t s_delta[kMaxRuns];
   __shared__ uint32_t s_grp[kGroups + 1];
   __shared__ uint32_t s_tot[kTileMaxCells + 1];  // offsets of the whole tile (several passes)
   __shared__ __align__(16) Vs s_v[3][kTileCap];  // streamed velocities, canonical order
-  __shared__ double s_x[A ? 3 : 1][A ? kTileCap : 1];  // SRD+a: cell-frame positions, alike
-  // kinetic-energy terms: in the place of the velocities, which only the
-  // moments of SRD+a read after the momentum
-  __shared__ double s_kin[A && M ? kTileCap : 1];
+  // SRD+a: cell-frame positions, alike
+  __shared__ __align__(16) double s_x[A ? 3 : 1][A ? kTileCap : 1];
+  static_assert(sizeof(double) * 3 * kTileCap >= sizeof(uint32_t) * kIds, "ids fit");
+  uint32_t* const s_id = A ? (uint32_t*)&s_x[0][0] : s_ids;
+  // kinetic-energy terms: in the place of the velocities (SRD+a, which reads
+  // them after the momentum, adds the terms along with its moments)
   static_assert(sizeof(Vs) * 3 * kTileCap >= sizeof(double) * kTileCap, "terms fit");
-  double* const s_k = A ? s_kin : (double*)&s_v[0][0];
+  double* const s_k = (double*)&s_v[0][0];
   // mean velocities in FP64 where the cell's record has FP32 but the sums were
   // not FP32 ones
   constexpr bool kWide = F == kFormSplit && X;
   __shared__ double s_mean[kWide ? 3 : 1][kWide ? kTileMaxCells : 1];
   __shared__ typename CellRec<F, A>::T s_cell[kTileMaxCells];
 
-  __shared__ uint16_t s_dcell[kDrawList];
+  // side work: the cells still to draw, in the place of the velocities
+  static_assert(sizeof(Vs) * 3 * kTileCap >= sizeof(uint16_t) * kDrawList, "list fits");
   __shared__ uint32_t s_dused;
 
   const uint64_t t = as_const(d.ctrl)->step + j;
@@ -1979,7 +2001,7 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
   // it is done
   const uint32_t group = blockIdx.x / 8u, turn = group / w.period;
   if (turn * 8u < w.blocks && group - turn * w.period == w.period - 1u) {
-    DrawList dl{s_dcell, &s_dused, 0u};
+    DrawList dl{(uint16_t*)&s_v[0][0], &s_dused, 0u};
     side_work<W, M>(d, w, turn * 8u + blockIdx.x % 8u, t + 1, cur ^ 1u, dl);
     return;
   }
@@ -2279,7 +2301,17 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
           s_v[0][qc] = v[k].v[0];
           s_v[1][qc] = v[k].v[1];
           s_v[2][qc] = v[k].v[2];
-          if constexpr (A) {
+          meta[k] = lc | qc << 8;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wave_sync();
+      if constexpr (A) {
+        // after every lane's last look at the ids
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t qc = meta[k] >> 8;
+          if (lane + k * NT < np) {
             // under Lees-Edwards shear a particle taken as its image (side
             // -1 / +1) sits at x - d / x + d
             double xq = (double)Fm::pos(p[k], 0);
@@ -2292,11 +2324,9 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
             s_x[1][qc] = frame_pos(Fm::pos(p[k], 1), st[1]);
             s_x[2][qc] = frame_pos(Fm::pos(p[k], 2), st[2]);
           }
-          meta[k] = lc | qc << 8;
         }
-        __builtin_amdgcn_sched_barrier(0);
+        wave_sync();
       }
-      wave_sync();
 
       // mean velocities (and centres of mass): a lane per cell and half for the
       // three components, or per component too
@@ -2359,7 +2389,7 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
           return (double)s_cell[c].V[k];
         }
       };
-      if constexpr (M) {
+      if constexpr (M && !A) {
         // kinetic-energy terms by the particles' lanes
 #pragma unroll
         for (int k = 0; k < NS; ++k) {
