@@ -13,6 +13,7 @@
 
 #include "mpc.h"
 #include "mpc_internal.h"
+#include "sample_table.h"
 
 using namespace mpc;
 
@@ -1150,12 +1151,7 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
   const StatePtrs& S = s->dev.S[s->cur];
   // one allocation: the sample's states, indices, and the table that finds
   // their slots (see k_sample_find)
-  uint32_t mask = 0;
-  if ((uint64_t)m * 16 <= B.np) {
-    mask = 1024;
-    while (mask < 8 * (uint64_t)m) mask *= 2;
-    mask -= 1;
-  }
+  const uint32_t mask = sample_table_mask((uint64_t)m, B.np);
   const size_t o_sel = align256(sizeof(double) * 6 * (size_t)m);
   const size_t o_tab = o_sel + align256(sizeof(uint32_t) * (size_t)m);
   const size_t n_tab = mask ? 2 * ((size_t)mask + 1) : (size_t)B.np;

@@ -27,6 +27,7 @@
 
 #include "mpc_internal.h"
 #include "philox_dev.h"
+#include "sample_table.h"
 
 namespace mpc {
 
@@ -2765,14 +2766,12 @@ __global__ void k_canon_perm(uint32_t* __restrict__ perm, const uint32_t* __rest
 // Sampled state: the stored slots of selected logical particles, then a gather
 // of their records as FP64 in cell units (the split form's cell + offset is
 // exact in FP64).  A logical index with no stored slot yields NaN.  A sample
-// of at most a sixteenth of the box goes into a hash table of eight entries
-// per particle, and every slot looks its index up there; a larger one uses the
+// of at most 1/32 of the box goes into a hash table of 8 to 16 entries per
+// particle, and every slot looks its index up there; a larger one uses the
 // inverse of the whole index array, four bytes written at random per particle
-// of the box (24 ms at 384^3, where the table of 32768 takes 1 ms).
+// of the box (24 ms at 384^3, where the table of 32768 takes 1 ms), because
+// the table would take more memory than that.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t sample_hash(uint32_t key, uint32_t mask) {
-  return ((key * 0x9E3779B1u) >> 7) & mask;
-}
 // keys: mask + 1 entries, kNoSlot = free
 __global__ __launch_bounds__(kThreads) void k_sample_insert(const uint32_t* __restrict__ lidx,
                                                             uint32_t m, uint32_t* keys,
