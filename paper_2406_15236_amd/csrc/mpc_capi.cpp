@@ -241,7 +241,9 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   P.off_pblocks = take(sizeof(PBlock) * P.npblocks);
   P.off_partials = take(sizeof(double) * 4 * P.npblocks);
   P.off_vmean = take(sizeof(double) * 3 * nbox);
-  P.off_obs = take(sizeof(double) * 8 * kObsSums);
+  P.off_obs = take(std::max<size_t>(sizeof(double) * 8 * kObsSums,
+                                    4 * sizeof(ObsTotal) + sizeof(ObsRow<4>) *
+                                        std::min<uint64_t>(kObsRows, P.npblocks)));
   // draw blocks of one wavefront each: about 1024 of them if the box is small,
   // so that they run beside each other, else as long as their lists allow
   P.drawb = (uint32_t)std::min<uint64_t>(
@@ -304,6 +306,10 @@ struct Neumaier {
 
 }  // namespace
 
+// Order of the slots of a box: the caller's; the output of a step of this
+// tiling; neither (runs to be appended in any order, tiles of another tiling).
+enum : char { kSlotsCaller, kSlotsStep, kSlotsOther };
+
 struct mpc_sim {
   std::vector<mpc_params> params;
   Plan plan;
@@ -320,7 +326,7 @@ struct mpc_sim {
   bool keys_valid = false;
   bool have_binning = false;
   bool binning_ready = false;  // the binning export holds the last step's binning
-  std::vector<char> stepped;   // per box: its slots are the output of a step of this tiling
+  std::vector<char> slots;     // per box: what its slots' order is (kSlots*)
   bool use_graph = true;
   int32_t graph_steps = 1;         // steps per replay of the chunk graph
   bool graph_ready = false;
@@ -409,8 +415,10 @@ void build_tiles(mpc_sim* s) {
   s->L.ntiles = (uint32_t)s->tiles.size();
   s->dev.ntile = s->L.ntiles;
   s->dev.maxr = (uint32_t)std::min<uint64_t>(kMaxRuns, s->plan.run_pool / s->tiles.size());
-  s->keys_valid = false;  // the run lists belong to a tiling
-  s->stepped.assign(s->boxes.size(), 0);
+  s->keys_valid = false;  // the run lists belong to a tiling, and so do the steps' outputs
+  s->slots.resize(s->boxes.size(), kSlotsCaller);
+  for (char& o : s->slots)
+    if (o == kSlotsStep) o = kSlotsOther;
   // default grid: about four tiles per wavefront.  Short-lived wavefronts keep
   // the tiles in flight close together in the list, so that the gathered runs
   // are still in L2 (collide of 384^3 FP64 16.7 ms with 12288 wavefronts of 230
@@ -483,6 +491,7 @@ int ensure_keys(mpc_sim* s) {
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   HIPCHK(s, launch_sort(s->dev, s->L, s->cur, s->cur ^ 1u));
   s->cur ^= 1u;
+  s->slots.assign(s->boxes.size(), kSlotsOther);
   HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   s->keys_valid = true;
   s->binning_ready = false;
@@ -641,11 +650,11 @@ uint32_t obs_tile_cells(double density) {
   return (uint32_t)std::max<double>(kMinTileCells, std::min<double>(kTileMaxCells, floor(target)));
 }
 
-// Sums of the first nv of the four partial sums of particle blocks [pb0, pb0 +
+// Momentum and energy from the partial sums of particle blocks [pb0, pb0 +
 // npb), compensated.  Of many blocks the device first makes kObsSums sums of
 // twice the precision each (copied and added here, the 553 000 blocks of a
 // 384^3 box had taken 4 ms per pass).
-int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, int nv, Neumaier* a) {
+int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, double (&sum)[4]) {
   const bool many = npb > 1024;
   const size_t rows = many ? kObsSums : npb, width = many ? 8 : 4;
   std::vector<double> part(rows * width);
@@ -653,11 +662,54 @@ int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, int nv, Neumaier* a) {
   HIPCHK(s, hipMemcpyAsync(part.data(), many ? s->dev.obs : s->dev.partials + 4 * (size_t)pb0,
                            sizeof(double) * part.size(), hipMemcpyDeviceToHost, s->L.stream));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  for (size_t q = 0; q < rows; ++q)
-    for (int k = 0; k < nv; ++k) {
-      a[k].add(part[q * width + k]);
-      if (many) a[k].add(part[q * width + 4 + k]);
+  for (int k = 0; k < 4; ++k) {
+    Neumaier a;
+    for (size_t q = 0; q < rows; ++q) {
+      a.add(part[q * width + k]);
+      if (many) a.add(part[q * width + 4 + k]);
     }
+    sum[k] = a.val();
+  }
+  return MPC_OK;
+}
+
+// A sum's digits, rounded once.
+double exact_value(const ObsTotal& t) {
+  if (t.anchor < 0) return 0.0;
+  if (t.anchor >= kObsBad) return NAN;
+  __int128 d[3];
+  for (int j = 0; j < 3; ++j) d[j] = (__int128)t.hi[j] << 64 | t.lo[j];
+  // carries: d[2] 2^80 + low, 0 <= low < 2^80, in units of 2^(40 anchor - 1103)
+  constexpr __int128 kMask = ((__int128)1 << 40) - 1;
+  d[1] += d[0] >> 40;
+  d[2] += d[1] >> 40;
+  unsigned __int128 low = (unsigned __int128)((d[1] & kMask) << 40 | (d[0] & kMask));
+  __int128 high = d[2];
+  const bool neg = high < 0;
+  if (neg) {
+    high = -high - (low != 0 ? 1 : 0);
+    if (low != 0) low = ((unsigned __int128)1 << 80) - low;
+  }
+  // |high| < 2^73: 55 bits and more with a sticky one decide the rounding
+  double x;
+  if (high == 0) {
+    x = ldexp((double)low, 40 * t.anchor - 1103);
+  } else {
+    const unsigned __int128 rest = low & (((unsigned __int128)1 << 26) - 1);
+    x = ldexp((double)((unsigned __int128)high << 54 | low >> 26 | (rest != 0 ? 1u : 0u)),
+              40 * t.anchor - 1103 + 26);
+  }
+  return neg ? -x : x;
+}
+
+// Momentum and energy (NV = 4) or relative energy (NV = 1) of a box in sums that do
+// not depend on the order of its slots.
+template <int NV>
+int sum_exact(mpc_sim* s, int32_t box, double* sum) {
+  ObsTotal t[NV];
+  HIPCHK(s, launch_obs_exact(s->dev, s->L, (uint32_t)box, s->boxes[box].np, s->cur, NV, s->vmean, t));
+  HIPCHK(s, hipStreamSynchronize(s->L.stream));
+  for (int k = 0; k < NV; ++k) sum[k] = exact_value(t[k]);
   return MPC_OK;
 }
 
@@ -665,32 +717,38 @@ int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, int nv, Neumaier* a) {
 int obs_box(mpc_sim* s, int32_t box, double* P, double* E, double* K) {
   const BoxDev& B = s->boxes[box];
   const uint32_t pb0 = s->box_pb0[box], npb = s->box_pb0[box + 1] - pb0;
-  uint32_t* order = nullptr;
-  if (s->form == MPC_FP64 && s->stepped[box]) {
-    // the chains of the buffer that the next step writes are free until then
-    order = s->dev.rnext[s->cur ^ 1u];
-    s->binning_ready = false;
-    HIPCHK(s, launch_obs_order(s->dev, s->L, (uint32_t)box, (uint32_t)B.L[1] * (uint32_t)B.nlz,
-                               (uint32_t)B.L[0], s->cur, obs_tile_cells(B.density), order));
+  // The slots of a step depend on the order in which runs were appended.  FP64
+  // momentum and energy are added in an order of the particles' cells then (a
+  // total momentum is a sum of rounding errors, of which every digit depends on
+  // that order), all other sums are free of the order.
+  const char slots = s->slots[box];
+  double sum[4];
+  int rc;
+  if (slots == kSlotsCaller || (s->form == MPC_FP64 && slots == kSlotsStep)) {
+    uint32_t* order = nullptr;
+    if (slots == kSlotsStep) {
+      // the chains of the buffer that the next step writes are free until then
+      order = s->dev.rnext[s->cur ^ 1u];
+      s->binning_ready = false;
+      HIPCHK(s, launch_obs_order(s->dev, s->L, (uint32_t)box, (uint32_t)B.L[1] * (uint32_t)B.nlz,
+                                 (uint32_t)B.L[0], s->cur, obs_tile_cells(B.density), order));
+    }
+    HIPCHK(s, launch_obs_pass1(s->dev, s->L, pb0, npb, s->cur, order));
+    rc = sum_partials(s, pb0, npb, sum);
+  } else {
+    rc = sum_exact<4>(s, box, sum);
   }
-  HIPCHK(s, launch_obs_pass1(s->dev, s->L, pb0, npb, s->cur, order));
-  Neumaier a[4];
-  int rc = sum_partials(s, pb0, npb, 4, a);
   if (rc) return rc;
   const double M = (double)B.np * B.mass;
   double vm[3];
   for (int k = 0; k < 3; ++k) {
-    P[k] = a[k].val();
+    P[k] = sum[k];
     vm[k] = P[k] / M;
   }
-  *E = a[3].val();
+  *E = sum[3];
   HIPCHK(s, hipMemcpyAsync(s->vmean + 3 * (size_t)box, vm, sizeof vm, hipMemcpyHostToDevice,
                            s->L.stream));
-  HIPCHK(s, launch_obs_pass2(s->dev, s->L, pb0, npb, s->cur, s->vmean));
-  Neumaier k2[1];
-  if ((rc = sum_partials(s, pb0, npb, 1, k2))) return rc;
-  *K = k2[0].val();
-  return MPC_OK;
+  return sum_exact<1>(s, box, K);
 }
 
 }  // namespace
@@ -934,7 +992,7 @@ int mpc_step(mpc_sim* s, int64_t nsteps) {
   advance_mirror(s, nsteps);
   s->have_binning = true;
   s->binning_ready = false;
-  s->stepped.assign(s->boxes.size(), 1);
+  s->slots.assign(s->boxes.size(), kSlotsStep);
   return MPC_OK;
 }
 
@@ -990,7 +1048,7 @@ int mpc_step_profiled(mpc_sim* s, int64_t nsteps, mpc_kernel_times* acc) {
   advance_mirror(s, nsteps);
   s->have_binning = true;
   s->binning_ready = false;
-  s->stepped.assign(s->boxes.size(), 1);
+  s->slots.assign(s->boxes.size(), kSlotsStep);
   return MPC_OK;
 }
 
@@ -1051,7 +1109,7 @@ int mpc_init_state(mpc_sim* s, uint64_t init_seed) {
   s->keys_valid = false;
   s->have_binning = false;
   s->binning_ready = false;
-  s->stepped.assign(s->boxes.size(), 0);
+  s->slots.assign(s->boxes.size(), kSlotsCaller);
   return MPC_OK;
 }
 
@@ -1096,7 +1154,7 @@ int mpc_set_state(mpc_sim* s, int32_t box, const double* x, const double* v, int
   s->keys_valid = false;
   s->have_binning = false;
   s->binning_ready = false;
-  s->stepped[box] = 0;
+  s->slots[box] = kSlotsCaller;
   return MPC_OK;
 }
 
@@ -1270,6 +1328,9 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
   hipStream_t st = s->L.stream;
   const uint64_t step0 = s->step;
   const uint32_t cur0 = s->cur;
+  std::vector<char> slots0 = s->slots;
+  for (char& o : slots0)
+    if (o == kSlotsStep) o = kSlotsOther;
   const int T0 = s->tile_override, g0 = s->grid_override, y0 = s->yblock, o0 = s->order;
   // the arrays of the current state buffer, backed up on the device (or in
   // host memory if the device has no room) and restored before every trial
@@ -1316,7 +1377,7 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
     s->keys_valid = false;
     s->have_binning = false;
     s->binning_ready = false;
-    s->stepped.assign(s->boxes.size(), 0);
+    s->slots = slots0;
     HIPCHK(s, launch_set_ctrl(s->dev, s->L, step0, cur0, s->R, 1));
     return MPC_OK;
   };

@@ -13,6 +13,8 @@ constexpr int kTileMaxCells = 32;           // cells per collide tile (< kCollid
 constexpr int kObsPass = 256;               // particles per pass of the observables' order
 constexpr int kObsSums = 128;               // sums left of the observables' partial sums
 constexpr int kObsList = 320;               // particles of an obs tile listed in LDS
+constexpr uint32_t kObsRows = 2048;         // most blocks of the order-free sums
+constexpr int kObsBad = 60;                 // their anchor after a term that is not finite
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
 constexpr int kPartBlock = kThreads * 4;    // particles per block of per-particle kernels
@@ -118,6 +120,17 @@ struct PhantomSums {   // phantom particles of an occupied wall-cut cell
   double pad;
 };
 
+template <int NV>
+struct ObsRow {        // order-free sums of a block of particles (see k_obs_exact)
+  long long d[NV][3];  // digits of 40 bits, lowest first
+  int32_t anchor[NV];  // bin of the top digit: its unit is 2^(40 anchor - 1023)
+};
+struct ObsTotal {      // one sum of a box
+  uint64_t lo[3];      // digits as 128-bit integers
+  int64_t hi[3];
+  int32_t anchor, pad;
+};
+
 // Particle records, one per storage slot (array of structures): the collide
 // gathers a particle with one or two 16-byte loads per 16 bytes of record, so
 // that a run of consecutive slots is one contiguous span of memory instead of
@@ -179,7 +192,9 @@ struct Dev {           // device pointers carved from the workspace
   Tile* tiles;
   PBlock* pblocks;
   double* partials;    // per-block observable partial sums
-  double* obs;         // kObsSums rows of their sums: high parts [4], low parts [4]
+  double* obs;         // kObsSums rows of their sums: high parts [4], low parts [4];
+                       // or four ObsTotal and kObsRows rows (ObsRow<4>) of the
+                       // order-free sums
   double4* draws[2];      // per cell: rotation axis, z of attempt 0 of the gamma draw
   // thermostat: per cell, the least count that accepts attempt 0 and the first
   // of its later attempts << 16 in the block's segment of later_seg(drawb) attempts
@@ -232,8 +247,10 @@ hipError_t launch_obs_order(const Dev& d, const Launch& l, uint32_t box, uint32_
                             uint32_t l0, uint32_t cur, uint32_t To, uint32_t* order);
 hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
                             const uint32_t* order);
-hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
-                            const double* vmean_dev);
+// nv sums (4: momentum and energy; 1: relative energy, vmean) of a box: *total
+
+hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
+                            int nv, const double* vmean, ObsTotal* total);
 hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
 // sel: box-local logical indices, overwritten; keys: 2 (mask + 1) entries of a

@@ -3118,8 +3118,10 @@ __global__ __launch_bounds__(kThreads) void k_init_state(Dev d, uint32_t k0, uin
 }
 
 // ---------------------------------------------------------------------------
-// Observables: per-block partial sums (FP64), of many blocks summed further by
-// k_obs_sums, the rest in order on the host.  pass 1: P (3), E; pass 2: sum m |v - vmean|^2.
+// Observables: momentum and energy of slots in a fixed order as per-block
+// partial sums (FP64), of many blocks summed further by k_obs_sums, the rest in
+// order on the host; else, and for the relative energy, sums that do not depend
+// on the order (k_obs_exact).
 // ---------------------------------------------------------------------------
 template <int F>
 __device__ __forceinline__ void load_vel_d(const StatePtrs& S, uint32_t i, double (&v)[3]) {
@@ -3354,27 +3356,199 @@ __global__ __launch_bounds__(kThreads) void k_obs_pass1(Dev d, uint32_t pb0, uin
   }
 }
 
-template <int F>
-__global__ __launch_bounds__(kThreads) void k_obs_pass2(Dev d, uint32_t pb0, uint32_t cur,
-                                                        const double* vmean) {
-  __shared__ double s_red[kThreads];
-  const uint32_t blk = pb0 + blockIdx.x;
-  const PBlock pb = load_pblock(d.pblocks, blk);
-  BoxRef B = as_const(d.boxes)[pb.box];
+// Sums that do not depend on the order of their terms (of the velocities where
+// no order of the slots is fixed, and of every form's relative energy).  A term
+// x becomes three whole digits of 40 bits on a fixed grid of exponents, with
+// the top digit in bin floor(e / 40) of the largest exponent e so far: digits
+// below the third are cut off term by term and those that a larger exponent
+// pushes out are dropped, so that what is left at the end depends on the terms
+// alone.  It is short of the true sum by less than n 2^-80 times the largest
+// term.  The digits are FP64 numbers: at most 8192 of 2^40 a thread stay below
+// 2^53.  The kernel reads what plain sums read, once, and is bound by that;
+// about 11 FP64 operations a term take a tenth of the time.
+struct ExactSum {
+  double a[3];  // digits, lowest first
+  int anchor;   // bin of the top digit; -1: none yet
+};
+__device__ __forceinline__ void exact_grow(ExactSum& s, uint32_t e) {
+  const int b = e == 2047u ? kObsBad : (int)(e / 40u);
+  const int by = b - s.anchor;
+  s.a[0] = by == 1 ? s.a[1] : (by == 2 ? s.a[2] : 0.0);
+  s.a[1] = by == 1 ? s.a[2] : 0.0;
+  s.a[2] = 0.0;
+  s.anchor = b;
+}
+__device__ __forceinline__ void exact_add(ExactSum& s, double x) {
+  const uint32_t e = (uint32_t)((uint64_t)__double_as_longlong(x) >> 52) & 0x7ffu;
+  if (__builtin_expect(e >= 40u * (uint32_t)(s.anchor + 1), 0)) exact_grow(s, e);
+  // 2^(1023 - 40 anchor); any finite number once a term was not finite
+  const uint32_t se = s.anchor == kObsBad ? 1023u : 2046u - 40u * (uint32_t)s.anchor;
+  double r = x * __longlong_as_double((long long)((uint64_t)se << 52));
+  double w = __builtin_trunc(r);
+  s.a[2] += w;
+  r = (r - w) * 0x1p40;
+  w = __builtin_trunc(r);
+  s.a[1] += w;
+  s.a[0] += __builtin_trunc((r - w) * 0x1p40);
+}
+// Digits of a sum anchored at bin `from`, lowest first, moved to bin `to`.
+__device__ __forceinline__ void exact_move(long long (&v)[3], int from, int to) {
+  const int by = to - from;
+  v[0] = by == 0 ? v[0] : (by == 1 ? v[1] : (by == 2 ? v[2] : 0ll));
+  v[1] = by == 0 ? v[1] : (by == 1 ? v[2] : 0ll);
+  v[2] = by == 0 ? v[2] : 0ll;
+}
+
+// NV = 4: momentum and energy; 1: sum m |v - vmean|^2.  Particles [blockIdx.x
+// per, (blockIdx.x + 1) per) of the box into row blockIdx.x.
+template <int F, int NV>
+__global__ __launch_bounds__(kThreads) void k_obs_exact(Dev d, uint32_t box, uint32_t cur,
+                                                        const double* vmean, uint32_t per) {
+  __shared__ ObsRow<NV> s_row[kThreads / 64];
+  BoxRef B = as_const(d.boxes)[box];
   const StatePtrs S = d.S[cur];
-  const uint32_t pend = B.pbase + B.np;
-  const double V[3] = {vmean[3 * pb.box], vmean[3 * pb.box + 1], vmean[3 * pb.box + 2]};
-  double acc = 0.0;
-  for (int s = 0; s < kPartBlock / kThreads; ++s) {
-    const uint32_t i = pb.p0 + s * kThreads + threadIdx.x;
-    if (i >= pend) continue;
-    double v[3];
-    load_vel_d<F>(S, i, v);
-    const double dx = v[0] - V[0], dy = v[1] - V[1], dz = v[2] - V[2];
-    acc += B.mass * (dx * dx + dy * dy + dz * dz);
+  const uint32_t i0 = blockIdx.x * per, i1 = min(i0 + per, B.np);
+  double V[3] = {0.0, 0.0, 0.0};
+  if (NV == 1) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) V[k] = vmean[3 * box + k];
   }
-  const double r = block_sum_d(acc, s_red);
-  if (threadIdx.x == 0) d.partials[(uint64_t)blk * 4] = r;
+  ExactSum acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = ExactSum{{0.0, 0.0, 0.0}, -1};
+  // a pass of four particles a thread, the next one's loads in flight beside it
+  constexpr int U = kPartBlock / kThreads;
+  double v[U][3], w[U][3];
+  auto load = [&](uint32_t q, double (&r)[U][3]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t i = q + u * kThreads + threadIdx.x;
+      if (i < i1) load_vel_d<F>(S, B.pbase + i, r[u]);
+    }
+  };
+  load(i0, v);
+  for (uint32_t q = i0; q < i1; q += kPartBlock) {
+    load(q + kPartBlock, w);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (q + u * kThreads + threadIdx.x < i1) {
+        if constexpr (NV == 4) {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) exact_add(acc[k], B.mass * v[u][k]);
+          exact_add(acc[3], 0.5 * B.mass *
+                                (v[u][0] * v[u][0] + v[u][1] * v[u][1] + v[u][2] * v[u][2]));
+        } else {
+          const double dx = v[u][0] - V[0], dy = v[u][1] - V[1], dz = v[u][2] - V[2];
+          exact_add(acc[0], B.mass * (dx * dx + dy * dy + dz * dz));
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 3; ++k) v[u][k] = w[u][k];
+    }
+  }
+  // the wavefront, then the block: all at their largest bin, as integers (at
+  // most 2^53 a thread, 2^61 a block)
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    int top = acc[k].anchor;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) top = max(top, __shfl_xor(top, m, 64));
+    long long t[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) t[j] = acc[k].anchor == kObsBad ? 0ll : (long long)acc[k].a[j];
+    exact_move(t, acc[k].anchor, top);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) t[j] += __shfl_xor(t[j], m, 64);
+      if (lane == 0) s_row[wave].d[k][j] = t[j];
+    }
+    if (lane == 0) s_row[wave].anchor[k] = top;
+  }
+  __syncthreads();
+  if (threadIdx.x < NV) {
+    const int k = (int)threadIdx.x;
+    int top = -1;
+    for (int w = 0; w < kThreads / 64; ++w) top = max(top, s_row[w].anchor[k]);
+    long long sum[3] = {0, 0, 0};
+    for (int w = 0; w < kThreads / 64; ++w) {
+      long long t[3] = {s_row[w].d[k][0], s_row[w].d[k][1], s_row[w].d[k][2]};
+      exact_move(t, s_row[w].anchor[k], top);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) sum[j] += t[j];
+    }
+    ObsRow<NV>& o = ((ObsRow<NV>*)((ObsTotal*)d.obs + 4))[blockIdx.x];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) o.d[k][j] = sum[j];
+    o.anchor[k] = top;
+  }
+}
+
+// All rows of a box to one total: kThreads threads for each value.
+template <int NV>
+__global__ __launch_bounds__(kThreads * NV) void k_obs_total(Dev d, uint32_t rows) {
+  constexpr uint32_t kWaves = kThreads / 64;
+  __shared__ ObsTotal s_t[kWaves * NV];
+  const ObsRow<NV>* row = (const ObsRow<NV>*)((const ObsTotal*)d.obs + 4);
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, k = wave / kWaves;
+  __int128 s[3] = {0, 0, 0};
+  int top = -1;
+  auto move = [&](int to) {  // as exact_move
+    const int by = to - top;
+    s[0] = by == 0 ? s[0] : (by == 1 ? s[1] : (by == 2 ? s[2] : 0));
+    s[1] = by == 0 ? s[1] : (by == 1 ? s[2] : 0);
+    s[2] = by == 0 ? s[2] : 0;
+    top = to;
+  };
+#pragma unroll 4
+  for (uint32_t q = threadIdx.x % kThreads; q < rows; q += kThreads) {
+    long long t[3] = {row[q].d[k][0], row[q].d[k][1], row[q].d[k][2]};
+    const int at = row[q].anchor[k];
+    if (at > top) move(at);
+    exact_move(t, at, top);
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] += t[j];
+  }
+  int all = top;
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) all = max(all, __shfl_xor(all, m, 64));
+  move(all);
+#pragma unroll
+  for (int m = 1; m < 64; m <<= 1) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const uint64_t lo = __shfl_xor((unsigned long long)s[j], m, 64);
+      const int64_t hi = __shfl_xor((long long)(s[j] >> 64), m, 64);
+      s[j] += (__int128)hi << 64 | lo;
+    }
+  }
+  auto put = [&](ObsTotal& o) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      o.lo[j] = (uint64_t)s[j];
+      o.hi[j] = (int64_t)(s[j] >> 64);
+    }
+    o.anchor = top;
+  };
+  if (lane == 0) put(s_t[wave]);
+  __syncthreads();
+  if (lane == 0 && wave == k * kWaves) {
+    for (uint32_t w = wave; w < wave + kWaves; ++w) all = max(all, s_t[w].anchor);
+    move(all);
+    __int128 sum[3] = {s[0], s[1], s[2]};
+    for (uint32_t w = wave + 1; w < wave + kWaves; ++w) {
+#pragma unroll
+      for (int j = 0; j < 3; ++j) s[j] = (__int128)s_t[w].hi[j] << 64 | s_t[w].lo[j];
+      top = s_t[w].anchor;
+      move(all);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) sum[j] += s[j];
+    }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) s[j] = sum[j];
+    put(((ObsTotal*)d.obs)[k]);
+  }
 }
 
 // Sums of many blocks' partials: each thread adds a stride of them and the
@@ -3672,12 +3846,48 @@ hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_
   return hipGetLastError();
 }
 
-hipError_t launch_obs_pass2(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
-                            const double* vmean) {
-  if (npb == 0) return hipSuccess;
-  MPC_FORM_DISPATCH(l.form, k_obs_pass2, dim3(npb), dim3(kThreads), 0, l.stream, d, pb0, cur,
-                    vmean);
-  return hipGetLastError();
+// Blocks and particles of each, whole passes: eight blocks per compute unit for
+// the loads in flight (256^3 split, two passes of 0.9 ms: 1.9 ms with 1024
+// blocks and more, 2.3 with 512), fewer where a block would have less than four
+// passes.
+static uint32_t obs_exact_blocks(uint32_t np, uint32_t* per) {
+  const uint64_t passes = ((uint64_t)np + kPartBlock - 1) / kPartBlock;
+  const uint64_t each = std::max<uint64_t>((passes + kObsRows - 1) / kObsRows,
+                                           std::min<uint64_t>(4, (passes + 2047) / 2048));
+  // whole numbers below 2^53 in every thread
+  static_assert(((1ull << 31) / kPartBlock / kObsRows) * (kPartBlock / kThreads) <= 8192, "terms");
+  *per = (uint32_t)(each * kPartBlock);
+  return (uint32_t)((passes + each - 1) / each);
+}
+template <int F, int NV>
+static void launch_obs_exact_form(const Dev& d, const Launch& l, uint32_t box, uint32_t np,
+                                  uint32_t cur, const double* vmean) {
+  uint32_t per;
+  const uint32_t rows = obs_exact_blocks(np, &per);
+  hipLaunchKernelGGL((k_obs_exact<F, NV>), dim3(rows), dim3(kThreads), 0, l.stream, d, box, cur,
+                     vmean, per);
+  hipLaunchKernelGGL(k_obs_total<NV>, dim3(1), dim3(kThreads * NV), 0, l.stream, d, rows);
+}
+hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
+                            int nv, const double* vmean, ObsTotal* total) {
+  const bool all = nv == 4;
+  switch (l.form) {
+    case kFormF64:
+      if (all) launch_obs_exact_form<kFormF64, 4>(d, l, box, np, cur, vmean);
+      else launch_obs_exact_form<kFormF64, 1>(d, l, box, np, cur, vmean);
+      break;
+    case kFormF32:
+      if (all) launch_obs_exact_form<kFormF32, 4>(d, l, box, np, cur, vmean);
+      else launch_obs_exact_form<kFormF32, 1>(d, l, box, np, cur, vmean);
+      break;
+    default:
+      if (all) launch_obs_exact_form<kFormSplit, 4>(d, l, box, np, cur, vmean);
+      else launch_obs_exact_form<kFormSplit, 1>(d, l, box, np, cur, vmean);
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return hipMemcpyAsync(total, d.obs, sizeof(ObsTotal) * (size_t)nv, hipMemcpyDeviceToHost,
+                        l.stream);
 }
 
 hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb) {
