@@ -302,7 +302,7 @@ int mpc_destroy(mpc_sim* s);
  * mpc_get_state would.  x[3][n], v[3][n]: caller-owned device arrays, FP64
  * SoA in physical units as in mpc_set_state; on return they hold the state
  * after the steps in the same particle order.  All working memory (both
- * state buffers, run lists, draws, tables) is a static device array of 896 MiB
+ * state buffers, run lists, draws, tables) is a static device array of 704 MiB
  * inside the library, one per device, held until the process ends; no device
  * memory is allocated.  Boxes of more than 256 MiB, counted as 114 B per
  * particle, 45 B per cell (93 B with walls) and tables -> MPC_ERANGE (about

@@ -51,6 +51,17 @@ int auto_tile_cells(double density, int l0, uint64_t rows) {
   return (l0 + per_row - 1) / per_row;
 }
 
+// Runs that the table of a tile holds, of at most kMaxRuns: three rows of three
+// tiles in three layers send it one run each, and a tile of few particles has
+// no more runs than particles, so a table for the mean number of particles and
+// three standard deviations is enough (a fuller tile goes to chains).  Tables of
+// 32 runs had taken 768 bytes for every tile, eight times what else a thin
+// sparse box needs.
+uint64_t tile_runs(double density, int tile_cells) {
+  const double mean = density * tile_cells;
+  return (uint64_t)std::max(1.0, std::min<double>(kMaxRuns, ceil(mean + 3.0 * sqrt(mean))));
+}
+
 struct Plan {
   std::vector<BoxPlan> box;
   uint64_t ntot = 0, ctot = 0, cpad = 0;
@@ -161,6 +172,7 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   int rc = validate(p, nbox, why);
   if (rc) return rc;
   P.box.resize(nbox);
+  uint64_t tiles = 0, maxr = 1;
   for (int32_t b = 0; b < nbox; ++b)
     P.rows += (uint64_t)p[b].L[1] * ((uint64_t)p[b].L[2] + ((p[b].flags & MPC_WALLS_Z) ? 2 : 0));
   for (int32_t b = 0; b < nbox; ++b) {
@@ -187,7 +199,8 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
     const int ta = auto_tile_cells(q.density, q.L[0], P.rows);
     const uint64_t auto_tiles = rows * ((q.L[0] + ta - 1) / ta);
     P.max_tiles += std::max(auto_tiles, rows * ((q.L[0] + kMinTileCells - 1) / kMinTileCells));
-    P.run_pool += auto_tiles * kMaxRuns;
+    tiles += auto_tiles;
+    maxr = std::max(maxr, tile_runs(q.density, ta));  // one length for all boxes
     P.npblocks += (P.box[b].n + kPartBlock - 1) / kPartBlock;
   }
   P.nscan = (uint32_t)((P.ctot + kScanBlock - 1) / kScanBlock);
@@ -223,7 +236,7 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   off = shared0;
   // a tiling with more tiles than the automatic one has shorter run tables,
   // of at least one run a tile
-  P.run_pool = std::max<uint64_t>(P.run_pool, P.max_tiles);
+  P.run_pool = std::max<uint64_t>(tiles * maxr, P.max_tiles);
   for (int k = 0; k < 3; ++k) P.off_tcnt[k] = take(8 * P.max_tiles);
   for (int k = 0; k < 2; ++k) {
     P.off_runs[k] = take(sizeof(Run) * P.run_pool);
@@ -268,9 +281,11 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
 // process end; host code reaches it only through the address that
 // hipGetSymbolAddress returns for the current device.
 constexpr size_t kScratchLimit = (size_t)256 << 20;  // see scratch_charge
-// the workspace of a call within the limit: up to 3.3 times its charge in a
-// sparse box, where the cells' draws and the tiles' tables dominate
-constexpr size_t kScratchBytes = (size_t)896 << 20;
+// The workspace of a call within the limit: at most 2.7 times its charge, in a
+// box of rows of one cell with 0.1 particles per cell, where the cells' draws (64
+// bytes, 82 with the thermostat) and the tiles' tables (52 bytes and 24 a run)
+// dominate.
+constexpr size_t kScratchBytes = (size_t)704 << 20;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex scratch_mu;
