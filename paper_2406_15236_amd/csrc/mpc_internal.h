@@ -234,7 +234,7 @@ struct Launch {
 hipError_t launch_zero_u32(uint32_t* p, uint64_t n, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint64_t n, uint32_t value, hipStream_t s);
 hipError_t launch_binning(const Dev& d, const Launch& l, const StatePtrs& S, uint64_t t);
-hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to);
+hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to, int caller);
 hipError_t launch_prefix(const Dev& d, const Launch& l);
 hipError_t launch_advance(const Dev& d, const Launch& l, uint32_t n);
 hipError_t launch_collide(const Dev& d, const Launch& l);

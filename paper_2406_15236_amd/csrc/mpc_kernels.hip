@@ -24,6 +24,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mpc_internal.h"
 #include "philox_dev.h"
@@ -1058,9 +1059,15 @@ __device__ __forceinline__ uint32_t tile_of(BoxRef B, const int (&c)[3]) {
 }
 
 // Sort by tile of a state set from outside (order arbitrary): particles per
-// tile of step t (high word of the tile's counter) ...
+// tile of step t (high word of the tile's counter), and of every particle its
+// tile and its rank there (in the arrays of the chains, which no run uses yet)
+// ... Neighbouring lanes of one tile share an atomic, so that a state already in
+// order (its tiling changed, its binning exported) does not queue at one word
+// (256^3 FP64: 4.7 ms, 9.5 with an atomic each).  Of a random state every
+// particle takes one, which bounds the kernel: 25 a nanosecond (256^3: 6.6 ms,
+// 7.3 on the whole 64-bit counter).
 template <int F, bool W>
-__global__ __launch_bounds__(kThreads) void k_tile_count(Dev d, uint32_t from, uint32_t to) {
+__global__ __launch_bounds__(kThreads) void k_tile_count(Dev d, uint32_t from) {
   using Fm = Form<F>;
   __shared__ double s_sh[3];
   const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
@@ -1077,63 +1084,108 @@ __global__ __launch_bounds__(kThreads) void k_tile_count(Dev d, uint32_t from, u
   __syncthreads();
   const double s[3] = {s_sh[0], s_sh[1], s_sh[2]};
   const double dle = W ? 0.0 : le_offset(B, t + 1);
-  const uint32_t pend = B.pbase + B.np;
+  const uint32_t pend = B.pbase + B.np, lane = threadIdx.x & 63;
   uint32_t err = 0;
+  constexpr int U = kPartBlock / kThreads;
+  uint32_t tl[U], old[U], lead[U];
 #pragma unroll
-  for (int k = 0; k < kPartBlock / kThreads; ++k) {
+  for (int k = 0; k < U; ++k) {
     const uint32_t i = pb.p0 + k * kThreads + threadIdx.x;
-    if (i >= pend) continue;
-    typename Fm::P p;
-    typename Fm::Vv v;
-    Fm::load(S, i, p, v);
-    Fm::template stream<W>(p, v, B, dle, !W && B.le);
-    int c[3];
-    Fm::template coords<W>(p, s, B, c, err, dle, !W && B.le);
-    atomicAdd(&d.tcnt[0][tile_of(B, c)], 1ull << 32);
+    tl[k] = kNoSlot;
+    old[k] = 0u;
+    if (i < pend) {
+      typename Fm::P p;
+      typename Fm::Vv v;
+      Fm::load(S, i, p, v);
+      Fm::template stream<W>(p, v, B, dle, !W && B.le);
+      int c[3];
+      Fm::template coords<W>(p, s, B, c, err, dle, !W && B.le);
+      tl[k] = tile_of(B, c);
+    }
+    const uint32_t before = __shfl_up(tl[k], 1, 64);
+    const uint64_t heads = __ballot(lane == 0 || before != tl[k]);
+    const uint64_t upto = heads & (~0ull >> (63u - lane)), after = heads & ~(~0ull >> (63u - lane));
+    lead[k] = 63u - (uint32_t)__clzll((long long)upto);
+    const uint32_t end = after ? (uint32_t)__ffsll((unsigned long long)after) - 1u : 64u;
+    if (lane == lead[k] && i < pend)
+      old[k] = atomicAdd((uint32_t*)&d.tcnt[0][tl[k]] + 1, end - lane);
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t i = pb.p0 + k * kThreads + threadIdx.x;
+    const uint32_t rank = __shfl(old[k], (int)lead[k], 64) + (lane - lead[k]);
+    if (i < pend) {
+      d.rnext[0][i] = tl[k];
+      d.rnext[1][i] = rank;
+    }
   }
   if (err) atomicOr(&d.ctrl->err, err);
 }
 
-// ... and, once the prefix of those counts is known, the records into the
-// other buffer, tile by tile (the low word counts the particles placed).
-template <int F, bool W>
+// ... and, once the prefix of those counts is known, the records into the other
+// buffer, tile by tile.  Consecutive lanes move consecutive words of a record,
+// so that a record is one access.  Of a random state one side of the move is
+// random; single particles of whole sectors are better written (split form, 32
+// bytes with the index: 256^3 7.3 ms, a gather 10.8), others better read, after
+// their slots' indices were placed in the id array (FP64: 5.5 + 6.9 ms; records
+// and ids written at random 14.9, three stores a lane 16.1).
 __global__ __launch_bounds__(kThreads) void k_tile_scatter(Dev d, uint32_t from, uint32_t to) {
-  using Fm = Form<F>;
-  __shared__ double s_sh[3];
-  const PBlock pb = load_pblock(d.pblocks, blockIdx.x);
-  BoxRef B = as_const(d.boxes)[pb.box];
-  const uint64_t t = d.ctrl->step;
-  const StatePtrs in = d.S[from], out = d.S[to];
-  if (threadIdx.x == 0) {
-    double s[3];
-    shift_of(B, t, s);
-    s_sh[0] = s[0];
-    s_sh[1] = s[1];
-    s_sh[2] = s[2];
-  }
-  __syncthreads();
-  const double s[3] = {s_sh[0], s_sh[1], s_sh[2]};
-  const double dle = W ? 0.0 : le_offset(B, t + 1);
-  const uint32_t pend = B.pbase + B.np;
-  uint32_t err = 0;
+  __shared__ uint32_t s_j[kPartBlock];
+  const uint32_t i0 = blockIdx.x * kPartBlock;
 #pragma unroll
   for (int k = 0; k < kPartBlock / kThreads; ++k) {
-    const uint32_t i = pb.p0 + k * kThreads + threadIdx.x;
-    if (i >= pend) continue;
-    typename Fm::P p, p2;
-    typename Fm::Vv v, v2;
-    uint32_t id;
-    Fm::load_all(in, i, p, v, id);
-    p2 = p;
-    v2 = v;
-    Fm::template stream<W>(p2, v2, B, dle, !W && B.le);
-    int c[3];
-    Fm::template coords<W>(p2, s, B, c, err, dle, !W && B.le);
-    const uint32_t tl = tile_of(B, c);
-    const uint32_t j = d.toff[tl] + (uint32_t)atomicAdd(&d.tcnt[0][tl], 1ull);
-    if (j < d.ntot) Fm::store_all(out, j, p, v, id);
+    const uint32_t q = k * kThreads + threadIdx.x, i = i0 + q;
+    s_j[q] = i < d.ntot ? d.toff[d.rnext[0][i]] + d.rnext[1][i] : kNoSlot;
   }
-  if (err) atomicOr(&d.ctrl->err, err);
+  __syncthreads();
+  constexpr uint32_t W = sizeof(RecSplit) / sizeof(uint4);
+  const uint4* in = (const uint4*)d.S[from].rec + (size_t)i0 * W;
+  uint4* out = (uint4*)d.S[to].rec;
+#pragma unroll
+  for (uint32_t k = 0; k < W * (kPartBlock / kThreads); ++k) {
+    const uint32_t w = k * kThreads + threadIdx.x, j = s_j[w / W];
+    if (j < d.ntot) out[(size_t)j * W + w % W] = in[w];
+  }
+}
+__global__ __launch_bounds__(kThreads) void k_tile_place(Dev d, uint32_t to) {
+  uint32_t* id = d.S[to].id;
+  uint32_t j[kPartBlock / kThreads];
+#pragma unroll
+  for (int k = 0; k < kPartBlock / kThreads; ++k) {
+    const uint32_t i = blockIdx.x * kPartBlock + k * kThreads + threadIdx.x;
+    j[k] = i < d.ntot ? d.toff[d.rnext[0][i]] + d.rnext[1][i] : kNoSlot;
+  }
+#pragma unroll
+  for (int k = 0; k < kPartBlock / kThreads; ++k)
+    if (j[k] < d.ntot) id[j[k]] = blockIdx.x * kPartBlock + k * kThreads + threadIdx.x;
+}
+// caller: the slots are in the caller's order, their ids their numbers
+template <int F>
+__global__ __launch_bounds__(kThreads) void k_tile_gather(Dev d, uint32_t from, uint32_t to,
+                                                          int caller) {
+  using Word = typename std::conditional<F == kFormF64, double2, float2>::type;
+  constexpr uint32_t W = rec_bytes(F) / sizeof(Word);
+  static_assert(W * sizeof(Word) == rec_bytes(F), "whole words");
+  __shared__ uint32_t s_i[kPartBlock];
+  const StatePtrs in = d.S[from], out = d.S[to];
+  const uint32_t j0 = blockIdx.x * kPartBlock;
+#pragma unroll
+  for (int k = 0; k < kPartBlock / kThreads; ++k) {
+    const uint32_t q = k * kThreads + threadIdx.x, j = j0 + q;
+    uint32_t i = 0;
+    if (j < d.ntot) {
+      i = min(out.id[j], d.ntot - 1u);
+      out.id[j] = caller ? i : in.id[i];
+    }
+    s_i[q] = i;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t k = 0; k < W * (kPartBlock / kThreads); ++k) {
+    const uint32_t w = k * kThreads + threadIdx.x, q = w / W;
+    if (j0 + q < d.ntot)
+      ((Word*)out.rec)[(size_t)j0 * W + w] = ((const Word*)in.rec)[(size_t)s_i[q] * W + w % W];
+  }
 }
 
 // ... and one run per occupied tile.
@@ -3678,25 +3730,8 @@ static hipError_t launch_tile_prefix(const Dev& d, const Launch& l) {
 
 // Sort of the state in buffer `from` into buffer `to` by tile of the next
 // step, the run lists of `to`, and the side work of that step.
-template <int F>
-static void launch_sort_form(const Dev& d, const Launch& l, uint32_t from, uint32_t to,
-                             bool scatter) {
-  const dim3 g(l.npblocks), b(kThreads);
-  if (scatter) {
-    if (l.walls) {
-      hipLaunchKernelGGL((k_tile_scatter<F, true>), g, b, 0, l.stream, d, from, to);
-    } else {
-      hipLaunchKernelGGL((k_tile_scatter<F, false>), g, b, 0, l.stream, d, from, to);
-    }
-  } else {
-    if (l.walls) {
-      hipLaunchKernelGGL((k_tile_count<F, true>), g, b, 0, l.stream, d, from, to);
-    } else {
-      hipLaunchKernelGGL((k_tile_count<F, false>), g, b, 0, l.stream, d, from, to);
-    }
-  }
-}
-hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to) {
+// caller: every box's slots are in the caller's order.
+hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to, int caller) {
   if (l.npblocks == 0) return hipSuccess;
   hipError_t e;
   for (int k = 0; k < 3; ++k)
@@ -3707,13 +3742,26 @@ hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to
         hipSuccess)
       return e;
   }
-  for (int pass = 0; pass < 2; ++pass) {
-    switch (l.form) {
-      case kFormF64: launch_sort_form<kFormF64>(d, l, from, to, pass == 1); break;
-      case kFormF32: launch_sort_form<kFormF32>(d, l, from, to, pass == 1); break;
-      default: launch_sort_form<kFormSplit>(d, l, from, to, pass == 1); break;
+  const dim3 gc(l.npblocks), b(kThreads);
+  switch (l.form * 2 + (l.walls ? 1 : 0)) {
+    case 0: hipLaunchKernelGGL((k_tile_count<kFormF64, false>), gc, b, 0, l.stream, d, from); break;
+    case 1: hipLaunchKernelGGL((k_tile_count<kFormF64, true>), gc, b, 0, l.stream, d, from); break;
+    case 2: hipLaunchKernelGGL((k_tile_count<kFormF32, false>), gc, b, 0, l.stream, d, from); break;
+    case 3: hipLaunchKernelGGL((k_tile_count<kFormF32, true>), gc, b, 0, l.stream, d, from); break;
+    case 4: hipLaunchKernelGGL((k_tile_count<kFormSplit, false>), gc, b, 0, l.stream, d, from); break;
+    default: hipLaunchKernelGGL((k_tile_count<kFormSplit, true>), gc, b, 0, l.stream, d, from); break;
+  }
+  if ((e = launch_tile_prefix(d, l)) != hipSuccess) return e;
+  const dim3 gp((uint32_t)((l.ntot + kPartBlock - 1) / kPartBlock));
+  if (l.form == kFormSplit) {
+    hipLaunchKernelGGL(k_tile_scatter, gp, b, 0, l.stream, d, from, to);
+  } else {
+    hipLaunchKernelGGL(k_tile_place, gp, b, 0, l.stream, d, to);
+    if (l.form == kFormF64) {
+      hipLaunchKernelGGL(k_tile_gather<kFormF64>, gp, b, 0, l.stream, d, from, to, caller);
+    } else {
+      hipLaunchKernelGGL(k_tile_gather<kFormF32>, gp, b, 0, l.stream, d, from, to, caller);
     }
-    if (pass == 0 && (e = launch_tile_prefix(d, l)) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_tile_runs, dim3((d.ntile + kThreads - 1) / kThreads), dim3(kThreads), 0,
                      l.stream, d, to);
