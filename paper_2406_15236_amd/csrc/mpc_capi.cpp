@@ -352,6 +352,7 @@ struct mpc_sim {
   int num_cu = 256, occupancy = 4;
   double* vmean = nullptr;
   char* ws = nullptr;
+  int device = 0;         // of the workspace (and the stream)
   char* stage = nullptr;  // device staging of set_state and get_state, kept up to kKeepStage
   size_t stage_bytes = 0;
   std::string err;
@@ -599,6 +600,20 @@ int read_ids(mpc_sim* s, const StatePtrs& S, uint64_t p0, std::vector<uint32_t>&
   }
   return MPC_OK;
 }
+
+// Makes the handle's device the current one for a call that allocates: the
+// caller's current device may be another.
+struct OnDevice {
+  int before = -1;
+  explicit OnDevice(const mpc_sim* s) {
+    int now = -1;
+    if (hipGetDevice(&now) == hipSuccess && now != s->device && hipSetDevice(s->device) == hipSuccess)
+      before = now;
+  }
+  ~OnDevice() {
+    if (before >= 0) (void)hipSetDevice(before);
+  }
+};
 
 // Device staging for up to n particles (48 bytes each) and a flag before them.
 // Small ones stay with the handle; without device memory the run lists' part
@@ -918,7 +933,14 @@ int mpc_create(const mpc_params* p, int32_t nbox, void* workspace, size_t bytes,
 
   int dev = 0;
   hipDeviceProp_t prop;
-  if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
+  hipPointerAttribute_t attr;
+  if (hipGetDevice(&dev) == hipSuccess) s->device = dev;
+  if (hipPointerGetAttributes(&attr, workspace) == hipSuccess) {
+    s->device = attr.device;
+  } else {
+    (void)hipGetLastError();  // static scratch: of the current device
+  }
+  if (hipGetDeviceProperties(&prop, s->device) == hipSuccess)
     s->num_cu = prop.multiProcessorCount;
   s->occupancy = 2;
   if (collide_occupancy(s->L, &s->occupancy) != hipSuccess ||
@@ -1138,6 +1160,7 @@ int mpc_set_state(mpc_sim* s, int32_t box, const double* x, const double* v, int
     return MPC_EINVAL;
   }
   const double a = s->params[box].a;
+  const OnDevice on(s);
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
   Stage st;
   get_stage(s, n, &st);
@@ -1182,6 +1205,7 @@ int mpc_get_state(mpc_sim* s, int32_t box, double* x, double* v, int64_t n) {
   int rc = mpc_sync(s);
   if (rc) return rc;
   const double a = s->params[box].a;
+  const OnDevice on(s);
   Stage st;
   get_stage(s, n, &st);
   const int64_t chunk = std::min(n, st.cap);
@@ -1223,6 +1247,7 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
   }
   int rc = mpc_sync(s);
   if (rc || m == 0) return rc;
+  const OnDevice on(s);
   const StatePtrs& S = s->dev.S[s->cur];
   // one allocation: the sample's states, indices, and the table that finds
   // their slots (see k_sample_find)
@@ -1341,6 +1366,7 @@ int mpc_autotune(mpc_sim* s, int32_t trial_steps, int32_t* tile_cells, int32_t* 
   if (!s || trial_steps < 1 || trial_steps > 1000) return MPC_EINVAL;
   int rc = mpc_sync(s);
   if (rc) return rc;
+  const OnDevice on(s);
   const Plan& P = s->plan;
   hipStream_t st = s->L.stream;
   const uint64_t step0 = s->step;
