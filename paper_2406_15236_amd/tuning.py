@@ -2,10 +2,13 @@
 
 `mpc_autotune` times a coordinate search over tilings on the live state;
 results do not depend on the tiling, only the speed does.  This module keeps
-the chosen tiling (cells per tile, persistent grid, rows per block, tile
-order) in a JSON file keyed by the device (architecture name and compute-unit
-count), the storage form, the feature flags and the box shapes, so that a
-later handle of the same kind skips the timing runs.
+the chosen tiling (cells per tile, grid, rows per block, tile order) in a JSON
+file keyed by the generation of the kernels that were timed, the device
+(architecture name and compute-unit count), the storage form, the feature
+flags and the box shapes, so that a later handle of the same kind skips the
+timing runs.  Entries of other generations stay in the file and are not
+applied: a grid of a few wavefronts per compute unit, best for kernels that
+gathered sorted slots, costs those that gather runs 15 % at 384^3.
 
 The file is `$MPC_TUNE_CACHE` if set, else `tuning_cache.json` beside this
 module.  Entries are plain JSON; a corrupt or unreadable file is treated as
@@ -20,6 +23,7 @@ import tempfile
 
 DEFAULT_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tuning_cache.json")
 FIELDS = ("tile_cells", "grid", "yblock", "order")
+KERNELS = "runs1"  # generation of the collide's tiling and grid; change it with them
 
 
 def cache_path(path: str | None = None) -> str:
@@ -35,11 +39,11 @@ def device_tag() -> str:
 
 
 def cache_key(device: str, params) -> str:
-    """Key of a set of boxes: device, form, flags, and the box shapes -- every
+    """Key of a set of boxes: kernels, device, form, flags, and the box shapes -- every
     (L, density) for up to four boxes, else the box count with the particle
     total and the mean density rounded to a power of two."""
     p0 = params[0]
-    head = f"{device}|form{p0.form}|flags{p0.flags}"
+    head = f"{KERNELS}|{device}|form{p0.form}|flags{p0.flags}"
     if len(params) <= 4:
         shapes = ";".join(f"{q.L[0]}x{q.L[1]}x{q.L[2]}@{q.density:g}" for q in params)
         return f"{head}|{shapes}"
