@@ -2143,8 +2143,8 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       return lc;
     };
 
-    // a tile of more than one pass, or with chains: particles per cell first
-    const bool slow = cu.np > (uint32_t)kTileCap || cu.nrun > maxr;
+    // a tile of more than one pass: particles per cell first
+    const bool slow = cu.np > (uint32_t)kTileCap;
     if (slow) {
       wave_sync();
       if (lane < (uint32_t)kTileMaxCells) s_cnt[lane] = 0u;
@@ -2229,6 +2229,32 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
             }
           }
         });
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          const uint32_t q = lane + k * NT;
+          ii[k] = q < np ? s_id[q] : 0u;
+        }
+        wave_sync();
+      } else if (__builtin_expect(cu.nrun > maxr, 0)) {
+        // runs of the table by their lanes, then the chains, a lane each
+        const uint32_t inc = wave_scan_dpp(cu.run.count);
+        const uint32_t pre = inc - cu.run.count;
+        wave_sync();
+        for (uint32_t q = 0; q < cu.run.count && pre + q < (uint32_t)kTileCap; ++q)
+          s_id[pre + q] = cu.run.start + q;
+        uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        uint32_t i = lane < maxr ? d.rhead[cur][(size_t)T.tid * maxr + lane] : kNoSlot;
+        while (const uint64_t m = __ballot(i < d.ntot)) {
+          const uint32_t q = n + lanes_below(m);
+          n += (uint32_t)__popcll(m);
+          if (i < d.ntot) {
+            if (q < (uint32_t)kTileCap) s_id[q] = i;
+            i = d.rnext[cur][i];
+          }
+        }
+        np = min(n, (uint32_t)kTileCap);
+        if (np != cu.np) err |= kErrKey;
         wave_sync();
 #pragma unroll
         for (int k = 0; k < NS; ++k) {
@@ -2625,53 +2651,43 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       }
       wave_sync();
       if (__builtin_expect(nfar != 0u, 0)) {
-        // far particles: one run per destination, found one by one
-        uint32_t fd[NS], fpos[NS];
-        uint64_t left[NS];
+        // far particles: ordered by destination, a run for each, by the rank of
+        // every one among all (particles of several cells a step, 64^3 FP64: with
+        // the destinations found one after the other, and their chains read
+        // three times, 823 us a step)
+        uint32_t fd[NS];
 #pragma unroll
         for (int k = 0; k < NS; ++k) {
           const uint32_t q = lane + k * NT;
-          const bool far = q < np && (gk[k] & 0xffu) == (uint32_t)kGroups;
-          fd[k] = far ? s_id[q] : kNoSlot;
-          left[k] = __ballot(far);
-          fpos[k] = 0u;
+          fd[k] = q < np && (gk[k] & 0xffu) == (uint32_t)kGroups ? s_id[q] : kNoSlot;
         }
-        uint32_t done = 0, ng = 0, rd = kNoSlot, rs = 0, rn = 0;
-        while (done < nfar) {
-          uint32_t dest = 0;
-          bool found = false;
+        wave_sync();
 #pragma unroll
-          for (int k = 0; k < NS; ++k)
-            if (!found && left[k]) {
-              dest = (uint32_t)__builtin_amdgcn_readlane((int)fd[k], __ffsll((unsigned long long)left[k]) - 1);
-              found = true;
+        for (int k = 0; k < NS; ++k)
+          if (fd[k] != kNoSlot) s_id[gk[k] >> 8] = fd[k];
+        if (lane < 4u) s_id[nfar + lane] = kNoSlot;  // whole groups of four
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < NS; ++k) {
+          if (fd[k] != kNoSlot) {
+            const uint32_t me = gk[k] >> 8, f = fd[k];
+            uint32_t lt = 0, eq = 0, eb = 0;
+            for (uint32_t a = 0; a < nfar; a += 4) {
+              const uint4 w = *(const uint4*)&s_id[a];
+              const uint32_t e = (w.x == f ? 1u : 0u) | (w.y == f ? 2u : 0u) |
+                                 (w.z == f ? 4u : 0u) | (w.w == f ? 8u : 0u);
+              lt += (w.x < f ? 1u : 0u) + (w.y < f ? 1u : 0u) + (w.z < f ? 1u : 0u) +
+                    (w.w < f ? 1u : 0u);
+              eq += (uint32_t)__popc(e);
+              if (a + 4 <= me) {
+                eb += (uint32_t)__popc(e);
+              } else if (a < me) {
+                eb += (uint32_t)__popc(e & ((1u << (me - a)) - 1u));
+              }
             }
-          if (!found) break;
-          uint32_t n = 0;
-#pragma unroll
-          for (int k = 0; k < NS; ++k) {
-            const bool same = (left[k] >> lane & 1ull) && fd[k] == dest;
-            const uint64_t m = __ballot(same);
-            if (same) fpos[k] = done + n + lanes_below(m);
-            n += (uint32_t)__popcll(m);
-            left[k] &= ~m;
+            gk[k] = (uint32_t)kGroups | (lt + eb) << 8;
+            if (eb == 0u) push_run(d, nxt, tnx, f, base + far0 + lt, eq);
           }
-          if (lane == (ng & 63u)) {
-            rd = dest;
-            rs = done;
-            rn = n;
-          }
-          done += n;
-          if ((++ng & 63u) == 0u || done >= nfar) {
-            if (rn) push_run(d, nxt, tnx, rd, base + far0 + rs, rn);
-            rn = 0u;
-          }
-        }
-#pragma unroll
-        for (int k = 0; k < NS; ++k) {
-          const uint32_t q = lane + k * NT;
-          if (q < np && (gk[k] & 0xffu) == (uint32_t)kGroups)
-            gk[k] = (uint32_t)kGroups | fpos[k] << 8;
         }
       }
       if (gdest != kNoSlot) push_run(d, nxt, tnx, gdest, base + gpre, gn);
@@ -2693,7 +2709,7 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
       cs = ce;
       wave_sync();
     } while (cs < (uint32_t)nc);
-    if (slow && lane < maxr) d.rhead[cur][(size_t)T.tid * maxr + lane] = kNoSlot;
+    if (cu.nrun > maxr && lane < maxr) d.rhead[cur][(size_t)T.tid * maxr + lane] = kNoSlot;
     // advance the pipeline
     it += walk.stride;
     tcur = tnext;
