@@ -21,7 +21,7 @@ SOURCES = [os.path.join(HERE, "csrc", "mpc_kernels.hip"),
 # and 5 with the thermostat in FP64, 158 instead of 140 without it).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          "-ffp-contract=off", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-mllvm", "-disable-machine-licm", "-Wall", "-Wno-unused-function"]
+         "-mllvm", "-disable-machine-licm", "-Wall", "-Werror=unused"]
 
 
 def hipcc() -> str:

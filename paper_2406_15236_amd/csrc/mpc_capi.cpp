@@ -563,13 +563,6 @@ int capture_graph(mpc_sim* s) {
   return MPC_OK;
 }
 
-// Host FP64 <-> stored form of one box.
-template <typename T>
-int copy_h2d(mpc_sim* s, void* dst_base, uint64_t elem0, const std::vector<T>& src) {
-  HIPCHK(s, hipMemcpyAsync((T*)dst_base + elem0, src.data(), sizeof(T) * src.size(),
-                           hipMemcpyHostToDevice, s->L.stream));
-  return MPC_OK;
-}
 template <typename T>
 int copy_d2h(mpc_sim* s, const void* src_base, uint64_t elem0, std::vector<T>& dst) {
   HIPCHK(s, hipMemcpyAsync(dst.data(), (const T*)src_base + elem0, sizeof(T) * dst.size(),

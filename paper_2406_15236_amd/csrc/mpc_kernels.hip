@@ -2409,7 +2409,7 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
 
       // mean velocities (and centres of mass): a lane per cell and half for the
       // three components, or per component too
-      const uint32_t ncp = ce - cs;
+      const uint32_t ncell = ce - cs;
       const bool phantoms = W && !B.slip && wall_fraction(st[2], z0 - 1, L2) > 0.0;
       auto means = [&](auto width, uint32_t cell, uint32_t k0, bool valid) {
         constexpr int N = decltype(width)::value;
@@ -2453,12 +2453,12 @@ void k_collide(Dev d, Side w, uint32_t j, uint32_t ntiles, int xcd_remap) {
           }
         }
       };
-      if (6u * ncp <= (uint32_t)NT) {
+      if (6u * ncell <= (uint32_t)NT) {
         const uint32_t u = lane >> 1;
-        const uint32_t k0 = (u >= ncp ? 1u : 0u) + (u >= 2u * ncp ? 1u : 0u);
-        means(Width<1>{}, cs + u - k0 * ncp, k0, u < 3u * ncp);
+        const uint32_t k0 = (u >= ncell ? 1u : 0u) + (u >= 2u * ncell ? 1u : 0u);
+        means(Width<1>{}, cs + u - k0 * ncell, k0, u < 3u * ncell);
       } else {
-        means(Width<3>{}, cs + (lane >> 1), 0u, (lane >> 1) < ncp);
+        means(Width<3>{}, cs + (lane >> 1), 0u, (lane >> 1) < ncell);
       }
       wave_sync();
       auto mean_of = [&](uint32_t c, int k) -> double {
