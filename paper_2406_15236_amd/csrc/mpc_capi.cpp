@@ -504,13 +504,12 @@ hipError_t enqueue_steps(mpc_sim* s, hipStream_t st, int64_t n) {
 // the run lists): sort by tile of the next step into the other buffer.
 int ensure_keys(mpc_sim* s) {
   if (s->keys_valid) return MPC_OK;
-  HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
+  HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur ^ 1u, s->R, 0));
   const bool caller = std::count(s->slots.begin(), s->slots.end(), (char)kSlotsCaller) ==
                       (int64_t)s->slots.size();
   HIPCHK(s, launch_sort(s->dev, s->L, s->cur, s->cur ^ 1u, caller));
   s->cur ^= 1u;
   s->slots.assign(s->boxes.size(), kSlotsOther);
-  HIPCHK(s, launch_set_ctrl(s->dev, s->L, s->step, s->cur, s->R, 0));
   s->keys_valid = true;
   s->binning_ready = false;
   return MPC_OK;

@@ -1188,6 +1188,20 @@ __global__ __launch_bounds__(kThreads) void k_tile_gather(Dev d, uint32_t from, 
   }
 }
 
+// Before a sort: no particles, no runs, no chains in any set.
+__global__ __launch_bounds__(kThreads) void k_tile_clear(Dev d) {
+  const uint64_t stride = (uint64_t)gridDim.x * kThreads, i0 = (uint64_t)blockIdx.x * kThreads + threadIdx.x;
+  for (uint64_t i = i0; i < d.ntile; i += stride) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) d.tcnt[k][i] = 0ull;
+  }
+  const uint64_t heads = (uint64_t)d.ntile * d.maxr;
+  for (uint64_t i = i0; i < heads; i += stride) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k) d.rhead[k][i] = kNoSlot;
+  }
+}
+
 // ... and one run per occupied tile.
 __global__ __launch_bounds__(kThreads) void k_tile_runs(Dev d, uint32_t to) {
   const uint32_t i = blockIdx.x * kThreads + threadIdx.x;
@@ -3750,14 +3764,9 @@ static hipError_t launch_tile_prefix(const Dev& d, const Launch& l) {
 hipError_t launch_sort(const Dev& d, const Launch& l, uint32_t from, uint32_t to, int caller) {
   if (l.npblocks == 0) return hipSuccess;
   hipError_t e;
-  for (int k = 0; k < 3; ++k)
-    if ((e = launch_zero_u32((uint32_t*)d.tcnt[k], 2ull * d.ntile, l.stream)) != hipSuccess)
-      return e;
-  for (int k = 0; k < 2; ++k) {
-    if ((e = launch_fill_u32(d.rhead[k], (uint64_t)d.ntile * d.maxr, kNoSlot, l.stream)) !=
-        hipSuccess)
-      return e;
-  }
+  const uint64_t clear = (uint64_t)d.ntile * std::max(d.maxr, 2u) / kThreads + 1;
+  hipLaunchKernelGGL(k_tile_clear, dim3((uint32_t)std::min<uint64_t>(clear, 65536)), dim3(kThreads),
+                     0, l.stream, d);
   const dim3 gc(l.npblocks), b(kThreads);
   switch (l.form * 2 + (l.walls ? 1 : 0)) {
     case 0: hipLaunchKernelGGL((k_tile_count<kFormF64, false>), gc, b, 0, l.stream, d, from); break;
