@@ -125,6 +125,9 @@ struct ObsRow {        // order-free sums of a block of particles (see k_obs_exa
   long long d[NV][3];  // digits of 40 bits, lowest first
   int32_t anchor[NV];  // bin of the top digit: its unit is 2^(40 anchor - 1023)
 };
+struct Vec3 {
+  double v[3];
+};
 struct ObsTotal {      // one sum of a box
   uint64_t lo[3];      // digits as 128-bit integers
   int64_t hi[3];
@@ -250,7 +253,7 @@ hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_
 // nv sums (4: momentum and energy; 1: relative energy, vmean) of a box: *total
 
 hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
-                            int nv, const double* vmean, ObsTotal* total);
+                            int nv, const Vec3& vmean, ObsTotal* total);
 hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
 // sel: box-local logical indices, overwritten; keys: 2 (mask + 1) entries of a

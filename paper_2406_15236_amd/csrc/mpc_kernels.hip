@@ -3485,16 +3485,12 @@ __device__ __forceinline__ void exact_move(long long (&v)[3], int from, int to) 
 // per, (blockIdx.x + 1) per) of the box into row blockIdx.x.
 template <int F, int NV>
 __global__ __launch_bounds__(kThreads) void k_obs_exact(Dev d, uint32_t box, uint32_t cur,
-                                                        const double* vmean, uint32_t per) {
+                                                        Vec3 vmean, uint32_t per) {
   __shared__ ObsRow<NV> s_row[kThreads / 64];
   BoxRef B = as_const(d.boxes)[box];
   const StatePtrs S = d.S[cur];
   const uint32_t i0 = blockIdx.x * per, i1 = min(i0 + per, B.np);
-  double V[3] = {0.0, 0.0, 0.0};
-  if (NV == 1) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) V[k] = vmean[3 * box + k];
-  }
+  const double V[3] = {vmean.v[0], vmean.v[1], vmean.v[2]};
   ExactSum acc[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) acc[k] = ExactSum{{0.0, 0.0, 0.0}, -1};
@@ -3934,7 +3930,7 @@ static uint32_t obs_exact_blocks(uint32_t np, uint32_t* per) {
 }
 template <int F, int NV>
 static void launch_obs_exact_form(const Dev& d, const Launch& l, uint32_t box, uint32_t np,
-                                  uint32_t cur, const double* vmean) {
+                                  uint32_t cur, const Vec3& vmean) {
   uint32_t per;
   const uint32_t rows = obs_exact_blocks(np, &per);
   hipLaunchKernelGGL((k_obs_exact<F, NV>), dim3(rows), dim3(kThreads), 0, l.stream, d, box, cur,
@@ -3942,7 +3938,7 @@ static void launch_obs_exact_form(const Dev& d, const Launch& l, uint32_t box, u
   hipLaunchKernelGGL(k_obs_total<NV>, dim3(1), dim3(kThreads * NV), 0, l.stream, d, rows);
 }
 hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
-                            int nv, const double* vmean, ObsTotal* total) {
+                            int nv, const Vec3& vmean, ObsTotal* total) {
   const bool all = nv == 4;
   switch (l.form) {
     case kFormF64:

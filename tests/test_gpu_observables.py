@@ -127,3 +127,22 @@ def test_energy_beyond_the_range_is_refused(mpc):
             with pytest.raises(mpc.MPCError) as e:
                 sim.observables()
             assert e.value.code == mpc.ESTATE
+
+
+def test_more_tiles_than_one_launch_of_wavefronts(mpc):
+    """2^26 rows of one cell: a wavefront each would be 2^32 threads, which one
+    launch does not take."""
+    box = dict(boxes()[0], L=(1, 8192, 8192), density=0.004, mbs=False)
+    print("case observables of 2^26 rows", flush=True)
+    with mpc.Sim(box) as sim:
+        sim.init_state(3)
+        o0 = sim.observables()
+        sim.step(2)
+        o1 = sim.observables()
+        v = sim.get_state()[1]
+    P, E, T = fsums(box, v)
+    assert abs(o1["E"] - E) <= 2.0**-52 * E and abs(o1["T"] - T) <= 2.0**-51 * T
+    # no thermostat: energy and momentum are kept, each by rounding of n terms
+    n = v.shape[1]
+    assert abs(o1["E"] - o0["E"]) < n * 2.0**-52 * E
+    assert np.abs(o1["P"] - o0["P"]).max() < n * 2.0**-52 * np.abs(v).max()
