@@ -146,7 +146,9 @@ typedef struct {
                              0 = plain periodic.  With MPC_WALLS_Z -> MPC_EINVAL  */
 } mpc_params;
 
-/* Observables of one box (FP64, compensated sums over the particles). */
+/* Observables of one box (FP64 sums, compensated or exact, over the particles;
+ * the same calls return the same bits, whatever order the steps leave the
+ * particles in). */
 typedef struct {
   uint64_t step;       /* number of completed steps                     */
   uint64_t n;          /* particles                                     */
@@ -229,8 +231,12 @@ int mpc_set_step(mpc_sim* s, uint64_t step);
  * Conversions: FP64 exact; FP32 rounds to nearest; SPLIT32 stores
  * cell = floor(x/a), offset = (float)(x/a - cell) (an offset that rounds to 1
  * moves to the next cell).  get returns the exact FP64 value of what is
- * stored.  Both synchronise and move the box through host staging buffers a
- * few million particles at a time.  get returns MPC_ESTATE if the stored
+ * stored.  Both synchronise.  The conversions run on the device, in staging
+ * of 48 n + 256 bytes there (at most 1 GiB, then in parts): up to 64 MiB stay
+ * with the handle until mpc_destroy, more is freed at return.  It comes from
+ * the workspace's device; when there is no memory, the part of the workspace
+ * that holds the run lists serves, and the next step sorts the particles by
+ * tile again (results do not change).  get returns MPC_ESTATE if the stored
  * logical indices are not a permutation of [0, n) (x and v then hold only
  * part of the state); set leaves the state unchanged on MPC_EINVAL (the
  * positions are checked before anything is copied). */

@@ -1,6 +1,6 @@
 // mpc_capi.cpp -- host side of the C ABI declared in include/mpc.h: parameter
-// validation, workspace planning, tile tables, step sequencing (direct
-// launches or a replayed hipGraph of one step), state transfer, observables.
+// validation, workspace planning, tile tables, step sequencing (direct launches
+// or replayed hipGraphs of several steps), state transfer, observables.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -530,9 +530,9 @@ int drop_graph(mpc_sim* s) {
   return MPC_OK;
 }
 
-// Steps per graph.  Without a wish of the caller 16: a graph of one step took
-// 21.0 us a step at 16^3, single launches 15.4, graphs of 10 steps 14.8 and of
-// 50 steps 14.2 (before the tiles of small boxes got shorter).
+// Steps per graph.  Without a wish of the caller 16: graphs of 2 steps take 13.5
+// us a step at 16^3, of 8 11.0, of 16 and single launches 10.6, of 50 10.3 (24^3
+// with the thermostat 18.2, 15.7, 15.3 and 15.0), and a graph spares the host.
 int64_t graph_chunk(const mpc_sim* s) { return s->graph_steps > 1 ? s->graph_steps : 16; }
 
 // One executable graph of `steps` consecutive steps (every step reads the

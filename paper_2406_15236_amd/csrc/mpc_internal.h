@@ -18,7 +18,7 @@ constexpr int kObsBad = 60;                 // their anchor after a term that is
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
 constexpr int kPartBlock = kThreads * 4;    // particles per block of per-particle kernels
-constexpr int kMaxRuns = 32;                // runs in a tile's table (more go to chains)
+constexpr int kMaxRuns = 32;                // most runs in a tile's table (more go to chains)
 constexpr int kGroups = 27;                 // next-step tiles of a pass: 3 per row, 9 rows
 constexpr int kTileBlock = kThreads * 4;    // tiles per block of the tile prefix
 constexpr uint32_t kTileOne = 16384;        // most tiles with a prefix in one launch
@@ -184,7 +184,8 @@ struct Dev {           // device pointers carved from the workspace
   unsigned long long* tcnt[3];  // particles << 32 | runs; sets in turn (Ctrl::tri)
   Run* runs[2];        // maxr per tile
   uint32_t* rhead[2];  // maxr chain heads per tile (tiles with more runs)
-  uint32_t* rnext[2];  // next slot of a chain, per slot
+  uint32_t* rnext[2];  // next slot of a chain, per slot; in a sort every
+                       // particle's tile and rank there
   uint32_t* toff;      // first output slot of each tile
   uint32_t* tblk;      // particles per block of tiles
   uint32_t maxr, ntile;

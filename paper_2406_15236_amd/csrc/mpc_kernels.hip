@@ -17,8 +17,8 @@
 //             step index only
 // and after the last of n steps
 //   advance : t += n, and the buffers in turn.
-// When the state was set from outside, a counting sort by tile puts it in this
-// order first.  Every kernel reads the step index and buffer from Ctrl and adds
+// When the state was set from outside, its tiling changed or its binning was
+// exported, a counting sort by tile puts it in this order first.  Every kernel reads the step index and buffer from Ctrl and adds
 // the number j of its step in the launch sequence, so that a captured graph of
 // steps can be replayed.
 #include <math.h>
@@ -624,8 +624,6 @@ struct Form<kFormF64> {
     const int ci[3] = {0, 0, 0};
     coords_of<W>(ci, xf, s, B, c, err, dle, le);
   }
-  // Lees-Edwards side of the collision cell: +1 below the lower z face,
-  // -1 above the upper one, else 0
   // x coordinate of the collision cell (as coords)
   __device__ static int cell_x(const P& p, const double (&s)[3], BoxRef B, double dle, bool le) {
     const double y = (double)p.x[0] + s[0];
@@ -639,6 +637,8 @@ struct Form<kFormF64> {
     }
     return wrap1(c, B.L[0]);
   }
+  // Lees-Edwards side of the collision cell: +1 below the lower z face,
+  // -1 above the upper one, else 0
   __device__ static int le_side(const P& p, double sz, BoxRef B) {
     const double cz = floor(p.x[2] + sz);
     return cz < 0.0 ? 1 : (cz >= B.Ld[2] ? -1 : 0);
