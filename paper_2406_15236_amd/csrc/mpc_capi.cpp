@@ -698,12 +698,10 @@ int sum_partials(mpc_sim* s, uint32_t pb0, uint32_t npb, double (&sum)[4]) {
   return MPC_OK;
 }
 
-// A sum's digits, rounded once.
-double exact_value(const ObsTotal& t) {
-  if (t.anchor < 0) return 0.0;
-  if (t.anchor >= kObsBad) return NAN;
-  __int128 d[3];
-  for (int j = 0; j < 3; ++j) d[j] = (__int128)t.hi[j] << 64 | t.lo[j];
+// A sum's digits under bin `anchor`, rounded once.
+double exact_value(__int128 (&d)[3], int anchor) {
+  if (anchor < 0) return 0.0;
+  if (anchor >= kObsBad) return NAN;
   // carries: d[2] 2^80 + low, 0 <= low < 2^80, in units of 2^(40 anchor - 1103)
   constexpr __int128 kMask = ((__int128)1 << 40) - 1;
   d[1] += d[0] >> 40;
@@ -718,11 +716,11 @@ double exact_value(const ObsTotal& t) {
   // |high| < 2^73: 55 bits and more with a sticky one decide the rounding
   double x;
   if (high == 0) {
-    x = ldexp((double)low, 40 * t.anchor - 1103);
+    x = ldexp((double)low, 40 * anchor - 1103);
   } else {
     const unsigned __int128 rest = low & (((unsigned __int128)1 << 26) - 1);
     x = ldexp((double)((unsigned __int128)high << 54 | low >> 26 | (rest != 0 ? 1u : 0u)),
-              40 * t.anchor - 1103 + 26);
+              40 * anchor - 1103 + 26);
   }
   return neg ? -x : x;
 }
@@ -731,10 +729,23 @@ double exact_value(const ObsTotal& t) {
 // not depend on the order of its slots.
 template <int NV>
 int sum_exact(mpc_sim* s, int32_t box, const Vec3& vmean, double* sum) {
-  ObsTotal t[NV];
-  HIPCHK(s, launch_obs_exact(s->dev, s->L, (uint32_t)box, s->boxes[box].np, s->cur, NV, vmean, t));
+  ObsResult<NV> r;
+  HIPCHK(s, launch_obs_exact(s->dev, s->L, (uint32_t)box, s->boxes[box].np, s->cur, vmean, &r));
   HIPCHK(s, hipStreamSynchronize(s->L.stream));
-  for (int k = 0; k < NV; ++k) sum[k] = exact_value(t[k]);
+  for (int k = 0; k < NV; ++k) {
+    __int128 d[3] = {0, 0, 0};
+    int top = -1;
+    if (!r.rows) {
+      top = r.total[k].anchor;
+      for (int j = 0; j < 3; ++j) d[j] = (__int128)r.total[k].hi[j] << 64 | r.total[k].lo[j];
+    }
+    for (uint32_t q = 0; q < r.rows; ++q) top = std::max(top, r.row[q].anchor[k]);
+    for (uint32_t q = 0; q < r.rows; ++q) {
+      const int by = top - r.row[q].anchor[k];
+      for (int j = 0; j + by < 3; ++j) d[j] += r.row[q].d[k][j + by];
+    }
+    sum[k] = exact_value(d, top);
+  }
   return MPC_OK;
 }
 

@@ -14,6 +14,7 @@ constexpr int kObsPass = 256;               // particles per pass of the observa
 constexpr int kObsSums = 128;               // sums left of the observables' partial sums
 constexpr int kObsList = 320;               // particles of an obs tile listed in LDS
 constexpr uint32_t kObsRows = 2048;         // most blocks of the order-free sums
+constexpr uint32_t kObsFew = 32;            // rows that the host adds itself
 constexpr int kObsBad = 60;                 // their anchor after a term that is not finite
 constexpr int kScanItems = 16;              // cells per thread in the scan kernels
 constexpr int kScanBlock = kThreads * kScanItems;
@@ -133,6 +134,12 @@ struct ObsTotal {      // one sum of a box
   int64_t hi[3];
   int32_t anchor, pad;
 };
+template <int NV>
+struct ObsResult {     // sums of a box as copied to the host
+  uint32_t rows;       // rows to add; 0: totals
+  ObsTotal total[NV];
+  ObsRow<NV> row[kObsFew];
+};
 
 // Particle records, one per storage slot (array of structures): the collide
 // gathers a particle with one or two 16-byte loads per 16 bytes of record, so
@@ -251,10 +258,10 @@ hipError_t launch_obs_order(const Dev& d, const Launch& l, uint32_t box, uint32_
                             uint32_t l0, uint32_t cur, uint32_t To, uint32_t* order);
 hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb, uint32_t cur,
                             const uint32_t* order);
-// nv sums (4: momentum and energy; 1: relative energy, vmean) of a box: *total
-
+// NV sums (4: momentum and energy; 1: relative energy, vmean) of a box
+template <int NV>
 hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
-                            int nv, const Vec3& vmean, ObsTotal* total);
+                            const Vec3& vmean, ObsResult<NV>* out);
 hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb);
 hipError_t launch_remove_mean(const Dev& d, const Launch& l, const double* vmean_dev);
 // sel: box-local logical indices, overwritten; keys: 2 (mask + 1) entries of a

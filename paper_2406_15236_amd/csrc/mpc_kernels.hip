@@ -3917,47 +3917,50 @@ hipError_t launch_obs_pass1(const Dev& d, const Launch& l, uint32_t pb0, uint32_
 
 // Blocks and particles of each, whole passes: eight blocks per compute unit for
 // the loads in flight (256^3 split, two passes of 0.9 ms: 1.9 ms with 1024
-// blocks and more, 2.3 with 512), fewer where a block would have less than four
-// passes.
+// blocks and more, 2.3 with 512); few enough for the host to add their rows where
+// that takes at most four passes a block (a launch less: 24x20x18 FP32 85 and 80
+// us a call).
 static uint32_t obs_exact_blocks(uint32_t np, uint32_t* per) {
   const uint64_t passes = ((uint64_t)np + kPartBlock - 1) / kPartBlock;
-  const uint64_t each = std::max<uint64_t>((passes + kObsRows - 1) / kObsRows,
-                                           std::min<uint64_t>(4, (passes + 2047) / 2048));
+  const uint64_t each =
+      passes <= 4 * kObsFew
+          ? (passes + kObsFew - 1) / kObsFew
+          : std::max<uint64_t>((passes + kObsRows - 1) / kObsRows, std::min<uint64_t>(4, (passes + 2047) / 2048));
   // whole numbers below 2^53 in every thread
   static_assert(((1ull << 31) / kPartBlock / kObsRows) * (kPartBlock / kThreads) <= 8192, "terms");
   *per = (uint32_t)(each * kPartBlock);
   return (uint32_t)((passes + each - 1) / each);
 }
 template <int F, int NV>
-static void launch_obs_exact_form(const Dev& d, const Launch& l, uint32_t box, uint32_t np,
-                                  uint32_t cur, const Vec3& vmean) {
+static hipError_t obs_exact_form(const Dev& d, const Launch& l, uint32_t box, uint32_t np,
+                                 uint32_t cur, const Vec3& vmean, ObsResult<NV>* out) {
   uint32_t per;
   const uint32_t rows = obs_exact_blocks(np, &per);
   hipLaunchKernelGGL((k_obs_exact<F, NV>), dim3(rows), dim3(kThreads), 0, l.stream, d, box, cur,
                      vmean, per);
-  hipLaunchKernelGGL(k_obs_total<NV>, dim3(1), dim3(kThreads * NV), 0, l.stream, d, rows);
-}
-hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
-                            int nv, const Vec3& vmean, ObsTotal* total) {
-  const bool all = nv == 4;
-  switch (l.form) {
-    case kFormF64:
-      if (all) launch_obs_exact_form<kFormF64, 4>(d, l, box, np, cur, vmean);
-      else launch_obs_exact_form<kFormF64, 1>(d, l, box, np, cur, vmean);
-      break;
-    case kFormF32:
-      if (all) launch_obs_exact_form<kFormF32, 4>(d, l, box, np, cur, vmean);
-      else launch_obs_exact_form<kFormF32, 1>(d, l, box, np, cur, vmean);
-      break;
-    default:
-      if (all) launch_obs_exact_form<kFormSplit, 4>(d, l, box, np, cur, vmean);
-      else launch_obs_exact_form<kFormSplit, 1>(d, l, box, np, cur, vmean);
-  }
+  out->rows = rows <= kObsFew ? rows : 0u;
+  if (!out->rows)
+    hipLaunchKernelGGL(k_obs_total<NV>, dim3(1), dim3(kThreads * NV), 0, l.stream, d, rows);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  return hipMemcpyAsync(total, d.obs, sizeof(ObsTotal) * (size_t)nv, hipMemcpyDeviceToHost,
-                        l.stream);
+  return out->rows ? hipMemcpyAsync(out->row, (ObsTotal*)d.obs + 4, sizeof(ObsRow<NV>) * rows,
+                                    hipMemcpyDeviceToHost, l.stream)
+                   : hipMemcpyAsync(out->total, d.obs, sizeof(ObsTotal) * NV, hipMemcpyDeviceToHost,
+                                    l.stream);
 }
+template <int NV>
+hipError_t launch_obs_exact(const Dev& d, const Launch& l, uint32_t box, uint32_t np, uint32_t cur,
+                            const Vec3& vmean, ObsResult<NV>* out) {
+  switch (l.form) {
+    case kFormF64: return obs_exact_form<kFormF64, NV>(d, l, box, np, cur, vmean, out);
+    case kFormF32: return obs_exact_form<kFormF32, NV>(d, l, box, np, cur, vmean, out);
+    default: return obs_exact_form<kFormSplit, NV>(d, l, box, np, cur, vmean, out);
+  }
+}
+template hipError_t launch_obs_exact<4>(const Dev&, const Launch&, uint32_t, uint32_t, uint32_t,
+                                        const Vec3&, ObsResult<4>*);
+template hipError_t launch_obs_exact<1>(const Dev&, const Launch&, uint32_t, uint32_t, uint32_t,
+                                        const Vec3&, ObsResult<1>*);
 
 hipError_t launch_obs_sums(const Dev& d, const Launch& l, uint32_t pb0, uint32_t npb) {
   hipLaunchKernelGGL(k_obs_sums, dim3(kObsSums), dim3(kThreads), 0, l.stream, d, pb0, npb);
