@@ -387,17 +387,19 @@ void build_tiles(mpc_sim* s) {
   s->tiles.clear();
   const uint64_t yb = (uint64_t)std::max(1, s->yblock);
   uint32_t tbase = 0;
-  for (size_t b = 0; b < s->boxes.size(); ++b) {
-    BoxDev& B = s->boxes[b];
-    const int T = s->tile_override ? s->tile_override
-                                   : auto_tile_cells(B.density, B.L[0], s->plan.rows);
-    B.T = (uint32_t)T;
-    B.ntx = (uint32_t)((B.L[0] + T - 1) / T);
+  for (BoxDev& B : s->boxes) {
+    B.T = (uint32_t)(s->tile_override ? s->tile_override
+                                      : auto_tile_cells(B.density, B.L[0], s->plan.rows));
+    B.ntx = ((uint32_t)B.L[0] + B.T - 1) / B.T;
     B.tbase = tbase;
+    tbase += (uint32_t)B.nlz * (uint32_t)B.L[1] * B.ntx;
+  }
+  s->tiles.reserve(tbase);  // once: growing it box by box copied all tiles so far
+  for (size_t b = 0; b < s->boxes.size(); ++b) {
+    const BoxDev& B = s->boxes[b];
+    const int T = (int)B.T;
     const uint64_t L0 = (uint64_t)B.L[0], L1 = (uint64_t)B.L[1], nz = (uint64_t)B.nlz;
     const uint64_t ntx = B.ntx;
-    tbase += (uint32_t)(nz * L1 * ntx);
-    s->tiles.reserve(tbase);
     auto add = [&](uint64_t cz, uint64_t cy, uint64_t tx) {
       const uint64_t row = cz * L1 + cy, cx = tx * (uint64_t)T;
       Tile t;
