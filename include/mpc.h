@@ -175,8 +175,8 @@ typedef struct mpc_sim mpc_sim;
 
 /* Bytes of device workspace needed for nbox boxes with parameters p[0..nbox).
  * The workspace holds the double-buffered particle state, the run lists of the
- * tiles (or, in their place, keys, permutation, cell counts and offsets for
- * mpc_get_binning), the cells' draws and small tables.  Errors: MPC_EINVAL,
+ * tiles (or, in their place or beside them, keys, permutation, cell counts and
+ * offsets for mpc_get_binning), the cells' draws and small tables.  Errors: MPC_EINVAL,
  * MPC_ERANGE. */
 int mpc_workspace_bytes(const mpc_params* p, int32_t nbox, size_t* bytes);
 
@@ -264,8 +264,9 @@ int mpc_get_particles(mpc_sim* s, int32_t box, const int64_t* idx, int64_t m, do
  * Keys are x-fastest: ((c_z' * L1) + c_y) * L0 + c_x with c_z' = c_z (periodic)
  * or c_z + 1 (walls).  Any pointer may be NULL.  MPC_EINVAL if no step has
  * run since the state was set.  The binning is formed from the last step's
- * input on the first call after a step; the next step then sorts the particles
- * by tile again (results do not change). */
+ * input on the first call after a step; in boxes of more than some 90 000
+ * particles in all the next step then sorts the particles by tile again (results
+ * do not change). */
 int mpc_get_binning(mpc_sim* s, int32_t box, uint32_t* key, uint32_t* perm, uint32_t* offset);
 
 /* Autotuner: choose the collide tiling (cells per tile, persistent grid size,

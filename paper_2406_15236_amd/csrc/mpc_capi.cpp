@@ -23,6 +23,8 @@ constexpr uint64_t kMaxIndex = 0x7fffffffull;  // particle and cell indices stay
 constexpr int64_t kStateChunk = int64_t(1) << 22;  // particles per host staging chunk
 constexpr size_t kKeepStage = (size_t)64 << 20;    // largest device staging a handle keeps
 constexpr size_t kMaxStage = (size_t)1 << 30;      // and largest of one call
+constexpr size_t kSmallCopy = (size_t)256 << 10;   // a state read back in one copy
+constexpr size_t kOwnExport = (size_t)1 << 20;     // largest binning export with memory of its own
 constexpr int kMinTileCells = 4;
 constexpr int32_t kMaxGraphSteps = 1000;  // steps captured in one graph
 static_assert(MPC_MAX_CELL_PARTICLES == kTileCap, "the ABI's cell limit is one collide pass");
@@ -69,7 +71,8 @@ struct Plan {
   uint64_t max_tiles = 0, npblocks = 0;
   uint64_t rows = 0;      // rows of cells in all boxes
   uint32_t drawb = 0;     // cells per draw block
-  size_t off_shared = 0, shared = 0;  // run lists or binning export
+  size_t off_shared = 0, shared = 0;  // run lists and binning export
+  bool own_export = false;            // the export does not take the run lists' memory
   uint64_t run_pool = 0;  // runs of all tiles' tables per state buffer
   size_t charge = 0;      // bytes the static scratch is checked against
   size_t rec = 0;  // bytes per particle record
@@ -222,9 +225,10 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
     P.off_rec[s] = take(P.rec * P.ntot);
     P.off_id[s] = P.split ? 0 : take(4 * P.ntot);
   }
-  // the binning export and the run lists of the tiles share their memory:
-  // the export is formed from the last step's input when it is asked for, and
-  // the next step then sorts the state by tile again
+  // the binning export and the run lists of the tiles share their memory: the
+  // export is formed from the last step's input when it is asked for, and the
+  // next step then sorts the state by tile again.  That sort is most of a step of
+  // a small box (3^3: 60 us), whose export has its own memory
   const size_t shared0 = off;
   P.off_key = take(4 * P.ntot);
   P.off_perm = take(4 * P.ntot);
@@ -233,7 +237,8 @@ int make_plan(const mpc_params* p, int32_t nbox, Plan& P, std::string* why) {
   P.off_offset = take(4 * (P.cpad + 1));
   P.off_scan = take(4 * (size_t)P.nscan);
   const size_t shared1 = off;
-  off = shared0;
+  P.own_export = shared1 - shared0 <= kOwnExport;
+  if (!P.own_export) off = shared0;
   // a tiling with more tiles than the automatic one has shorter run tables,
   // of at least one run a tile
   P.run_pool = std::max<uint64_t>(tiles * maxr, P.max_tiles);
@@ -1231,10 +1236,20 @@ int mpc_get_state(mpc_sim* s, int32_t box, double* x, double* v, int64_t n) {
     double* dv = st.data + 3 * m;
     HIPCHK(s, launch_state_out(s->L, s->dev.S[s->cur], B.pbase, B.np, (uint32_t)i0, dx, dv,
                                (uint32_t)m, a, st.flag));
-    if ((rc = stage_copy(s, dx, dv, x, v, n, i0, m, false))) return rc;
     uint32_t bad = 0;
-    HIPCHK(s, hipMemcpyAsync(&bad, st.flag, sizeof bad, hipMemcpyDeviceToHost, s->L.stream));
-    HIPCHK(s, hipStreamSynchronize(s->L.stream));
+    const size_t arr = sizeof(double) * 3 * (size_t)m;
+    if (m == n && 2 * arr <= kSmallCopy) {  // flag and arrays lie one after the other
+      std::vector<char> all(256 + 2 * arr);
+      HIPCHK(s, hipMemcpyAsync(all.data(), st.flag, all.size(), hipMemcpyDeviceToHost, s->L.stream));
+      HIPCHK(s, hipStreamSynchronize(s->L.stream));
+      memcpy(&bad, all.data(), sizeof bad);
+      memcpy(x, all.data() + 256, arr);
+      memcpy(v, all.data() + 256 + arr, arr);
+    } else {
+      if ((rc = stage_copy(s, dx, dv, x, v, n, i0, m, false))) return rc;
+      HIPCHK(s, hipMemcpyAsync(&bad, st.flag, sizeof bad, hipMemcpyDeviceToHost, s->L.stream));
+      HIPCHK(s, hipStreamSynchronize(s->L.stream));
+    }
     if (bad) {
       s->err = "logical particle indices are not a permutation";
       return MPC_ESTATE;
@@ -1344,7 +1359,8 @@ int mpc_get_binning(mpc_sim* s, int32_t box, uint32_t* key, uint32_t* perm, uint
   // logical order before that step
   const StatePtrs& Sin = s->dev.S[s->cur ^ 1u];
   if (!s->binning_ready) {
-    s->keys_valid = false;  // the export takes the memory of the run lists
+    // the export takes the memory of the run lists
+    if (!s->plan.own_export) s->keys_valid = false;
     HIPCHK(s, launch_binning(s->dev, s->L, Sin, s->step - 1));
     HIPCHK(s, launch_canon_perm(s->dev, s->L, Sin));
     s->binning_ready = true;

@@ -979,7 +979,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_down(Dev d, uint32_t nblk) {
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) sum += v[k];
   uint32_t total;
-  uint32_t run = d.scan_blk[blockIdx.x] + block_exclusive_scan(sum, s_w, total);
+  uint32_t run = (nblk > 1 ? d.scan_blk[blockIdx.x] : 0u) + block_exclusive_scan(sum, s_w, total);
   uint4* o4 = (uint4*)(d.offset + base);
 #pragma unroll
   for (int k = 0; k < kScanItems / 4; ++k) {
@@ -3736,9 +3736,11 @@ hipError_t launch_binning(const Dev& d, const Launch& l, const StatePtrs& S, uin
     case 4: hipLaunchKernelGGL((k_key_hist<kFormSplit, false>), g, b, 0, l.stream, d, S, t); break;
     default: hipLaunchKernelGGL((k_key_hist<kFormSplit, true>), g, b, 0, l.stream, d, S, t); break;
   }
-  hipLaunchKernelGGL(k_scan_reduce, dim3(l.nscan), dim3(kThreads), 0, l.stream, d.hist,
-                     d.scan_blk);
-  hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, l.stream, d.scan_blk, l.nscan);
+  if (l.nscan > 1) {
+    hipLaunchKernelGGL(k_scan_reduce, dim3(l.nscan), dim3(kThreads), 0, l.stream, d.hist,
+                       d.scan_blk);
+    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, l.stream, d.scan_blk, l.nscan);
+  }
   hipLaunchKernelGGL(k_scan_down, dim3(l.nscan), dim3(kThreads), 0, l.stream, d, l.nscan);
   const uint32_t blocks = (uint32_t)((l.ntot + kThreads * 4 - 1) / (kThreads * 4));
   hipLaunchKernelGGL(k_scatter, dim3(blocks), dim3(kThreads), 0, l.stream, d.key, d.rank,

@@ -41,6 +41,8 @@ BOXES = {
     "periodic": [box_of((23, 11, 9)), box_of((5, 4, 3), seed=8), box_of((40, 3, 2), density=0.3)],
     "walls": [box_of((17, 9, 8), walls=True, g=(1e-3, 0.0, 0.0)),
               box_of((33, 5, 4), walls=True, seed=9)],
+    # the binning export in the run lists' memory
+    "larger": [box_of((44, 36, 9), mbs=False), box_of((9, 8, 7), mbs=False, seed=2)],
 }
 
 

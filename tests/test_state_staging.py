@@ -111,6 +111,10 @@ def test_staging_inside_the_workspace(record, form, L):
             if base:
                 assert lo <= dev and dev + n <= hi
                 covered[base[0]] += n
+        if into == 0 and 2 * size <= 256 << 10:  # one copy of flag and arrays
+            assert [(lo <= e[3] and e[3] + e[4] <= hi, e[4]) for e in c["events"] if
+                    e[4] > 4096 or e[4] == 256 + 2 * size][-1] == (True, 256 + 2 * size)
+            continue
         passes = 1 if into == 0 else max(1, covered[c["x"]] // size)
         assert set(covered.values()) == {passes * size} and passes <= 2
 
